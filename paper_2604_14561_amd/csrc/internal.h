@@ -82,6 +82,22 @@ inline void with_policy(bool nt_ld, bool nt_st, F&& f) {
     }
 }
 
+// Division of an index by a launch constant: multiply-high by ceil(2^32 / d), exact while n * d < 2^32 (the host
+// makes sure of it for the largest n of every use, or takes the plain division); d = 1 has no magic.
+struct Divisor {
+    uint32_t d, magic;
+};
+inline Divisor make_divisor(uint32_t d) {
+    Divisor f{d ? d : 1u, 0u};
+    if (f.d > 1u) f.magic = (uint32_t)((((uint64_t)1 << 32) + f.d - 1) / f.d);
+    return f;
+}
+template <bool MAGIC>
+__device__ __forceinline__ uint32_t div_by(uint32_t n, const Divisor& f) {
+    if (!MAGIC) return n / f.d;
+    return f.d == 1u ? n : __umulhi(n, f.magic);
+}
+
 // ---- device helpers -------------------------------------------------------
 
 // One 16-byte vector (8 bf16), the unit every kernel moves; a native vector type, so the
@@ -164,8 +180,24 @@ __device__ __forceinline__ bool vec_changed_double(const vec16& c, const vec16& 
     return changed;
 }
 
+// The same decision on bit patterns: the largest |d| of a vector as an unsigned number (NaN above infinity above all numbers);
+// larger than tau_bits: changed; equal to tie_bits and nothing changed: compare again in double.
+__device__ __forceinline__ uint32_t vec_largest_difference(const vec16& c, const vec16& p) {
+    const uint32_t cw[4] = {c.x, c.y, c.z, c.w};
+    const uint32_t pw[4] = {p.x, p.y, p.z, p.w};
+    uint32_t largest = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        largest = max(largest, __float_as_uint(bf16_lo(cw[i]) - bf16_lo(pw[i])) & 0x7fffffffu);
+        largest = max(largest, __float_as_uint(bf16_hi(cw[i]) - bf16_hi(pw[i])) & 0x7fffffffu);
+    }
+    return largest;
+}
+
 struct Thresholds {
     float tau, tau_s, tau_tie;   // see vec_suspect / vec_changed
+    uint32_t tau_bits, tie_bits; // see vec_largest_difference (tie_bits: a pattern no |d| has when tau is 0)
+    int32_t always;              // a negative or NaN threshold: everything counts as changed
 };
 
 inline Thresholds make_thresholds(float tau) {
@@ -173,6 +205,9 @@ inline Thresholds make_thresholds(float tau) {
     th.tau = tau;
     th.tau_s = tau > 0.f ? tau : (tau == 0.f ? __builtin_bit_cast(float, 1u) : tau);
     th.tau_tie = tau > 0.f ? tau : __builtin_nanf("");
+    th.always = !(tau >= 0.f);
+    th.tau_bits = th.always ? 0u : __builtin_bit_cast(uint32_t, tau) & 0x7fffffffu;
+    th.tie_bits = tau > 0.f ? th.tau_bits : 0xffffffffu;
     return th;
 }
 

@@ -55,17 +55,6 @@ struct UnpackSource {
     int recv_major;
 };
 
-// Division of an index by a launch constant: multiply-high by ceil(2^32 / d), exact while n * d < 2^32 (the host
-// checks the largest n of every use and falls back to the hardware-free plain division otherwise); d = 1 has no magic.
-struct Divisor {
-    uint32_t d, magic;
-};
-template <bool MAGIC>
-__device__ __forceinline__ uint32_t div_by(uint32_t n, const Divisor& f) {
-    if (!MAGIC) return n / f.d;
-    return f.d == 1u ? n : __umulhi(n, f.magic);
-}
-
 // Workgroup (t, part): verdict over vectors [part * share, (part + 1) * share) of tile t's index space
 // g = s * seg8 + v (S segments of seg8 vectors), written to byte `part` of the tile's flag word.
 // FROM_BUF: the current values are read from the exchange buffer (and written to their place in the
@@ -366,8 +355,7 @@ static int select_launch(int32_t S, int32_t N, int32_t W, int32_t tile_tokens,
     // need every tensor below 4 GiB
     bool magic = (uint64_t)S * sh.slab8 * 16u < ((uint64_t)1 << 32);
     auto divisor = [&](uint32_t d, uint64_t max_n) {
-        Divisor f{d ? d : 1u, 0u};
-        if (f.d > 1u) f.magic = (uint32_t)((((uint64_t)1 << 32) + f.d - 1) / f.d);
+        const Divisor f = make_divisor(d);
         if (max_n * f.d >= ((uint64_t)1 << 32)) magic = false;
         return f;
     };
