@@ -1,0 +1,10 @@
+// The projection's main kernel writing both, Q and K normalised and rotated.
+#include "gemm_kernel.h"
+
+namespace cocodiff {
+
+#define ENTRY(NI, NJ) (const void*)qkv_gemm_direct_kernel<NI, NJ, OUT_FUSED>,
+const void* const kFusedKernels[] = {COCODIFF_FUSED_TILES(ENTRY)};
+#undef ENTRY
+
+}  // namespace cocodiff
