@@ -3,22 +3,18 @@
 // power-limited part it sustains 1.91 PFLOP/s at 0.70 pJ/flop in a register-only loop against 1.72 PFLOP/s at
 // 0.77 pJ/flop for v_mfma_f32_32x32x16_bf16, for the same LDS traffic per flop (a wavefront's tile decides that).
 //
-// Workgroup tile (tokens x features): 256 x 256, 288 x 192 or 192 x 192 -- the host takes the one with the fewest
-// rounds of tiles over the compute units, weighted by a measured per-flop cost (plan_launch).  K step 64: a row
-// segment of either operand is one whole 128-byte line (half lines halve the L1 fill rate).  W rides the MFMA "A"
-// side, so an accumulator lane holds four consecutive features of one token.  Both operands are K-contiguous; LDS
-// tiles keep rows contiguous and store 16-byte column c of row r at column c ^ swz(r), which makes the 128-bit
-// fragment reads bank-conflict free.
-//
-// Main kernel (K a multiple of 64, at least three steps): global -> LDS directly (no staging registers) through two
-// rings, three slots for X tiles and two for W tiles (160 KB for the 256 x 256 tile).  Eight wavefronts, four along
-// the features x two along the tokens, two per SIMD, so one can multiply while the other waits for LDS, memory or
-// the barrier.  General kernel (any K that is a multiple of 8): global -> registers -> LDS, zero-filled K tail.
-// The epilogue rounds to bf16, transposes through the (now idle) LDS and writes 16-byte vectors: rows of [N][D],
-// row pieces straight into their chunks of the exchange buffer, or row pieces of the head-parallel tensor -- or, in
-// the fused form (tiles 256 features wide, so that they hold whole heads), it first RMS-normalises and rotates Q and K
-// on the fp32 accumulators (paper Section II-B's norm and RoPE, one rounding in all) and writes both the chunks and
-// the head-parallel tensor.
+// Main kernel (gemm_kernel.h; K a multiple of 64, at least three steps): K steps of 64 -- a row segment of either operand is
+// one whole 128-byte line (half lines halve the L1 fill rate) -- go from global memory to LDS directly through two rings that
+// turn from tile to tile of a persistent workgroup; four wavefronts, one per SIMD.  W rides the MFMA "A" side, so an
+// accumulator lane holds consecutive features of one token.  Both operands are K-contiguous; LDS tiles keep rows contiguous
+// and store 16-byte column c of row r at column c ^ swz(r), which makes the 128-bit fragment reads bank-conflict free.  Its
+// epilogue rounds to bf16 and stores 16-byte vectors from registers: rows of [N][D], row pieces straight into their chunks of
+// the exchange buffer, or row pieces of the head-parallel tensor -- or, in the fused form (tiles 128 or 256 features wide, so
+// that they hold whole heads), it first RMS-normalises and rotates Q and K on the fp32 accumulators (paper Section II-B's norm
+// and RoPE, one rounding in all) and writes both the chunks and the head-parallel tensor.
+// The tile (tokens x features) is chosen among the built shapes by an estimate of the launch's clocks (plan_launch).
+// General kernel (any K that is a multiple of 8): global -> registers -> LDS, zero-filled K tail, 256 x 256 tiles, out through
+// a transpose in LDS.
 #include <algorithm>
 #include <initializer_list>
 
@@ -27,10 +23,9 @@
 namespace cocodiff {
 
 constexpr int BM = 256;          // tokens and features per workgroup tile of the general kernel
-constexpr int kTileBytes = BM * BK * 2;                  // one operand tile of one K step of the fallback kernel: 32 KB
+constexpr int kTileBytes = BM * BK * 2;                  // one operand tile of one K step of the general kernel: 32 KB
 constexpr int kStageBytes = 2 * kTileBytes;              // 64 KB
 constexpr int kLdsBytes = 2 * kStageBytes;               // 128 KB
-
 
 // Byte offset of 16-byte column c of row r inside a [rows][64] bf16 LDS tile.
 __device__ __forceinline__ uint32_t lds_off(uint32_t row, uint32_t c) { return row * 128u + ((c ^ swz(row)) << 4); }
@@ -249,7 +244,10 @@ static const TileKernel* tile_shapes(bool whole_heads, int* count) {
     return whole_heads ? fused : plain;
 }
 
-// Clocks of one workgroup's tile (measured; see plan_launch).
+// Clocks of one workgroup's tile, fitted to the built shapes: a K step is 17.2 clocks per MFMA of a wavefront and 60 for its
+// barrier, or the operands' way through L2 (40 bytes per clock and unit) where that is longer; then the epilogue.  Against all
+// shapes at 256 .. 20736 tokens x 256 .. 3072 features, one to three weights, both forms (45 launches), the shape of least
+// estimate is the fastest in 28 and within 3 % in all but one (2304 x 3072, three weights: 105.1 us for 100.6).
 static double tile_clocks(const TileKernel& t, int32_t D, bool whole_heads) {
     const double mfmas = (t.bm / 32) * (t.bn / 32) * 2.0, operand_bytes = (t.bm + t.bn) * BK * 2.0;
     const double step = std::max(mfmas * 17.2 + 60.0, operand_bytes / 40.0);
@@ -487,7 +485,8 @@ extern "C" int cocodiff_qkv_proj_fused(const cocodiff_shape* shape, const cocodi
     return proj_launch(shape, x, wq, wk, wv, qbuf, kbuf, vbuf, OUT_FUSED, slot_order, stream, &f);
 }
 
-// Flag records of the projection that flags V: 16 bytes per 16-token tile, one byte per 256-feature tile of V.
+// Flag records of the projection that flags V: 16 bytes per 16-token tile, one byte per feature tile of V (16 at most; plan_launch
+// sees to it with narrower tiles).
 static bool flags_in_projection(const cocodiff_shape* shape, int32_t tile_tokens) {
     return tile_tokens == 16 && (shape->D + 255) / 256 <= 16;
 }

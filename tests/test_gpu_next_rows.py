@@ -1121,3 +1121,78 @@ def test_vmajor_token_loop_over_denoising_steps(oracle):
         assert np.array_equal(to_host_bits(cache_dev), cache_host), step
         if k == Ns:                                                     # warm-up and every 10th step: full update
             assert np.array_equal(cache_host, cur)
+
+
+# Every tile shape of the projection, on ragged sizes, P = H ranks (a token tile's chunk changes inside a workgroup tile); the
+# second line of a shape gives its workgroups more than one tile each, so that the operand rings turn from tile to tile.
+@gpu
+@pytest.mark.parametrize("bm,bn,N,H,n_tensors", [
+    (256, 256, 8176, 7, 3), (256, 256, 16464, 7, 3), (288, 192, 11008, 4, 3), (288, 192, 21840, 5, 3),
+    (192, 192, 7200, 5, 3), (192, 192, 14480, 5, 3), (128, 256, 8208, 3, 3), (128, 256, 10864, 7, 3),
+    (256, 128, 5440, 5, 3), (256, 128, 12160, 5, 3), (96, 256, 48, 3, 1), (96, 256, 10976, 7, 3), (128, 128, 2720, 5, 3),
+    (96, 192, 3600, 5, 3), (96, 192, 8080, 5, 3), (96, 128, 5520, 5, 1), (96, 128, 12160, 4, 3), (64, 192, 4048, 11, 1),
+    (64, 128, 3280, 5, 1), (64, 64, 1680, 5, 1), (32, 64, 80, 5, 1),
+])
+def test_proj_every_tile_shape(oracle, bm, bn, N, H, n_tensors):
+    """[N][D] against the fp64 product on rows around the tiles' edges, the two other layouts bit-identical to it, nothing
+    written past the end.  (Tolerance: the projection's, one rounding to bf16.)"""
+    import torch
+    from synth import f32_to_bf16_bits
+    d, D, G = 64, 64 * H, 512
+    sh = cd.Shape.make(N, D, H, d, H)
+    plan = cd.qkv_proj_plan(sh, n_tensors)
+    print(f"proj {N}x{D}, {n_tensors} weights: {plan}", flush=True)
+    if plan["compute_units"] == 256:
+        assert (plan["tile_tokens"], plan["tile_features"]) == (bm, bn)
+    rng = np.random.default_rng(N * 31 + D)
+    x = f32_to_bf16_bits(rng.standard_normal((N, D), dtype=np.float32))
+    w = [f32_to_bf16_bits(rng.standard_normal((D, D), dtype=np.float32) * np.float32(D ** -0.5)) for _ in range(n_tensors)]
+    xd, wd = to_dev(x), [to_dev(a) for a in w] + [None] * (3 - n_tensors)
+    raw = [[torch.full((N * D + G,), 0x5A5A, dtype=torch.int16, device="cuda:0") if a is not None else None for a in wd] for _ in range(3)]
+    out = [[t[:N * D] if t is not None else None for t in r] for r in raw]
+    cd.qkv_proj(sh, xd, *wd, *out[0])
+    cd.qkv_proj_pack(sh, xd, *wd, *out[1], cd.SEND_MAJOR)
+    cd.qkv_proj_hs(sh, xd, *wd, *out[2])
+    _sync()
+    edges = np.concatenate([np.arange(e - 16, e + 16) for e in (16, bm, N // bm * bm, N - 16)])
+    ids = np.unique(np.clip(np.concatenate([edges, rng.integers(0, N, 64)]), 0, N - 1))
+    packed = dev_empty((N * D,))
+    for i in range(n_tensors):
+        got = to_host_bits(out[0][i]).reshape(N, D)
+        assert_float_parity(got[ids], oracle.qkv_proj(x[ids], w[i]), f"proj tile {bm}x{bn} weight {i}")
+        cd.a2a_pack(sh, out[0][i], packed, cd.SEND_MAJOR)
+        _sync()
+        assert torch.equal(out[1][i], packed)
+        assert np.array_equal(to_host_bits(out[2][i]).reshape(H, N, d), got.reshape(N, H, d).transpose(1, 0, 2))
+        for r in raw:
+            assert bool((r[i][N * D:] == 0x5A5A).all().cpu())
+
+
+@gpu
+@pytest.mark.parametrize("bm,bn,N,H,d", [
+    (256, 256, 20496, 7, 64), (256, 256, 13680, 5, 128), (256, 256, 19056, 1, 256), (224, 256, 16464, 7, 64),
+    (224, 256, 18160, 5, 128), (224, 256, 16336, 1, 256), (192, 256, 14480, 5, 64), (192, 256, 14496, 3, 128),
+    (192, 256, 13616, 1, 256), (160, 256, 21792, 3, 64), (160, 256, 8720, 5, 128), (160, 256, 10896, 1, 256),
+    (128, 256, 10864, 7, 64), (128, 256, 16368, 3, 128), (128, 256, 8176, 1, 256), (96, 256, 5520, 3, 64),
+    (96, 256, 3600, 3, 128), (96, 256, 5456, 1, 256), (64, 256, 48, 3, 64), (64, 256, 5408, 2, 128), (64, 256, 16, 1, 256),
+    (256, 128, 10960, 5, 64), (256, 128, 10896, 3, 128), (128, 128, 10800, 5, 64), (128, 128, 10800, 3, 128),
+    (96, 128, 1840, 5, 64), (96, 128, 2720, 2, 128), (64, 128, 1040, 5, 64), (64, 128, 1376, 2, 128), (32, 128, 80, 5, 64),
+    (32, 128, 48, 3, 128),
+])
+def test_proj_fused_every_tile_shape(oracle, bm, bn, N, H, d):
+    """Two or one heads of a wavefront, and heads that two wavefronts share; pairs in fours (heads of 128) and not (64, 256)."""
+    from synth import f32_to_bf16_bits
+    D = H * d
+    plan = cd.qkv_proj_plan(cd.Shape.make(N, D, H, d, H), 3, whole_heads=True)
+    if plan["compute_units"] == 256:
+        assert (plan["tile_tokens"], plan["tile_features"]) == (bm, bn), plan
+    rng = np.random.default_rng(N * 31 + D)
+    inp = {"X": f32_to_bf16_bits(rng.standard_normal((N, D), dtype=np.float32))}
+    for w in ("Wq", "Wk", "Wv"):
+        inp[w] = f32_to_bf16_bits(rng.standard_normal((D, D), dtype=np.float32) * np.float32(D ** -0.5))
+    for g_ in ("gamma_q", "gamma_k"):
+        inp[g_] = f32_to_bf16_bits((1.0 + 0.1 * rng.standard_normal(d)).astype(np.float32))
+    edges = np.concatenate([np.arange(e - 16, e + 16) for e in (16, bm, N // bm * bm, N - 16)])
+    ids = np.unique(np.clip(np.concatenate([edges, rng.integers(0, N, 64)]), 0, N - 1))
+    pairs = (d // 4, d // 4) if d == 128 else (d // 4 - 1, d // 4 + 1)
+    _fused_case(oracle, N, D, H, d, H, (16, N // 16), pairs, inp, ids, what=f"fused tile {bm}x{bn}")
