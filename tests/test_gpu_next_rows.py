@@ -1196,3 +1196,34 @@ def test_proj_fused_every_tile_shape(oracle, bm, bn, N, H, d):
     ids = np.unique(np.clip(np.concatenate([edges, rng.integers(0, N, 64)]), 0, N - 1))
     pairs = (d // 4, d // 4) if d == 128 else (d // 4 - 1, d // 4 + 1)
     _fused_case(oracle, N, D, H, d, H, (16, N // 16), pairs, inp, ids, what=f"fused tile {bm}x{bn}")
+
+
+@gpu
+@pytest.mark.parametrize("values", ["equal", "two_levels", "clusters", "all_bits", "neighbours"])
+@pytest.mark.parametrize("N", [1, 63, 65, 1024, 1025, 8192, 8200, 32768, 32769])
+def test_topk_key_ranges_and_lengths(oracle, N, values):
+    """Ranges of keys from one value to all finite floats (one to three histogram passes, a bin taken whole or in part, at the
+    edges of wavefronts, of the workgroup and of the LDS key cache): exactly the oracle's list, nothing behind it."""
+    import torch
+    rng = np.random.default_rng(N)
+    many = rng.random(N) < 0.3
+    if values == "equal":
+        m = np.full(N, 0.75, dtype=np.float32)
+    elif values == "two_levels":
+        m = np.where(many, 5.0, -3.0).astype(np.float32)
+    elif values == "clusters":
+        m = (np.where(many, 1200.0, 5.0) * (1.0 + 0.02 * rng.standard_normal(N))).astype(np.float32)
+    elif values == "all_bits":
+        m = rng.integers(0, 2 ** 32, size=N, dtype=np.uint32).view(np.float32)
+        m = np.where(np.isfinite(m), m, np.float32(0)).astype(np.float32)
+    else:       # consecutive floats
+        m = (rng.integers(0, 3 * 2048, size=N, dtype=np.uint32) + np.uint32(0x3F800000)).view(np.float32)
+    md = torch.from_numpy(m).to("cuda:0")
+    idx, n_act = dev_empty((N,), "i32"), dev_empty((1,), "i32")
+    for k in sorted({0, 1, N // 3, int(many.sum()), max(0, N - 1), N}):
+        idx.fill_(-1)
+        cd.vmajor_topk(1, N, md, k, idx, n_act)
+        _sync()
+        got = idx.cpu().numpy()
+        assert int(n_act.cpu()[0]) == k and np.all(got[k:] == -1)
+        assert np.array_equal(got[:k], oracle.topk_active(m.astype(np.float64), k)), (N, values, k)
