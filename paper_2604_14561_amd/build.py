@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import glob
 import os
+import re
 import subprocess
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
@@ -28,14 +29,50 @@ def _run(cmd: list) -> str:
     return err
 
 
+def accumulator_accesses(assembly: str) -> list:
+    """Instructions of the projection's main kernels (device assembly of gemm_*.hip) that touch an accumulation register
+    outside inline assembly.  Those kernels keep their accumulators in a0 .. by number, unknown to the compiler; nothing in the
+    language forbids it a short-lived copy there, so what it made is looked at: (line number, instruction) of each."""
+    found, kernel, inline = [], False, False
+    for n, line in enumerate(assembly.splitlines(), 1):
+        if re.match(r"[A-Za-z_]\w*:", line):
+            kernel = "qkv_gemm_direct_kernel" in line
+        elif "#ASMSTART" in line:
+            inline = True
+        elif "#ASMEND" in line:
+            inline = False
+        elif kernel and not inline and re.match(r"\t[a-z]", line):
+            instruction = line.split(";")[0].strip()
+            if re.search(r"[\s,\[]a(\d+\b|\[)", instruction):
+                found.append((n, instruction))
+    return found
+
+
+def _check_assembly(source: str, obj: str) -> None:
+    path = obj[:-len(".hip.o")] + "-hip-amdgcn-amd-amdhsa-gfx950.s"
+    with open(path) as f:
+        assembly = f.read()
+    if "qkv_gemm_direct_kernel" in assembly:
+        found = accumulator_accesses(assembly)
+        if found:
+            raise RuntimeError(f"{os.path.basename(source)}: the compiler uses accumulation registers of its own in "
+                               f"{len(found)} instructions, the first {found[0][1]!r}: they hold the projection's accumulators")
+
+
+def _compile(cmd: list) -> str:
+    err = _run(cmd)
+    _check_assembly(cmd[-3], cmd[-1])
+    return err
+
+
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     jobs = min(len(SOURCES), int(os.environ.get("MAX_JOBS", "0")) or os.cpu_count() or 1, 8)
     with tempfile.TemporaryDirectory() as tmp, ThreadPoolExecutor(jobs) as pool:
         objects = [os.path.join(tmp, os.path.basename(s) + ".o") for s in SOURCES]
-        cmds = [[hipcc] + HIPCC_FLAGS + ["-c", s, "-o", o] for s, o in zip(SOURCES, objects)]
+        cmds = [[hipcc] + HIPCC_FLAGS + ["-save-temps=obj", "-c", s, "-o", o] for s, o in zip(SOURCES, objects)]
         cmds[:] = sorted(cmds, key=lambda c: "gemm_fused" not in c[-3])      # the longest first
-        for err in pool.map(_run, cmds):
+        for err in pool.map(_compile, cmds):
             if verbose and err.strip():
                 print(err)
         _run([hipcc] + HIPCC_FLAGS + ["-shared", "-o", LIB_PATH] + objects)

@@ -98,8 +98,10 @@ __device__ __forceinline__ TileWalk tiles_of_block(const GemmArgs& a) {
 // The accumulators live in the accumulation registers a0 .. a255 by number, and the compiler does not know them: accumulator
 // tile (i, j) is a[4 (i NJ + j)] and the three behind it.  (Left to the compiler, it moves accumulators between the two
 // register files and to scratch memory -- at 256 of them the loops over K steps and tiles carry 128 moves each way per step.)
-// What the compiler may not do is keep something of its own there: reserve_accumulators in every K step and every token
-// tile of the epilogue tells it that all of them change.  The waits that these instructions need are in the code too: an MFMA
+// reserve_accumulators in every K step and every token tile of the epilogue tells it that all of them change, so it keeps
+// nothing of its own there from one of these places to the next.  That does not forbid a copy that lives between two of them: the
+// build reads the kernels' assembly and fails on any use of these registers that is not written here (build.py,
+// accumulator_accesses).  The waits that these instructions need are in the code too: an MFMA
 // result is read only behind mfma_results_ready(), and many instructions lie between clearing an accumulator and the next MFMA
 // on it.
 #define COCODIFF_ACC_0_63 \

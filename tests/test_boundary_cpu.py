@@ -205,3 +205,18 @@ def test_missing_library_fails_loudly(monkeypatch, tmp_path):
     assert "libcocodiff.so" in str(err.value)
     monkeypatch.undo()
     assert B.lib() is not None
+
+
+def test_build_refuses_accumulation_registers_of_the_compilers_own():
+    """The projection's kernels own a0 .. by number: an access that the compiler made is found, one in inline assembly, in
+    another kernel, in a comment or a name that only looks alike is not."""
+    from paper_2604_14561_amd.build import accumulator_accesses
+    ours = "_ZN8cocodiff22qkv_gemm_direct_kernelILi8ELi8ELi3EEEvNS_8GemmArgsE:\n"
+    clean = (ours + "\t;;#ASMSTART\n\tv_mfma_f32_16x16x32_bf16 a[0:3], v[0:3], v[4:7], a[0:3]\n\t;;#ASMEND\n"
+             "\tv_add_u32_e32 v1, v2, v3                ; a0\n\t.amdhsa_accum_offset 256\n\ts_cbranch_vccnz .LBB0_a1\n"
+             "_ZN8cocodiff9mfma_loopEv:\n\tv_accvgpr_write_b32 a5, v1\n")
+    assert accumulator_accesses(clean) == []
+    for made in ("v_accvgpr_write_b32 a5, v1", "v_accvgpr_read_b32 v1, a17", "global_load_dwordx4 a[8:11], v[0:1], off",
+                 "scratch_store_dword off, a3, s32", "v_mfma_f32_16x16x32_bf16 v[0:3], v[4:7], v[8:11], a[0:3]"):
+        planted = clean.replace("\tv_add_u32", "\t" + made + "\n\tv_add_u32")
+        assert accumulator_accesses(planted) == [(5, made)]
