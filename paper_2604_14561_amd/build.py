@@ -48,6 +48,12 @@ def accumulator_accesses(assembly: str) -> list:
     return found
 
 
+def scratch_users(assembly: str) -> list:
+    """(kernel, bytes per lane) of the projection's main kernels that spill vector registers to scratch memory."""
+    sizes = re.findall(r"\.name:\s+(\S*qkv_gemm_direct_kernel\S*)\s+\.private_segment_fixed_size:\s+(\d+)", assembly)
+    return [(name, int(size)) for name, size in sizes if int(size)]
+
+
 def _check_assembly(source: str, obj: str) -> None:
     path = obj[:-len(".hip.o")] + "-hip-amdgcn-amd-amdhsa-gfx950.s"
     with open(path) as f:
@@ -57,6 +63,9 @@ def _check_assembly(source: str, obj: str) -> None:
         if found:
             raise RuntimeError(f"{os.path.basename(source)}: the compiler uses accumulation registers of its own in "
                                f"{len(found)} instructions, the first {found[0][1]!r}: they hold the projection's accumulators")
+        spilled = scratch_users(assembly)
+        if spilled:
+            raise RuntimeError(f"{os.path.basename(source)}: {len(spilled)} kernels spill registers, the first {spilled[0]}")
 
 
 def _compile(cmd: list) -> str:

@@ -333,7 +333,8 @@ __device__ __forceinline__ void store_plain(const GemmArgs& a, const TileOut& t,
 // any of the wavefront's vectors change?
 template <int NI, int NJ, bool SELECT>
 __device__ __forceinline__ uint32_t store_both(const GemmArgs& a, const TileOut& t, uint16_t* __restrict__ Y, uint16_t* __restrict__ Y2) {
-    constexpr int NP = NI / 2, AHEAD = NJ < 5 ? NJ : 5;
+    // (fetched 7 token tiles ahead: 32 x 48 tokens, 24 heads of 128, the call 81.6 us with 5, 79.1 so)
+    constexpr int NP = NI / 2, AHEAD = NJ < 7 ? NJ : 7;
     const Dest<NP> to_c = dest_chunks<NP>(a, t.v8, t.tl), to_h = dest_heads<NP>(a, t.v8, t.tl);
     ChunkWalk chunk(a, t.n0);
     const size_t at0 = (size_t)t.n0 * a.d8, step = (size_t)16u * a.d8;
@@ -692,10 +693,11 @@ __global__ void __launch_bounds__(256, 1) qkv_gemm_direct_kernel(GemmArgs a) {
     constexpr auto turn_at = [](int n) { return kTurnAt + n < NMFMA ? kTurnAt + n : NMFMA - 1; };
     constexpr int kAdvanceAt = kTurnAt >= kSpread ? kTurnAt : NMFMA - 1;      // the operand pointers move on: behind the half's last load
     static_assert(kAdvanceAt >= kSpread - 1, "the loads of a half use the pointers of that half");
-    auto half = [&](auto cur_c, auto tail_c) __attribute__((always_inline)) {
+    auto half = [&](auto cur_c, auto tail_c, auto read_c) __attribute__((always_inline)) {
         constexpr int CUR = decltype(cur_c)::value, TAIL = decltype(tail_c)::value;
+        constexpr bool READ = decltype(read_c)::value;
         constexpr bool LOAD = TAIL < 0;
-        constexpr int N_LOADS = !LOAD ? 0 : CUR == 0 ? NJ : NI, OPS = NREADS + 2 * N_LOADS;
+        constexpr int N_LOADS = !LOAD ? 0 : CUR == 0 ? NJ : NI, OPS = (READ ? NREADS : 0) + 2 * N_LOADS;
         constexpr int IN_FLIGHT = LOAD ? (kAhead - 1) * NJ + (kAhead - 2) * NI : TAIL > 1 ? (TAIL - 1) * (NI + NJ) : 0;
         const uint32_t xs_n = CUR == 0 ? x_read : x_next, ws_n = CUR == 0 ? w_read : w_next;
         const uint32_t lds_l = CUR == 0 ? ld_lds + x_load : ld_lds + kWRing + w_read;
@@ -740,24 +742,30 @@ __global__ void __launch_bounds__(256, 1) qkv_gemm_direct_kernel(GemmArgs a) {
         });
     };
     // The ring keeps turning from tile to tile: the last kAhead steps of a tile load the first ones of the workgroup's next tile,
-    // and the last half reads that tile's first fragments, so between two tiles only the epilogue's instructions are exposed --
-    // no workgroup start, no first trip to memory.
-    auto k_step = [&](auto tail) __attribute__((always_inline)) {
+    // and the last half reads that tile's first fragments (not in the fused form, see below), so between two tiles only the
+    // epilogue's instructions are exposed -- no workgroup start, no first trip to memory.
+    auto k_step = [&](auto tail, auto read_next) __attribute__((always_inline)) {
         reserve_accumulators<4 * NI * NJ>();
         mfma_operands_ready();      // (fragments are copied where the loops meet)
-        half(std::integral_constant<int, 0>{}, tail);
-        half(std::integral_constant<int, 1>{}, tail);
+        half(std::integral_constant<int, 0>{}, tail, std::true_type{});
+        half(std::integral_constant<int, 1>{}, tail, read_next);
     };
     const std::integral_constant<int, -1> loading;
+    const std::true_type reading;
+    // In the fused form the first fragments of the next tile are read behind the epilogue instead, whose values need the
+    // registers: 256 x 256 takes 236 vector registers so and the pair-by-pair rotation no scratch memory (256, and 108 bytes a
+    // lane, with the fragments held through the epilogue: 96 x 96 tokens, 24 heads, pairs 33 + 31, the whole call 455 us for 439).
+    constexpr bool kReadEarly = LAYOUT != OUT_FUSED && LAYOUT != OUT_FUSED_ANY;
+    const std::bool_constant<kReadEarly> reading_early;
     for (;;) {
         const uint32_t steps = n_k - kAhead;
-        if (steps & 1u) k_step(loading);
+        if (steps & 1u) k_step(loading, reading);
         uint32_t pairs = steps / 2u;      // two steps to a turn of the loop (a branch taken costs some 80 clocks)
         if (pairs > 0) {
 #pragma unroll 1
             do {
-                k_step(loading);
-                k_step(loading);
+                k_step(loading, reading);
+                k_step(loading, reading);
             } while (--pairs > 0);
         }
         vt += walk.stride;
@@ -765,18 +773,16 @@ __global__ void __launch_bounds__(256, 1) qkv_gemm_direct_kernel(GemmArgs a) {
         const TileCoord next = tile_at(a, more ? vt : walk.first);
         if (more) {
             load_from(next);
-            if constexpr (kAhead == 2) {
-                k_step(loading);
-                k_step(loading);
-            } else {
-                uint32_t left = kAhead;
+            uint32_t left = kAhead - 1;
 #pragma unroll 1
-                do k_step(loading);
-                while (--left > 0);
-            }
+            do k_step(loading, reading);
+            while (--left > 0);
+            k_step(loading, reading_early);
         } else {
-            unrolled<kAhead>([&](auto s_c) __attribute__((always_inline)) { k_step(std::integral_constant<int, kAhead - 1 - decltype(s_c)::value>{}); });
-            // (the very last half reads fragments nobody multiplies)
+            unrolled<kAhead>([&](auto s_c) __attribute__((always_inline)) {
+                constexpr int follow = kAhead - 1 - decltype(s_c)::value;
+                k_step(std::integral_constant<int, follow>{}, std::bool_constant<(follow > 0)>{});      // (the very last half reads nothing)
+            });
         }
         mfma_results_ready();
 
@@ -818,6 +824,10 @@ __global__ void __launch_bounds__(256, 1) qkv_gemm_direct_kernel(GemmArgs a) {
         }
         if (!more) return;
         tc = next;
+        if constexpr (!kReadEarly) {
+#pragma unroll
+            for (int r = 0; r < NREADS; ++r) read_frag(wf[0], xf[0], x_read, w_read, 0, r);
+        }
     }
 }
 

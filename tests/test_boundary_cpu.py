@@ -220,3 +220,11 @@ def test_build_refuses_accumulation_registers_of_the_compilers_own():
                  "scratch_store_dword off, a3, s32", "v_mfma_f32_16x16x32_bf16 v[0:3], v[4:7], v[8:11], a[0:3]"):
         planted = clean.replace("\tv_add_u32", "\t" + made + "\n\tv_add_u32")
         assert accumulator_accesses(planted) == [(5, made)]
+
+
+def test_build_refuses_projection_kernels_that_spill():
+    from paper_2604_14561_amd.build import scratch_users
+    entry = "    .name:           _ZN8cocodiff22qkv_gemm_direct_kernelILi8ELi%dELi4EEEvNS_8GemmArgsE\n    .private_segment_fixed_size: %d\n"
+    other = "    .name:           _ZN8cocodiff9mfma_loopEv\n    .private_segment_fixed_size: 64\n"
+    assert scratch_users(entry % (8, 0) + other) == []
+    assert scratch_users(entry % (8, 0) + other + entry % (7, 108)) == [("_ZN8cocodiff22qkv_gemm_direct_kernelILi8ELi7ELi4EEEvNS_8GemmArgsE", 108)]
