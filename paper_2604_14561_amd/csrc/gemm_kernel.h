@@ -216,6 +216,33 @@ __device__ __forceinline__ Dest<NP> dest_heads(const GemmArgs& a, uint32_t v8, u
     return t;
 }
 
+// Whole lines for streamed stores.  A store of one vector per lane writes 64 consecutive bytes of sixteen tokens: half a line each,
+// its other half a vector later.  Streamed past the caches such halves cost: 64 x 72 tokens, 16 heads of 64, 84 tiles of V
+// and 168 of Q and K in one round, all storing at once: the fused epilogue took 24.9 k clocks of the tile's 61 k, 20.9 k with
+// whole lines; the call 41.4 -> 38.1 us, at 144 x 144 tokens, 24 heads of 128, 968 -> 916 us.
+// pair_lines exchanges the vectors of features 32 p .. (`a`) and 32 (p + 1) .. (`b`), p even, between the lanes of tokens t and
+// t + 8 of a token tile: `a` becomes the line of tokens 0 .. 7, the upper half of it in the lanes of tokens 8 .. 15, and `b` that
+// of tokens 8 .. 15.  paired() moves a lane's destinations along.
+__device__ __forceinline__ void pair_lines(vec16& a, vec16& b) {
+    constexpr int ROW_ROR_8 = 0x128;      // from the lane 8 further in the same row of 16; written in the upper / lower half row
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int x = (int)a[i], y = (int)b[i];
+        a[i] = (uint32_t)__builtin_amdgcn_update_dpp(x, y, ROW_ROR_8, 0xf, 0xc, false);
+        b[i] = (uint32_t)__builtin_amdgcn_update_dpp(y, x, ROW_ROR_8, 0xf, 0x3, false);
+    }
+}
+template <int NP>
+__device__ __forceinline__ Dest<NP> paired(Dest<NP> t, uint32_t tl, uint32_t row) {      // row: vectors from one token to the next
+    static_assert(NP % 2 == 0, "feature groups in pairs");
+#pragma unroll
+    for (int p = 0; p < NP; p += 2) {
+        if (tl >= 8u) t.lane[p] = t.lane[p + 1] - (size_t)8u * row;
+        t.lane[p + 1] = t.lane[p] + (size_t)8u * row;
+    }
+    return t;
+}
+
 // The token tile's part of an exchange-buffer address, stepped from one token tile to the next.
 struct ChunkWalk {
     uint32_t m;
@@ -335,15 +362,14 @@ template <int NI, int NJ, bool SELECT>
 __device__ __forceinline__ uint32_t store_both(const GemmArgs& a, const TileOut& t, uint16_t* __restrict__ Y, uint16_t* __restrict__ Y2) {
     // (fetched 7 token tiles ahead: 32 x 48 tokens, 24 heads of 128, the call 81.6 us with 5, 79.1 so)
     constexpr int NP = NI / 2, AHEAD = NJ < 7 ? NJ : 7;
-    const Dest<NP> to_c = dest_chunks<NP>(a, t.v8, t.tl), to_h = dest_heads<NP>(a, t.v8, t.tl);
+    const Dest<NP> to_c = paired(dest_chunks<NP>(a, t.v8, t.tl), t.tl, a.row8), to_h = paired(dest_heads<NP>(a, t.v8, t.tl), t.tl, a.d8);
     ChunkWalk chunk(a, t.n0);
     const size_t at0 = (size_t)t.n0 * a.d8, step = (size_t)16u * a.d8;
     vec16 *yc = reinterpret_cast<vec16*>(Y), *yh = reinterpret_cast<vec16*>(Y2) + at0;
     const vec16* yp = reinterpret_cast<const vec16*>(a.sel_prev) + at0;
-    // A load instruction reads half of a 128-byte line per token and its neighbour the other half.  Where every unit has one tile
-    // (nothing runs beside its epilogue) the line is kept for the second half: 3600 x 1152, 255 tiles, the whole call 46.3 us with
-    // streamed loads, 39.6 so.  In launches of more rounds streamed loads are the better or the equal ones: 2304 x 3072 130.9
-    // against 134.8 us, 99840 x 3072 4414 against 4485; 9216 x 3072 438.8 against 433.7.
+    // The previous V's lines are loaded whole, laid out as the vectors that they are compared with.  Streamed loads, but cached ones
+    // where every unit has one tile and all of V is read at once, behind the K loops: the whole call 39.8 us streamed and 38.1 cached
+    // at 4608 x 1024, 41.2 and 40.0 at 3600 x 1152, 48.3 and 46.8 at 3072 x 1536; 80.3 and 81.4 at 1536 x 3072.
     const bool one_round = (uint32_t)a.n_tiles <= gridDim.x;
     vec16 prev[AHEAD + 1][NP];
     auto fetch = [&](int j) __attribute__((always_inline)) {
@@ -366,6 +392,8 @@ __device__ __forceinline__ uint32_t store_both(const GemmArgs& a, const TileOut&
             take_acc<NJ, decltype(p_c)::value, j>(x, zero);
             v[decltype(p_c)::value] = pack_vec(x);
         });
+#pragma unroll
+        for (int p = 0; p < NP; p += 2) pair_lines(v[p], v[p + 1]);
         if (Y) store_groups<true>(yc + chunk.at, to_c, v, t.live_p);
         if (Y2) store_groups<false>(yh, to_h, v, t.live_p);
         if (SELECT) {
@@ -386,11 +414,9 @@ __device__ __forceinline__ uint32_t store_both(const GemmArgs& a, const TileOut&
             ties &= ties - 1u;
             const vec16* now = reinterpret_cast<const vec16*>(Y2) + at0 + step * j;
             bool changed = false;
-            for (int p = 0; p < t.live_p; ++p) {
-                const uint32_t v = t.v8 + 4u * p, h = v / a.d8;
-                const size_t at = (size_t)h * a.N_all * a.d8 + t.tl * a.d8 + (v - h * a.d8);
-                changed |= vec_changed_double(now[at], yp[step * j + at], a.sel_th.tau);
-            }
+#pragma unroll
+            for (int p = 0; p < NP; ++p)      // (every lane what it stored itself)
+                if (p < t.live_p) changed |= vec_changed_double(now[to_h.lane[p]], yp[step * j + to_h.lane[p]], a.sel_th.tau);
             verdict |= (__ballot(changed) != 0 ? 1u : 0u) << j;
         }
     }
@@ -491,7 +517,7 @@ __device__ __forceinline__ void store_normalised(const GemmArgs& a, const TileOu
         row_a[0] += a.row_step16[0] + (carry1 ? a.row_stride[0] : 0u);
     };
 
-    const Dest<NP> to_c = dest_chunks<NP>(a, t.v8, t.tl), to_h = dest_heads<NP>(a, t.v8, t.tl);
+    const Dest<NP> to_c = paired(dest_chunks<NP>(a, t.v8, t.tl), t.tl, a.row8), to_h = paired(dest_heads<NP>(a, t.v8, t.tl), t.tl, a.d8);
     ChunkWalk chunk(a, t.n0);
     vec16 *yc = reinterpret_cast<vec16*>(Y), *yh = reinterpret_cast<vec16*>(Y2) + (size_t)t.n0 * a.d8;
     const bf16x8 zero = zero_fragment();
@@ -527,6 +553,8 @@ __device__ __forceinline__ void store_normalised(const GemmArgs& a, const TileOu
             }
             v[p] = pack_vec(o);
         }
+#pragma unroll
+        for (int p = 0; p < NP; p += 2) pair_lines(v[p], v[p + 1]);
         if (Y) store_groups<true>(yc + chunk.at, to_c, v, t.live_p);
         if (Y2) store_groups<true>(yh, to_h, v, t.live_p);
         chunk.next(a);
