@@ -683,9 +683,11 @@ def test_unpack_select_equals_unpack_then_select(oracle, name, order):
                              None, NT, ws)
 
 
-def _fused_select_case(oracle, N, D, H, d, P, grid, pairs, inp, T, tau, n_changed, order, cap=None, sparse=False, what=""):
+def _fused_select_case(oracle, N, D, H, d, P, grid, pairs, inp, T, tau, n_changed, order, cap=None, sparse=False, what="",
+                       make_prev=None):
     """cocodiff_qkv_proj_fused_select against cocodiff_qkv_proj_fused followed by cocodiff_vmajor_select: every output
-    bit for bit; the selection also against the oracle on the GPU's V."""
+    bit for bit; the selection also against the oracle on the GPU's V.  make_prev(cur, rng): previous V, threshold and the
+    tiles that changed, in place of tau and n_changed."""
     import torch
     from synth import perturb_tiles
     sh = cd.Shape.make(N, D, H, d, P)
@@ -702,7 +704,9 @@ def _fused_select_case(oracle, N, D, H, d, P, grid, pairs, inp, T, tau, n_change
     _sync()
     cur = to_host_bits(v0)
     rng = np.random.default_rng(N + 3 * T)
-    if sparse:      # one element of one head differs per changed tile: the flag must come from a single lane
+    if make_prev:
+        prev, tau, changed = make_prev(cur, rng)
+    elif sparse:      # one element of one head differs per changed tile: the flag must come from a single lane
         prev = cur.copy()
         changed = np.sort(rng.permutation(NT)[:n_changed]).astype(np.int32)
         for t_ in changed:
@@ -741,7 +745,7 @@ def _fused_select_case(oracle, N, D, H, d, P, grid, pairs, inp, T, tau, n_change
     o_flags, o_idx, o_n, o_comp = oracle.vmajor_select(cur, prev, tau, T)
     assert b[3] == o_n and np.array_equal(b[2], o_idx[:o_n]) and np.array_equal(b[1], o_flags), f"{what}: selection differs from the oracle"
     assert np.array_equal(b[4], o_comp[:, :min(o_n, cap) * T])
-    if tau > 0 and tau < 0.01:
+    if make_prev or (tau > 0 and tau < 0.01):
         assert o_n == len(changed) and np.array_equal(o_idx[:o_n], np.sort(changed))
     return o_n
 
@@ -760,7 +764,7 @@ def test_proj_fused_select_equals_the_two_calls(oracle, name, order):
 
 @gpu
 @pytest.mark.parametrize("N,H,d,P,grid,pairs,T,tau,n_changed,cap,sparse", [
-    (272, 4, 64, 1, (17, 16), (16, 16), 16, 1e-3, 5, None, False),       # ragged token tile (272 = 192 + 80)
+    (272, 4, 64, 1, (17, 16), (16, 16), 16, 1e-3, 5, None, False),       # ragged last token tile (tiles of 32 tokens)
     (528, 3, 256, 1, (22, 24), (64, 64), 16, 1e-3, 33, 7, False),        # list longer than the compact buffer
     (96, 5, 64, 1, (2, 4, 12), (10, 11, 11), 16, 1e-3, 6, None, False),  # D = 320: ragged feature tile, two flag bytes per tile
     (512, 4, 128, 4, (16, 32), (40, 24), 16, 1e-3, 32, None, True),      # every tile changed, each in one element only
@@ -1168,8 +1172,7 @@ def test_proj_every_tile_shape(oracle, bm, bn, N, H, n_tensors):
             assert bool((r[i][N * D:] == 0x5A5A).all().cpu())
 
 
-@gpu
-@pytest.mark.parametrize("bm,bn,N,H,d", [
+FUSED_TILES = [
     (256, 256, 20496, 7, 64), (256, 256, 13680, 5, 128), (256, 256, 19056, 1, 256), (224, 256, 16464, 7, 64),
     (224, 256, 18160, 5, 128), (224, 256, 16336, 1, 256), (192, 256, 14480, 5, 64), (192, 256, 14496, 3, 128),
     (192, 256, 13616, 1, 256), (160, 256, 21792, 3, 64), (160, 256, 8720, 5, 128), (160, 256, 10896, 1, 256),
@@ -1178,7 +1181,11 @@ def test_proj_every_tile_shape(oracle, bm, bn, N, H, n_tensors):
     (256, 128, 10960, 5, 64), (256, 128, 10896, 3, 128), (128, 128, 10800, 5, 64), (128, 128, 10800, 3, 128),
     (96, 128, 1840, 5, 64), (96, 128, 2720, 2, 128), (64, 128, 1040, 5, 64), (64, 128, 1376, 2, 128), (32, 128, 80, 5, 64),
     (32, 128, 48, 3, 128),
-])
+]
+
+
+@gpu
+@pytest.mark.parametrize("bm,bn,N,H,d", FUSED_TILES)
 def test_proj_fused_every_tile_shape(oracle, bm, bn, N, H, d):
     """Two or one heads of a wavefront, and heads that two wavefronts share; pairs in fours (heads of 128) and not (64, 256)."""
     from synth import f32_to_bf16_bits
@@ -1196,6 +1203,72 @@ def test_proj_fused_every_tile_shape(oracle, bm, bn, N, H, d):
     ids = np.unique(np.clip(np.concatenate([edges, rng.integers(0, N, 64)]), 0, N - 1))
     pairs = (d // 4, d // 4) if d == 128 else (d // 4 - 1, d // 4 + 1)
     _fused_case(oracle, N, D, H, d, H, (16, N // 16), pairs, inp, ids, what=f"fused tile {bm}x{bn}")
+
+
+def _fused_inputs(rng, N, D, d):
+    from synth import f32_to_bf16_bits
+    inp = {"X": f32_to_bf16_bits(rng.standard_normal((N, D), dtype=np.float32))}
+    for w in ("Wq", "Wk", "Wv"):
+        inp[w] = f32_to_bf16_bits(rng.standard_normal((D, D), dtype=np.float32) * np.float32(D ** -0.5))
+    for g_ in ("gamma_q", "gamma_k"):
+        inp[g_] = f32_to_bf16_bits((1.0 + 0.1 * rng.standard_normal(d)).astype(np.float32))
+    return inp
+
+
+@gpu
+@pytest.mark.parametrize("bm,bn,N,H,d", FUSED_TILES + [
+    (256, 256, 20720, 7, 64), (256, 256, 20832, 7, 64),      # 7 and 6 of a wavefront's 8 token tiles exist
+    (32, 128, 128, 32, 64), (128, 128, 512, 30, 64),         # 16 and 15 flag bytes
+])
+def test_proj_fused_select_every_tile_shape(oracle, bm, bn, N, H, d):
+    """V flagged by every tile shape, on ragged sizes (seven heads of 64: the last 256 features are three of four 64s): one
+    element of one head differs in each of a third of the tiles, so that every lane's verdict counts."""
+    D = H * d
+    plan = cd.qkv_proj_plan(cd.Shape.make(N, D, H, d, 1), 3, whole_heads=True)
+    if plan["compute_units"] == 256:
+        assert (plan["tile_tokens"], plan["tile_features"]) == (bm, bn), plan
+    print(f"flagged fused tile {bm}x{bn}: {N}x{D}", flush=True)
+    P = H if N % (16 * H) == 0 else 1
+    _fused_select_case(oracle, N, D, H, d, P, (16, N // 16), (d // 4, d // 4), _fused_inputs(np.random.default_rng(N * 31 + D), N, D, d), 16,
+                       1e-3, max(1, N // 48), cd.SEND_MAJOR, sparse=True, what=f"flagged tile {bm}x{bn}")
+
+
+@gpu
+@pytest.mark.parametrize("N,H,d", [(272, 4, 64), (2304, 18, 64), (512, 4, 128), (528, 3, 256), (13616, 1, 256)])
+@pytest.mark.parametrize("sides", ["both", "above", "below"])
+def test_proj_fused_select_ties(oracle, N, H, d, sides):
+    """Differences whose fp32 value is exactly the threshold.  With |V| = tau and a previous value 2^-40 of it, the exact
+    difference is above tau where the signs differ and below it where they agree: the 64-bit comparison decides."""
+    D = H * d
+
+    def make_prev(cur, rng):
+        mag = cur & 0x7FFF
+        values, counts = np.unique(mag[(mag > 0x3C00) & (mag < 0x4100)], return_counts=True)
+        tau_bits = int(values[np.argmax(counts)])
+        prev, changed, used = cur.copy(), [], set()
+        for h, n, i in rng.permutation(np.argwhere(mag == tau_bits)):
+            if n // 16 in used or len(used) >= max(2, N // 32):
+                continue
+            used.add(n // 16)
+            above = sides == "above" or (sides == "both" and len(used) % 2)
+            prev[h, n, i] = (tau_bits - (40 << 7)) | ((int(cur[h, n, i]) ^ (0x8000 if above else 0)) & 0x8000)
+            if above:
+                changed.append(n // 16)
+        assert len(used) > 1
+        return prev, float(np.array([tau_bits << 16], dtype=np.uint32).view(np.float32)[0]), np.array(sorted(changed), dtype=np.int32)
+
+    _fused_select_case(oracle, N, D, H, d, 1, (16, N // 16), (d // 4, d // 4), _fused_inputs(np.random.default_rng(N + D), N, D, d), 16, 0.0, 0,
+                       cd.RECV_MAJOR, make_prev=make_prev, what=f"ties {sides} {N}x{D}")
+
+
+@gpu
+@pytest.mark.parametrize("tau", [-1.0, float("-inf"), -0.0])
+def test_proj_fused_select_negative_threshold(oracle, tau):
+    """Below zero everything is active, also where nothing changed; minus zero is zero."""
+    N, H, d = 272, 4, 64
+    n = _fused_select_case(oracle, N, H * d, H, d, 1, (16, 17), (16, 16), _fused_inputs(np.random.default_rng(5), N, H * d, d), 16, tau, 3,
+                           cd.SEND_MAJOR, sparse=True, what=f"tau {tau}")
+    assert n == (N // 16 if tau < 0 else 3)
 
 
 @gpu
