@@ -295,6 +295,54 @@ static LaunchPlan plan_launch(int32_t M, int32_t D, int32_t n_tensors, bool whol
     return p;
 }
 
+// How many tile rows tile_at walks together in a fused launch of tiles_m x tiles_n tiles on `workgroups` workgroups.  The operands of
+// a launch come from memory when they are read first -- a layer's weights are not on chip -- and a round in which any tile
+// reads something new runs at that pace, since a K step's loads are two steps ahead at most.  So the walk is chosen whose first
+// round touches every tile row and every column, if there is one: later rounds then find everything in the last-level cache.
+// Among those, the one with the fewest operand rows for the XCD that has most.  Else 8 rows: 8 x 4 tiles on an XCD's 32 units,
+// close to the least traffic through its L2.
+// The whole call, three weights that change from pass to pass, by group size (those that touch everything at once in brackets):
+//   2304 x 2560, 15 x 30 tiles   8: 112.1  6: 110.5  5: [105.9]  4: 115.3  3: [106.7] us
+//   3072 x 2560, 16 x 30         8: 127.6  6: 126.9  5: [116.1]  4: 126.5  3: [116.8]
+//   4608 x 2560, 24 x 30         8: [169.7]  6: 183.9  5: [169.7]  4: [170.8]  3: 184.9
+//   4608 x 2816, 29 x 33         8: 234.1  6: [208.3]  5: [206.9]  4: 219.8  3: 209.2
+//   2304 x 3072, 12 x 36         8: 136.6  6: 133.9  5: [126.9]  4: [125.3]  3: 136.9
+// and with everything on chip 109.5 (8) and 109.6 (4) at 2304 x 3072.
+static uint32_t rows_walked_together(const LaunchPlan& p, uint32_t tiles_n, uint32_t workgroups) {
+    const uint32_t tiles_m = (uint32_t)p.tiles_m;
+    if (tiles_m > 64 || tiles_n > 64 || tiles_m * tiles_n <= workgroups) return 8;
+    const uint32_t n_tiles = tiles_m * tiles_n;
+    const auto bits = [](uint32_t from, uint32_t count) { return (count >= 64 ? ~0ull : (1ull << count) - 1ull) << from; };
+    uint32_t best = 8, best_rows = UINT32_MAX;
+    for (uint32_t g : {8u, 6u, 5u, 4u, 3u}) {
+        uint64_t rows = 0, cols = 0;
+        uint32_t most = 0;
+        for (uint32_t xcd = 0; xcd < 8; ++xcd) {      // as tiles_of_block deals them out
+            const uint32_t per = n_tiles >> 3, rem = n_tiles & 7u;
+            uint32_t vt = xcd * per + std::min(xcd, rem);
+            const uint32_t end = vt + std::min(per + (xcd < rem ? 1u : 0u), (workgroups >> 3) + (xcd < (workgroups & 7u) ? 1u : 0u));
+            uint64_t r = 0, c = 0;
+            while (vt < end) {      // group by group, as tile_at walks
+                const uint32_t group = vt / (g * tiles_n), first = group * g, high = std::min(tiles_m - first, g);
+                const uint32_t from = vt - group * g * tiles_n, to = std::min(end - group * g * tiles_n, high * tiles_n);
+                c |= bits(from / high, (to - 1) / high - from / high + 1);
+                if (to - from >= high) r |= bits(first, high);
+                else
+                    for (uint32_t t = from; t < to; ++t) r |= 1ull << (first + t % high);
+                vt += to - from;
+            }
+            rows |= r;
+            cols |= c;
+            most = std::max(most, (uint32_t)(__builtin_popcountll(r) * p.bm + __builtin_popcountll(c) * p.bn));
+        }
+        if (rows == bits(0, tiles_m) && cols == bits(0, tiles_n) && most < best_rows) {
+            best = g;
+            best_rows = most;
+        }
+    }
+    return best;
+}
+
 }  // namespace cocodiff
 
 using namespace cocodiff;
@@ -394,6 +442,8 @@ static int proj_launch(const cocodiff_shape* shape, const cocodiff_bf16* x,
     a.tiles_n_per_tensor = plan.tiles_n_per_tensor;
     const uint32_t n_tiles = (uint32_t)a.tiles_m * a.tiles_n_per_tensor * a.n_tensors;
     a.n_tiles = (int32_t)n_tiles;
+    const uint32_t n_workgroups = (uint32_t)(plan.n_cu * pick->per_cu);      // workgroups at most
+    a.group = layout == OUT_FUSED ? rows_walked_together(plan, (uint32_t)a.tiles_n_per_tensor * a.n_tensors, n_workgroups) : 8u;
     // the four pairs of eight consecutive features are 32 consecutive bytes of a table row when every axis has a multiple of four
     bool quad_pairs = true;
     for (int ax = 0; ax < 3; ++ax) a.row_base[ax] = a.row_stride[ax] = a.row_span[ax] = a.row_end[ax] = a.row_step16[ax] = 0;
@@ -437,7 +487,7 @@ static int proj_launch(const cocodiff_shape* shape, const cocodiff_bf16* x,
     static const void* const staged[] = {(const void*)qkv_gemm_staged_kernel<OUT_SEQ>, (const void*)qkv_gemm_staged_kernel<OUT_CHUNKS>,
                                           (const void*)qkv_gemm_staged_kernel<OUT_HEADS>};
     if (ring_kernel)
-        le = hipLaunchKernel(pick->entry[layout == OUT_FUSED && !quad_pairs ? OUT_FUSED_ANY : layout], dim3(std::min(n_tiles, (uint32_t)(plan.n_cu * pick->per_cu))), dim3(256), kernel_args, pick->lds, st);
+        le = hipLaunchKernel(pick->entry[layout == OUT_FUSED && !quad_pairs ? OUT_FUSED_ANY : layout], dim3(std::min(n_tiles, n_workgroups)), dim3(256), kernel_args, pick->lds, st);
     else
         le = hipLaunchKernel(staged[layout], dim3(n_tiles), dim3(kStagedThreads), kernel_args, kLdsBytes, st);
     if (le != hipSuccess) return fail(COCODIFF_ERR_HIP, "qkv_proj: launch failed: %s", hipGetErrorString(le));

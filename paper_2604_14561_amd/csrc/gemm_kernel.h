@@ -23,6 +23,7 @@ struct GemmArgs {
     int32_t D;                 // features per tensor = K
     int32_t tiles_m, tiles_n_per_tensor, n_tiles;
     int32_t bm, bn;            // tile of the launch: tokens x features
+    uint32_t group;            // tile rows that are walked together (tile_at)
     // outputs in exchange-buffer (chunk) order instead of [N][D]: tokens per rank, ranks, 16-byte vectors per
     // chunk row and per chunk, slot order
     uint32_t Ns, P, row8, chunk8;
@@ -64,15 +65,14 @@ struct TileCoord {
     uint32_t tensor, m0, f0;
 };
 
-// Tile `vt` of the launch: groups of 8 tile rows walked column by column, so that tiles with neighbouring numbers share rows
-// of X and W.
+// Tile `vt` of the launch: groups of a.group tile rows walked column by column, so that tiles with neighbouring numbers share
+// rows of X and W.
 __device__ __forceinline__ TileCoord tile_at(const GemmArgs& a, uint32_t vt) {
     const uint32_t tiles_n = (uint32_t)a.tiles_n_per_tensor * a.n_tensors;
-    constexpr uint32_t GROUP = 8;
-    const uint32_t per_group = GROUP * tiles_n;
+    const uint32_t per_group = a.group * tiles_n;
     const uint32_t grp = vt / per_group;
-    const uint32_t first_m = grp * GROUP;
-    const uint32_t rows_here = min((uint32_t)a.tiles_m - first_m, GROUP);
+    const uint32_t first_m = grp * a.group;
+    const uint32_t rows_here = min((uint32_t)a.tiles_m - first_m, a.group);
     const uint32_t in_grp = vt - grp * per_group;
     const uint32_t tm = first_m + in_grp % rows_here;
     const uint32_t tn = in_grp / rows_here;
