@@ -217,12 +217,12 @@ __global__ void __launch_bounds__(kStagedThreads) qkv_gemm_staged_kernel(GemmArg
 // A tile shape of the main kernel: tokens x features, dynamic LDS, the kernels by OutLayout.
 struct TileKernel {
     int bm, bn, lds;
-    int per_cu;                   // workgroups that fit a compute unit together (LDS; 256 registers a wavefront below 65 accumulators)
+    int per_cu;                   // workgroups that share a compute unit
     const void* entry[5];
 };
 
 static const TileKernel* tile_shapes(bool whole_heads, int* count) {
-#define SHAPE(NI, NJ) {32 * NJ, 32 * NI, ring_lds_bytes(32 * NJ, 32 * NI), 4 * NI * NJ <= 64 && 2 * ring_lds_bytes(32 * NJ, 32 * NI) <= 160 * 1024 ? 2 : 1, {}},
+#define SHAPE(NI, NJ) {32 * NJ, 32 * NI, ring_lds_bytes(32 * NJ, 32 * NI), workgroups_per_unit(NI, NJ), {}},
     static TileKernel plain[] = {COCODIFF_PLAIN_TILES(SHAPE)};
     static TileKernel fused[] = {COCODIFF_FUSED_TILES(SHAPE)};
 #undef SHAPE
@@ -245,9 +245,12 @@ static const TileKernel* tile_shapes(bool whole_heads, int* count) {
 }
 
 // Clocks of one workgroup's tile, fitted to the built shapes: a K step is 17.2 clocks per MFMA of a wavefront and 60 for its
-// barrier, or the operands' way through L2 (40 bytes per clock and unit) where that is longer; then the epilogue.  Against all
-// shapes at 256 .. 20736 tokens x 256 .. 3072 features, one to three weights, both forms (45 launches), the shape of least
-// estimate is the fastest in 28 and within 3 % in all but one (2304 x 3072, three weights: 105.1 us for 100.6).
+// barrier, or the operands' way through L2 (40 bytes per clock and unit) where that is longer; then the epilogue.  A round is one
+// tile per unit also where two workgroups share it: they share its matrix cores and its way to L2 too.
+// Against all shapes at 256 .. 20736 tokens x 256 .. 3072 features, one to three weights, both forms, inputs that change from pass
+// to pass (120 launches), the shape of least estimate is the fastest in 81 and within 3 % in 110.  Four of the others take 8 to
+// 9 us, as long as the host needs for the call; the rest are plain forms: 20736 x 256 with three weights 18.9 us for 15.9, the
+// other five 4 to 8 % off.
 static double tile_clocks(const TileKernel& t, int32_t D, bool whole_heads) {
     const double mfmas = (t.bm / 32) * (t.bn / 32) * 2.0, operand_bytes = (t.bm + t.bn) * BK * 2.0;
     const double step = std::max(mfmas * 17.2 + 60.0, operand_bytes / 40.0);

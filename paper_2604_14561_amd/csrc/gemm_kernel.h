@@ -593,6 +593,9 @@ constexpr int kMaxLds = 160 * 1024;
 constexpr int ring_lds(int bm, int bn, int ahead) { return ((ahead + 1) * bm + ahead * bn) * BK * 2; }
 constexpr int steps_ahead(int bm, int bn) { return ring_lds(bm, bn, 4) <= kMaxLds ? 4 : ring_lds(bm, bn, 3) <= kMaxLds ? 3 : 2; }
 constexpr int ring_lds_bytes(int bm, int bn) { return ring_lds(bm, bn, steps_ahead(bm, bn)); }
+// Workgroups that share a compute unit: two where the rings fit twice (64 x 64 and 32 x 64 tiles); the kernel's launch bounds then
+// keep a wavefront to the 256 registers that leaves it (138 and 122 taken).
+constexpr int workgroups_per_unit(int ni, int nj) { return 2 * ring_lds_bytes(32 * nj, 32 * ni) <= kMaxLds ? 2 : 1; }
 
 // One global -> LDS load of 16 bytes per lane: lane l's vector lands at lds_addr + 16*l.  Written as inline
 // assembly so that the compiler does not tie later LDS reads to it with a full vmcnt wait (it cannot tell
@@ -628,7 +631,7 @@ __device__ __forceinline__ void wave_barrier() { asm volatile("s_barrier" ::: "m
 //              tiles, two rounds of 256 compute units, where 432 square tiles are 1.69;
 //   192 x 192: WN = 4, NI = 3, NJ = 6 (8 wavefronts of 48 x 96; 2 - 5 % faster than 4 wavefronts of 96 x 96).
 template <int NI, int NJ, int LAYOUT>
-__global__ void __launch_bounds__(256, 1) qkv_gemm_direct_kernel(GemmArgs a) {
+__global__ void __launch_bounds__(256, workgroups_per_unit(NI, NJ)) qkv_gemm_direct_kernel(GemmArgs a) {
     constexpr int TM = 2 * NJ * 16, TN = 2 * NI * 16;             // tokens, features per tile
     constexpr int kXBytes = TM * BK * 2, kWBytes = TN * BK * 2;   // one operand tile of one K step
     constexpr int NMFMA = NI * NJ, NREADS = NI + NJ;              // per wavefront and half
