@@ -360,8 +360,9 @@ COCODIFF_API int cocodiff_a2a_unpack_seq(const cocodiff_shape* shape, const coco
 
 /* Which tile the projection takes for this shape's rank range and n_tensors (1..3) weights in one launch, on the
  * current device: tile extent in tokens and features, number of workgroups (= tiles), compute units of the device.
- * whole_heads != 0: the choice cocodiff_qkv_proj_fused makes (its tiles are 256 features wide), else that of the
- * other projection calls.  Any out pointer may be NULL.  Host arithmetic only; it needs a current HIP device for
+ * whole_heads != 0: the choice cocodiff_qkv_proj_fused makes (its tiles are 128 or 256 features wide, no narrower than a
+ * head; cocodiff_qkv_proj_fused_select makes the same one, but takes tiles 256 features wide where D is above 2048), else
+ * that of the other projection calls.  Any out pointer may be NULL.  Host arithmetic only; it needs a current HIP device for
  * the unit count (COCODIFF_ERR_HIP without one).  For reports and for tests that must land on a given tile shape. */
 COCODIFF_API int cocodiff_qkv_proj_plan(const cocodiff_shape* shape, int32_t n_tensors, int32_t whole_heads,
                                         int32_t* tile_tokens, int32_t* tile_features, int32_t* n_tiles,
@@ -379,7 +380,7 @@ COCODIFF_API int cocodiff_rope_table_fill(const cocodiff_rope* rope, float* host
 COCODIFF_API int cocodiff_util_copy(const void* src, void* dst, size_t bytes, void* stream);
 
 /* Register-only matrix-core loop (v_mfma_f32_16x16x32_bf16, the projection kernel's instruction, on a 4 x 8 outer
- * product of pseudo-random operand fragments as in that kernel; no memory traffic): the calibration kernel the
+ * product of pseudo-random operand fragments; no memory traffic): the calibration kernel the
  * projection is priced against besides the published peak.  Launches `blocks` workgroups of 8 wavefronts, each
  * wavefront issuing iters * 32 MFMAs; `sink` is one DEVICE float that is practically never written.  Returns the
  * floating-point operations of the launch (> 0) or a negative error code; the caller times the launch. */

@@ -62,7 +62,7 @@ __global__ void __launch_bounds__(256) copy_kernel(const vec16* __restrict__ src
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 mfma_in_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float mfma_acc_t;
 
-constexpr int kRateNI = 4, kRateNJ = 8;   // the projection kernel's wavefront tile: 4 x 8 accumulator tiles of 16 x 16
+constexpr int kRateNI = 4, kRateNJ = 8;   // accumulator tiles of 16 x 16 per wavefront
 
 // Register-only loop of the projection kernel's matrix-core work: v_mfma_f32_16x16x32_bf16 on a 4 x 8 outer product
 // of operand fragments, token tile by token tile, 8 wavefronts per workgroup (two per SIMD), no memory traffic.  The fragments hold small pseudo-random bf16

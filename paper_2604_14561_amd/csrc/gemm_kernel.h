@@ -169,7 +169,8 @@ __device__ __forceinline__ void unrolled(F&& f) { for_each_index(std::make_integ
 // W's rows are loaded into LDS in an order (w_row_of) that leaves a lane, in the accumulator tiles 2p and 2p + 1 of a token
 // tile, with EIGHT consecutive features of one token: lane l has features 32 p + 8 (l / 16) .. + 7 of the wavefront's, token
 // l % 16 of the token tile -- one 16-byte vector, so nothing goes through LDS on the way out and the ring is free to take
-// the next tile's operands meanwhile.  A store instruction writes 64 consecutive bytes of sixteen tokens.
+// the next tile's operands meanwhile.  A store instruction writes 64 consecutive bytes of sixteen tokens (the fused form
+// exchanges vectors between lanes first and writes whole lines of eight, see pair_lines).
 // Sizes are kind: token ranges start and end at multiples of 16 and the launch's D is a multiple of 64, so a token tile or a
 // group of 32 features exists as a whole or not at all, and a token tile lies in one rank's chunk.  A destination address is
 // therefore a per-lane part (feature, token within the token tile: formed once) plus a part that is the same for the
@@ -429,8 +430,8 @@ __device__ __forceinline__ uint32_t store_both(const GemmArgs& a, const TileOut&
 // HEAD = d.  A wavefront holds 16 NI features of its tokens: one or two whole heads, or half of one, whose sums of squares the
 // two wavefronts exchange through `xch` (LDS, [wavefront][token]; two workgroup barriers, the second so that
 // nobody overwrites what the other still reads).
-// This stage's time is its instruction count (nothing else runs on the unit meanwhile), so the token's grid coordinates are
-// divided out once, for token tile 0, and then stepped as table row offsets: 16 tokens further is a.row_step16[] further in
+// Nothing else runs on the unit meanwhile, so this stage's instructions are exposed (where all units end together its stores take
+// longer still): the token's grid coordinates are divided out once, for token tile 0, and then stepped as table row offsets: 16 tokens further is a.row_step16[] further in
 // mixed radix, with carries (the absent axes of a one- or two-axis grid are grids of one cell: they never carry).  The
 // (cos, sin) values of a token tile are fetched from the table (L1 / L2) while its sums of squares are formed.
 // QUADS: every axis has a multiple of four pairs, so the four pairs of a vector are 32 consecutive bytes of a table row.
@@ -625,11 +626,8 @@ __device__ __forceinline__ void set_scalar(uint32_t& to, uint32_t from) { asm vo
 // completed is waited for in front of it.
 __device__ __forceinline__ void wave_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
-// Tile = (2 * NJ * 16) tokens x (WN * NI * 16) features, WN wavefronts along the features x 2 along the tokens:
-//   256 x 256: WN = 4, NI = 4, NJ = 8 (8 wavefronts of 64 features x 128 tokens);
-//   288 x 192: WN = 4, NI = 3, NJ = 9 (8 wavefronts of 48 x 144) -- 9216 tokens x 3072 features are exactly 512 such
-//              tiles, two rounds of 256 compute units, where 432 square tiles are 1.69;
-//   192 x 192: WN = 4, NI = 3, NJ = 6 (8 wavefronts of 48 x 96; 2 - 5 % faster than 4 wavefronts of 96 x 96).
+// Tile = 32 NJ tokens x 32 NI features: NI = NJ = 8 is 256 x 256, NI = 6, NJ = 9 is 288 x 192 -- 9216 tokens x 3072 features are
+// exactly 512 of those, two rounds of 256 compute units, where 432 square tiles are 1.69.
 template <int NI, int NJ, int LAYOUT>
 __global__ void __launch_bounds__(256, workgroups_per_unit(NI, NJ)) qkv_gemm_direct_kernel(GemmArgs a) {
     constexpr int TM = 2 * NJ * 16, TN = 2 * NI * 16;             // tokens, features per tile

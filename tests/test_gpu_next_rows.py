@@ -433,12 +433,12 @@ def test_proj_fused_matches_the_chain_oracle(oracle, name):
 
 @gpu
 @pytest.mark.parametrize("N,H,d,P,grid,pairs,rank", [
-    (272, 4, 64, 1, (17, 16), (16, 16), None),          # a head per wavefront; ragged token tile
-    (528, 3, 256, 1, (22, 24), (64, 64), None),         # a head across four wavefronts; D = 768: three tiles of 256
+    (272, 4, 64, 1, (17, 16), (16, 16), None),          # two wavefronts of one head each; ragged token tile
+    (528, 3, 256, 1, (22, 24), (64, 64), None),         # a head across two wavefronts; D = 768: three tiles of 256
     (96, 5, 64, 1, (2, 4, 12), (10, 11, 11), None),     # three axes, pair split off the 2-pair grid; D = 320: ragged feature tile
     (512, 4, 128, 4, (16, 32), (40, 24), 2),            # one rank of four
-    (384, 4, 64, 1, (2, 4, 48), (1, 15, 16), None),     # an axis of one pair: the rotation table is read from global memory
-    (12288, 4, 64, 1, (12288,), (32,), None),           # a table (3 MB) that does not fit LDS: global memory again
+    (384, 4, 64, 1, (2, 4, 48), (1, 15, 16), None),     # an axis of one pair
+    (12288, 4, 64, 1, (12288,), (32,), None),           # one axis, a table of 3 MB
     (608, 4, 128, 1, (19, 32), (63, 1), None),          # the fastest axis one pair wide
     (416, 8, 64, 1, (13, 32), (12, 20), None),          # two feature tiles, ragged third token tile
 ])
@@ -494,7 +494,7 @@ def test_proj_fused_random_small_shapes(oracle, N, H, d, P, grid, pairs):
 
 @gpu
 @pytest.mark.parametrize("N,H,d,grid,pairs,tile_tokens", [
-    (9120, 24, 128, (48, 190), (32, 32), 224),          # 41 x 12 x 3 tiles of 224 tokens, the last row 160 tokens; table 63 KB in LDS
+    (9120, 24, 128, (48, 190), (32, 32), 224),          # 41 x 12 x 3 tiles of 224 tokens, the last row 160 tokens
     (20720, 47, 64, (37, 16, 35), (10, 11, 11), 256),   # 81 x 12 x 3 tiles of 256 tokens, ragged in tokens (240) and features (192)
 ])
 def test_proj_fused_ragged_tiles_of_224_and_256_tokens(oracle, N, H, d, grid, pairs, tile_tokens):
