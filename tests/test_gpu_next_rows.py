@@ -1234,6 +1234,17 @@ def test_proj_fused_select_every_tile_shape(oracle, bm, bn, N, H, d):
 
 
 @gpu
+@pytest.mark.parametrize("N,H,grid", [(4608, 22, (64, 72)), (3600, 20, (45, 80)), (2304, 20, (48, 48)), (2304, 24, (48, 48))])
+def test_proj_fused_every_tile_of_a_few_rounds(oracle, N, H, grid):
+    """Launches of two to four rounds, whose tiles are walked in groups of 6, 5, 5 and 4 rows (29, 17, 15 and 12 rows of tiles, so
+    the last group has fewer): tokens of every row of tiles, all their features, against the oracle."""
+    d, D = 128, 128 * H
+    print(f"fused walk {N}x{D}", flush=True)
+    rng = np.random.default_rng(N + H)
+    _fused_case(oracle, N, D, H, d, 1, grid, (32, 32), _fused_inputs(rng, N, D, d), np.arange(5, N, 48), what=f"walk {N}x{D}")
+
+
+@gpu
 @pytest.mark.parametrize("N,H,d", [(272, 4, 64), (2304, 18, 64), (512, 4, 128), (528, 3, 256), (13616, 1, 256)])
 @pytest.mark.parametrize("sides", ["both", "above", "below"])
 def test_proj_fused_select_ties(oracle, N, H, d, sides):
