@@ -218,14 +218,25 @@ __global__ void __launch_bounds__(kStagedThreads) qkv_gemm_staged_kernel(GemmArg
 struct TileKernel {
     int bm, bn, lds;
     int per_cu;                   // workgroups that share a compute unit
+    int min_steps;                // K steps below which the shape is left out
     const void* entry[5];
 };
 
+// K steps from which on a launch may take the shapes that lie between the others, and counts its operands more dearly (tile_clocks).
+// What a shape between two others saves is operand bytes per unit (768 x 3072, Q and K fused, cold: 45.9 us with 96 x 256, 38.3 with
+// 160 x 128; V plain at 2304 x 3072 48.4 with 128 x 256, 43.9 with 160 x 192): with fewer steps the start, the first trip to memory
+// and the epilogue are as long as the K loop, and the estimate does not tell such shapes apart.
+constexpr int kLongSteps = 16;
+
 static const TileKernel* tile_shapes(bool whole_heads, int* count) {
-#define SHAPE(NI, NJ) {32 * NJ, 32 * NI, ring_lds_bytes(32 * NJ, 32 * NI), workgroups_per_unit(NI, NJ), {}},
-    static TileKernel plain[] = {COCODIFF_PLAIN_TILES(SHAPE)};
-    static TileKernel fused[] = {COCODIFF_FUSED_TILES(SHAPE)};
+#define SHAPE_FROM(STEPS, NI, NJ) {32 * NJ, 32 * NI, ring_lds_bytes(32 * NJ, 32 * NI), workgroups_per_unit(NI, NJ), STEPS, {}},
+#define SHAPE(NI, NJ) SHAPE_FROM(steps_ahead(32 * NJ, 32 * NI), NI, NJ)
+#define LONG_SHAPE(NI, NJ) SHAPE_FROM(kLongSteps, NI, NJ)
+    static TileKernel plain[] = {COCODIFF_PLAIN_TILES(SHAPE) COCODIFF_PLAIN_LONG_TILES(LONG_SHAPE)};
+    static TileKernel fused[] = {COCODIFF_FUSED_TILES(SHAPE) COCODIFF_FUSED_LONG_TILES(LONG_SHAPE)};
+#undef LONG_SHAPE
 #undef SHAPE
+#undef SHAPE_FROM
     constexpr int n_plain = sizeof(plain) / sizeof(plain[0]), n_fused = sizeof(fused) / sizeof(fused[0]);
     static const bool filled = [] {
         for (int i = 0; i < n_plain; ++i) {
@@ -245,16 +256,24 @@ static const TileKernel* tile_shapes(bool whole_heads, int* count) {
 }
 
 // Clocks of one workgroup's tile, fitted to the built shapes: a K step is 17.2 clocks per MFMA of a wavefront and 60 for its
-// barrier, or the operands' way through L2 (40 bytes per clock and unit) where that is longer; then the epilogue.  A round is one
-// tile per unit also where two workgroups share it: they share its matrix cores and its way to L2 too.
-// Against all shapes at 256 .. 20736 tokens x 256 .. 3072 features, one to three weights, both forms, inputs that change from pass
-// to pass (120 launches), the shape of least estimate is the fastest in 81 and within 3 % in 110.  Four of the others take 8 to
-// 9 us, as long as the host needs for the call; the rest are plain forms: 20736 x 256 with three weights 18.9 us for 15.9, the
-// other five 4 to 8 % off.
-static double tile_clocks(const TileKernel& t, int32_t D, bool whole_heads) {
+// barrier, or the operands' way through L1 where that is longer; then the epilogue.  A round is one tile per unit also where two
+// workgroups share it: they share its matrix cores and its way to L2 too.
+// Operands: a unit keeps no more than about 36 KB of loads in flight whatever the rings hold (streaming reads of 128-byte row
+// pieces by one workgroup per unit, any number of steps ahead: 45 GB/s and unit out of memory, 78 out of the last-level cache), so
+// its rate is that over the latency: 37 to 40 bytes per clock out of L2.
+// From kLongSteps K steps on, a byte costs another 0.016 clocks where all units are busy (traffic and clock that they share),
+// and the epilogue counts twice: without that, launches of many rounds took tiles of 160 x 256 and 192 x 192 for a last round a
+// little fuller.  Cold inputs, three weights: 5120 x 2560 fused 199.8 us with 160 x 256, 161.6 with 224 x 256; 6144 x 3072 plain
+// 287.6 with 192 x 192, 259.9 with 256 x 256; 12480 x 1536 plain 161.3 with 192 x 256, 144.7 with 256 x 256.
+// Against all shapes at 768 .. 26000 tokens x 1024 .. 3072 features, one to three weights, both forms, cold inputs (110 launches):
+// 0.2 % slower than the best shape on average, 6.3 % at worst; 0.8 % and 24 % with the estimate of short launches.  That one stands for
+// fewer K steps: 256 .. 20736 tokens x 256 .. 3072 features (120 launches), fastest in 81 and within 3 % in 110, the others
+// host-bound or plain and 4 to 8 % off but for 20736 x 256 with three weights (18.9 us for 15.9).
+static double tile_clocks(const TileKernel& t, int32_t D, bool whole_heads, double units_busy) {
+    const bool is_long = D / BK >= kLongSteps;
     const double mfmas = (t.bm / 32) * (t.bn / 32) * 2.0, operand_bytes = (t.bm + t.bn) * BK * 2.0;
-    const double step = std::max(mfmas * 17.2 + 60.0, operand_bytes / 40.0);
-    return (D / BK) * step + (whole_heads ? 2500.0 + 100.0 * mfmas : 1500.0 + 50.0 * mfmas);
+    const double step = std::max(mfmas * 17.2 + 60.0, operand_bytes / (is_long ? 37.0 : 40.0)) + (is_long ? operand_bytes * 0.016 * units_busy : 0.0);
+    return (D / BK) * step + (whole_heads ? 2500.0 + 100.0 * mfmas : 1500.0 + 50.0 * mfmas) * (is_long ? 2.0 : 1.0);
 }
 
 struct LaunchPlan {
@@ -280,10 +299,11 @@ static LaunchPlan plan_launch(int32_t M, int32_t D, int32_t n_tensors, bool whol
     double best = 0.0;
     for (int i = 0; i < n_shapes; ++i) {
         const TileKernel& t = shapes[i];
-        if (D / BK < steps_ahead(t.bm, t.bn)) continue;      // the rings are filled before the first step
+        if (D / BK < t.min_steps) continue;      // (the rings are filled before the first step)
         if (whole_heads && (d > t.bn || (flags && D > 16 * t.bn))) continue;      // a head spans two wavefronts at most; 16 flag bytes per token tile
         const int64_t tiles = (int64_t)((M + t.bm - 1) / t.bm) * ((D + t.bn - 1) / t.bn) * n_tensors;
-        const double cost = (double)((tiles + n_cu - 1) / n_cu) * tile_clocks(t, D, whole_heads);
+        const int64_t rounds = (tiles + n_cu - 1) / n_cu;
+        const double cost = (double)rounds * tile_clocks(t, D, whole_heads, (double)tiles / (double)(rounds * n_cu));
         if (forced_tile ? forced_tile == t.bm * 1000 + t.bn : (!p.pick || cost < best)) {
             p.pick = &t;
             best = cost;

@@ -860,11 +860,14 @@ __global__ void __launch_bounds__(256, workgroups_per_unit(NI, NJ)) qkv_gemm_dir
     }
 }
 
-// Tile shapes (NI, NJ) that are built: 32 NI features x 32 NJ tokens.
+// Tile shapes (NI, NJ) that are built: 32 NI features x 32 NJ tokens.  The LONG ones lie between the others and are taken for
+// launches of kLongSteps K steps and more only (plan_launch).
 #define COCODIFF_PLAIN_TILES(F) F(8, 8) F(6, 9) F(6, 6) F(8, 4) F(4, 8) F(8, 3) F(4, 4) F(6, 3) F(4, 3) F(6, 2) F(4, 2) F(2, 2) F(2, 1)
+#define COCODIFF_PLAIN_LONG_TILES(F) F(8, 6) F(6, 7) F(6, 5) F(6, 4) F(2, 3)
 #define COCODIFF_FUSED_TILES(F) F(8, 8) F(8, 7) F(8, 6) F(8, 5) F(8, 4) F(8, 3) F(8, 2) F(4, 8) F(4, 4) F(4, 3) F(4, 2) F(4, 1)
+#define COCODIFF_FUSED_LONG_TILES(F) F(4, 7) F(4, 6) F(4, 5)
 
-// Host pointers of the kernels of one layout, in the order of the list above; one source file each.
+// Host pointers of the kernels of one layout, in the order of the lists above; one source file each.
 extern const void* const kSeqKernels[];
 extern const void* const kChunkKernels[];
 extern const void* const kHeadKernels[];

@@ -4,7 +4,7 @@
 namespace cocodiff {
 
 #define ENTRY(NI, NJ) (const void*)qkv_gemm_direct_kernel<NI, NJ, OUT_SEQ>,
-const void* const kSeqKernels[] = {COCODIFF_PLAIN_TILES(ENTRY)};
+const void* const kSeqKernels[] = {COCODIFF_PLAIN_TILES(ENTRY) COCODIFF_PLAIN_LONG_TILES(ENTRY)};
 #undef ENTRY
 
 }  // namespace cocodiff

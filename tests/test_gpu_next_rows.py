@@ -1233,6 +1233,26 @@ def test_proj_fused_select_every_tile_shape(oracle, bm, bn, N, H, d):
                        1e-3, max(1, N // 48), cd.SEND_MAJOR, sparse=True, what=f"flagged tile {bm}x{bn}")
 
 
+# The shapes that only launches of 16 K steps and more take: one round of ragged tiles, and several.
+@gpu
+@pytest.mark.parametrize("bm,bn,N,H,n_tensors", [
+    (192, 256, 2736, 19, 3), (192, 256, 5472, 19, 3), (224, 192, 2720, 17, 3), (224, 192, 5440, 17, 3), (160, 192, 1904, 17, 3),
+    (160, 192, 3696, 21, 3), (128, 192, 1360, 17, 3), (96, 64, 544, 17, 2),
+])
+def test_proj_every_long_tile_shape(oracle, bm, bn, N, H, n_tensors):
+    test_proj_every_tile_shape(oracle, bm, bn, N, H, n_tensors)
+
+
+@gpu
+@pytest.mark.parametrize("bm,bn,N,H,d", [
+    (224, 128, 1872, 9, 128), (224, 128, 1904, 17, 64), (192, 128, 1584, 9, 128), (192, 128, 1632, 17, 64), (160, 128, 1296, 9, 128),
+    (160, 128, 1008, 21, 64),
+])
+def test_proj_fused_every_long_tile_shape(oracle, bm, bn, N, H, d):
+    test_proj_fused_every_tile_shape(oracle, bm, bn, N, H, d)
+    test_proj_fused_select_every_tile_shape(oracle, bm, bn, N, H, d)
+
+
 @gpu
 @pytest.mark.parametrize("N,H,grid", [(4608, 22, (64, 72)), (3600, 20, (45, 80)), (2304, 20, (48, 48)), (2304, 24, (48, 48))])
 def test_proj_fused_every_tile_of_a_few_rounds(oracle, N, H, grid):
