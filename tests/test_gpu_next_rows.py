@@ -71,6 +71,34 @@ def test_second_all_to_all_rank_ranges(oracle):
     assert np.array_equal(got[3 * cfg.Ns:7 * cfg.Ns], y.transpose(1, 0, 2)[3 * cfg.Ns:7 * cfg.Ns])
 
 
+# Divisors of one, of odd numbers and of powers of two, a last workgroup that is not full, and either side of the size from which a
+# lane moves one vector instead of two (20 MB: 3408 and 3424 tokens of 24 heads of 128).
+@gpu
+@pytest.mark.parametrize("N,H,d,P", [(16, 1, 8, 1), (48, 3, 8, 3), (336, 7, 24, 7), (1040, 5, 72, 1), (5 * 16 * 6, 10, 40, 5), (9 * 16, 9, 264, 9),
+                                     (3408, 24, 128, 1), (3424, 24, 128, 2), (3456, 24, 128, 24)])
+def test_permutations_odd_shapes(oracle, N, H, d, P):
+    import torch
+    print(f"permutations {N} tokens, {H} heads of {d}, {P} ranks", flush=True)
+    G = 64
+    rng = np.random.default_rng(N + H * d)
+    x = rng.integers(0, 65536, size=(N, H, d), dtype=np.uint16)
+    y = np.ascontiguousarray(x.transpose(1, 0, 2))
+    xd, yd = to_dev(x), to_dev(y)
+    ranges = [(0, P)] if P == 1 else [(0, 1), (1, P - 1)]
+    for order in (cd.SEND_MAJOR, cd.RECV_MAJOR):
+        for pack, unpack, src, want_buf, want_out in ((cd.a2a_pack, cd.a2a_unpack, xd, oracle.a2a_pack(x, P, order), y),
+                                                      (cd.a2a_pack_hs, cd.a2a_unpack_seq, yd, oracle.a2a_pack_hs(y, P, order), x)):
+            buf, out = (torch.full((N * H * d + G,), 0x5A5A, dtype=torch.int16, device="cuda:0") for _ in range(2))
+            for begin, count in ranges:
+                pack(cd.Shape.make(N, H * d, H, d, P, begin, count), src, buf[:N * H * d], order)
+            for begin, count in ranges:
+                unpack(cd.Shape.make(N, H * d, H, d, P, begin, count), buf[:N * H * d], out[:N * H * d], order)
+            _sync()
+            assert np.array_equal(to_host_bits(buf)[:N * H * d], want_buf.reshape(-1))
+            assert np.array_equal(to_host_bits(out)[:N * H * d], want_out.reshape(-1))
+            assert bool((buf[N * H * d:] == 0x5A5A).all().cpu()) and bool((out[N * H * d:] == 0x5A5A).all().cpu())
+
+
 @gpu
 @pytest.mark.parametrize("name", ["C1", "C3", "C4", "C5"])
 def test_gather_and_scatter_close_the_selection_loop(oracle, name):
