@@ -4,7 +4,7 @@
 //
 //   token_metric_kernel -- one wavefront per token streams the token's value vector from both tensors once
 //                          (HBM-bound), fp32 sum of |cur - prev| per lane, wavefront tree reduction;
-//   topk_kernel         -- one workgroup per segment (a logical rank's tokens), keys cached in LDS: the K-th largest
+//   topk_kernel         -- one workgroup per segment (a logical rank's tokens), keys in registers: the K-th largest
 //                          key by histograms over a range of keys that each pass narrows, then an
 //                          index-ordered compaction that takes every token above the threshold and the
 //                          lowest-indexed tokens equal to it until K are taken.
@@ -63,11 +63,11 @@ __device__ __forceinline__ uint32_t metric_key(float m) {
 
 constexpr int kTopkThreads = 1024;
 constexpr int kTopkWaves = kTopkThreads / 64;
-constexpr int kTopkUnroll = 8;                // metric values a lane has in flight
+constexpr int kTopkUnroll = 8;                // metric values a lane has in flight where the keys are not kept
 constexpr int kTopkBinBits = 11;              // bins of a pass: two per lane
-constexpr uint32_t kTopkCachedKeys = 32768;   // keys of one segment kept in LDS (128 KB) when they fit
 
-// Exclusive prefix sum of `v` over the workgroup in thread order; `total` gets the workgroup's sum.
+// Exclusive prefix sum of `v` over the workgroup in thread order; `total` gets the workgroup's sum.  (The caller has a barrier
+// between two calls: wave_tot is read to the end.)
 __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* wave_tot, uint32_t& total) {
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     uint32_t incl = v;
@@ -76,7 +76,6 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* wave_tot, u
         const uint32_t up = __shfl_up(incl, off, 64);
         if (lane >= (uint32_t)off) incl += up;
     }
-    __syncthreads();                               // wave_tot may still be read from the previous call
     if (lane == 63) wave_tot[wave] = incl;
     __syncthreads();
     uint32_t before = 0, tot = 0;
@@ -90,19 +89,21 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* wave_tot, u
     return before + incl - v;
 }
 
-// One workgroup per segment (a logical rank's tokens).  CACHED: the segment's keys sit in LDS after one read of
-// the metric; otherwise every pass reads the metric again (L2-resident).
-// One workgroup's chain of passes: bound by latency (barriers, LDS atomics on one address), not by bytes.  So the bins of a
-// pass divide the range the keys really have -- smallest to largest key first, then the bin that holds the K-th largest --
-// into 2048: digits at fixed places put most keys of a metric, which share sign and exponent, on one address, whose atomics
-// are served one at a time.  Three passes at most; a pass whose bin is taken whole is the last.  (12480 tokens, a metric of two
-// clusters: the token update around it 142.8 us with four passes over fixed bytes, 134.1 so.)
-// The list is written by 64 neighbouring tokens at a time (ballots), each wavefront its own run of them.
-template <bool CACHED>
+// One workgroup per segment (a logical rank's tokens); wavefront w owns a run of `steps` 64 neighbouring tokens.  STEPS > 0: a lane
+// keeps the keys of its (at most STEPS) tokens in registers after one read of the metric; 0: every pass reads the metric again
+// (L2-resident), kTopkUnroll values in flight.
+// One workgroup's chain of passes: bound by latency (the trip to memory, barriers, LDS atomics on one address), not by bytes.
+// So the metric is asked for in one burst, and the bins of a pass divide the range the keys really have -- smallest to largest
+// key first, then the bin that holds the K-th largest -- into 2048: digits at fixed places put most keys of a metric, which share
+// sign and exponent, on one address, whose atomics are served one at a time.  Three passes at most; a pass whose bin is taken whole
+// is the last.  (12480 tokens, a metric of two clusters: the token update around it 142.8 us with four passes over fixed
+// bytes, 133.5 so with the keys in LDS, eight loads in flight; 130.8 with the keys in registers and all loads in flight.  29520
+// tokens 229.4 -> 224.4; 43632 tokens, not kept, 349.5 -> 348.0.)
+// The list is written by 64 neighbouring tokens at a time (ballots).
+template <int STEPS>
 __global__ void __launch_bounds__(kTopkThreads) topk_kernel(const float* __restrict__ metric, uint32_t N, uint32_t K,
                                                             int32_t* __restrict__ idx, int32_t* __restrict__ n_active,
                                                             uint32_t id_stride) {
-    extern __shared__ uint32_t s_keys[];
     constexpr uint32_t kBins = 1u << kTopkBinBits;
     static_assert(kBins == 2 * kTopkThreads, "two bins per lane");
     __shared__ __align__(8) uint32_t hist[kBins];
@@ -114,20 +115,36 @@ __global__ void __launch_bounds__(kTopkThreads) topk_kernel(const float* __restr
     const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (threadIdx.x == 0) n_active[blockIdx.x] = (int32_t)K;
     if (K == 0) return;
+    const uint32_t steps = (N + kTopkThreads - 1) / kTopkThreads, run = wave * steps * 64u;
+    // f(s, key) for the keys of this lane's tokens run + 64 s + lane; beyond the segment's end the key is 0, which no metric has
+    // (the smallest is that of -infinity) and which lies outside every range of real keys
+    constexpr int kGroup = STEPS ? STEPS : kTopkUnroll;
+    uint32_t kept[kGroup];
+    auto load = [&](uint32_t s0) __attribute__((always_inline)) {
+        float m[kGroup];
+#pragma unroll
+        for (int k = 0; k < kGroup; ++k) m[k] = metric[min(run + 64u * (s0 + k) + lane, N - 1u)];
+#pragma unroll
+        for (int k = 0; k < kGroup; ++k) {
+            const uint32_t s = s0 + k;
+            kept[k] = s < steps && run + 64u * s + lane < N ? metric_key(m[k]) : 0u;
+        }
+    };
+    auto for_keys = [&](auto f) __attribute__((always_inline)) {
+        for (uint32_t s0 = 0; s0 < (STEPS ? 1u : steps); s0 += kGroup) {
+            if (!STEPS) load(s0);
+#pragma unroll
+            for (int k = 0; k < kGroup; ++k)
+                if (s0 + k < steps) f(s0 + k, kept[k]);
+        }
+    };
+    if (STEPS) load(0);
     // ---- the keys' range
     uint32_t low = 0xFFFFFFFFu, high = 0;
-    for (uint32_t n0 = threadIdx.x; n0 < N; n0 += kTopkUnroll * kTopkThreads) {
-        float m[kTopkUnroll];
-#pragma unroll
-        for (int k = 0; k < kTopkUnroll; ++k) m[k] = metric[min(n0 + k * kTopkThreads, N - 1u)];   // (the last one again beyond the end)
-#pragma unroll
-        for (int k = 0; k < kTopkUnroll; ++k) {
-            const uint32_t key = metric_key(m[k]);
-            low = min(low, key);
-            high = max(high, key);
-            if (CACHED && n0 + k * kTopkThreads < N) s_keys[n0 + k * kTopkThreads] = key;
-        }
-    }
+    for_keys([&](uint32_t, uint32_t key) __attribute__((always_inline)) {
+        low = min(low, key ? key : 0xFFFFFFFFu);
+        high = max(high, key);
+    });
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         low = min(low, (uint32_t)__shfl_xor(low, off, 64));
@@ -144,16 +161,15 @@ __global__ void __launch_bounds__(kTopkThreads) topk_kernel(const float* __restr
         low = min(low, wave_min[w]);
         high = max(high, wave_max[w]);
     }
-    auto key_at = [&](uint32_t n) { return CACHED ? s_keys[n] : metric_key(metric[n]); };
     // ---- the K-th largest key: in [low, low + range], the `remaining`-th largest there
     uint32_t range = high - low, remaining = K;
     bool whole;      // every key of the last bin is taken
     for (;;) {
         const int bits = range ? 32 - __clz((int)range) : 0, shift = bits > kTopkBinBits ? bits - kTopkBinBits : 0;
-        for (uint32_t n = threadIdx.x; n < N; n += kTopkThreads) {
-            const uint32_t off = key_at(n) - low;
+        for_keys([&](uint32_t, uint32_t key) __attribute__((always_inline)) {
+            const uint32_t off = key - low;
             if (off <= range) atomicAdd(&hist[off >> shift], 1u);
-        }
+        });
         __syncthreads();
         // bins from the top, two per lane; `above` = keys of the range in higher bins
         const uint32_t top = kBins - 1u - 2u * threadIdx.x;
@@ -172,26 +188,23 @@ __global__ void __launch_bounds__(kTopkThreads) topk_kernel(const float* __restr
         }
         __syncthreads();
         low += s_bin << shift;
-        range = (1u << shift) - 1u;
+        range = min((1u << shift) - 1u, 0xFFFFFFFFu - low);      // (not past the largest key, to the key 0 of no token)
         remaining = s_remaining;
         whole = remaining == s_count;
         if (whole || shift == 0) break;
     }
-    // ---- compaction in index order: take keys above `low`, and equal to it while there is room (`whole`: from `low` up);
-    // wavefront w owns a run of `steps` 64 tokens
-    const uint32_t steps = (N + kTopkThreads - 1) / kTopkThreads, run = wave * steps * 64u;
-    auto look = [&](uint32_t s, uint64_t& above, uint64_t& equal) __attribute__((always_inline)) {
-        const uint32_t n = run + 64u * s + lane, key = n < N ? key_at(n) : 0u;
-        above = __ballot(n < N && (key > low || (whole && key == low)));
-        equal = __ballot(n < N && !whole && key == low);
+    // ---- compaction in index order: take keys above `low`, and equal to it while there is room (`whole`: from `low` up)
+    auto look = [&](uint32_t key, uint64_t& above, uint64_t& equal) __attribute__((always_inline)) {
+        above = __ballot(key > low || (whole && key == low));
+        equal = __ballot(!whole && key == low);
     };
     uint32_t n_above = 0, n_equal = 0;
-    for (uint32_t s = 0; s < steps; ++s) {
+    for_keys([&](uint32_t, uint32_t key) __attribute__((always_inline)) {
         uint64_t above, equal;
-        look(s, above, equal);
+        look(key, above, equal);
         n_above += __popcll(above);
         n_equal += __popcll(equal);
-    }
+    });
     if (lane == 0) {
         wave_min[wave] = n_above;
         wave_max[wave] = n_equal;
@@ -204,17 +217,17 @@ __global__ void __launch_bounds__(kTopkThreads) topk_kernel(const float* __restr
     }
     const uint32_t rest = whole ? 0u : remaining;      // equal keys taken in all, the lowest-indexed ones
     pos += min(equal_before, rest);
-    for (uint32_t s = 0; s < steps; ++s) {
+    const uint64_t before = (1ull << lane) - 1ull;
+    for_keys([&](uint32_t s, uint32_t key) __attribute__((always_inline)) {
         uint64_t above, equal;
-        look(s, above, equal);
-        const uint64_t before = (1ull << lane) - 1ull;
+        look(key, above, equal);
         const uint32_t equal_here = equal_before + __popcll(equal & before);
         const bool take_equal = ((equal >> lane) & 1u) && equal_here < rest;
         const uint64_t taken = above | __ballot(take_equal);
         if ((taken >> lane) & 1u) idx[pos + __popcll(taken & before)] = (int32_t)(id_base + run + 64u * s + lane);
         pos += __popcll(taken);
         equal_before += __popcll(equal);
-    }
+    });
 }
 
 }  // namespace cocodiff
@@ -243,18 +256,15 @@ extern "C" int cocodiff_vmajor_topk(int32_t n_seg, int32_t N, const float* metri
     if ((int64_t)n_seg * N >= ((int64_t)1 << 31)) return fail(COCODIFF_ERR_SHAPE, "topk: n_seg * N must be below 2^31");
     if (n_keep < 0 || n_keep > N) return fail(COCODIFF_ERR_SHAPE, "topk: n_keep (%d) must be in [0, N = %d]", n_keep, N);
     if (!metric || !active_idx || !n_active) return fail(COCODIFF_ERR_NULL, "topk: NULL pointer");
-    if ((uint32_t)N <= kTopkCachedKeys) {
-        static int lds_ok = [] {
-            return (int)hipFuncSetAttribute((const void*)topk_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                            (int)(kTopkCachedKeys * sizeof(uint32_t)));
-        }();
-        if (lds_ok != (int)hipSuccess) return fail(COCODIFF_ERR_HIP, "topk: cannot raise the kernel's LDS limit");
-        hipLaunchKernelGGL(topk_kernel<true>, dim3(n_seg), dim3(kTopkThreads), (size_t)N * sizeof(uint32_t), as_stream(stream),
-                           metric, (uint32_t)N, (uint32_t)n_keep, active_idx, n_active, global_ids ? (uint32_t)N : 0u);
-    } else {
-        hipLaunchKernelGGL(topk_kernel<false>, dim3(n_seg), dim3(kTopkThreads), 0, as_stream(stream), metric, (uint32_t)N,
-                           (uint32_t)n_keep, active_idx, n_active, global_ids ? (uint32_t)N : 0u);
-    }
+    const auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(n_seg), dim3(kTopkThreads), 0, as_stream(stream), metric, (uint32_t)N, (uint32_t)n_keep, active_idx,
+                           n_active, global_ids ? (uint32_t)N : 0u);
+    };
+    // keys in registers up to 32 per lane: 16 wavefronts of a workgroup leave each 128 registers
+    if (N <= 4 * kTopkThreads) launch(topk_kernel<4>);
+    else if (N <= 16 * kTopkThreads) launch(topk_kernel<16>);
+    else if (N <= 32 * kTopkThreads) launch(topk_kernel<32>);
+    else launch(topk_kernel<0>);
     return check_launch("topk_kernel");
 }
 

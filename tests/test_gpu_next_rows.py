@@ -1359,3 +1359,26 @@ def test_topk_key_ranges_and_lengths(oracle, N, values):
         got = idx.cpu().numpy()
         assert int(n_act.cpu()[0]) == k and np.all(got[k:] == -1)
         assert np.array_equal(got[:k], oracle.topk_active(m.astype(np.float64), k)), (N, values, k)
+
+
+@gpu
+@pytest.mark.parametrize("N", [4095, 4096, 4097, 16384, 16385, 32767])
+def test_topk_edges_of_the_keys_a_lane_keeps(oracle, N):
+    """Segments on both sides of the lengths at which a lane keeps more keys, two segments so that the second one's bounds count;
+    infinities, NaN, both zeros and ties: exactly the oracle's lists, nothing behind them."""
+    import torch
+    rng = np.random.default_rng(N)
+    m = (rng.integers(0, 400, size=(2, N)) * 0.25 - 20.0).astype(np.float32)
+    for value in (np.nan, np.inf, -np.inf, -0.0, 0.0):
+        m[rng.random((2, N)) < 0.01] = value
+    m[:, -1] = -np.inf
+    md = torch.from_numpy(m).to("cuda:0")
+    idx, n_act = dev_empty((2, N), "i32"), dev_empty((2,), "i32")
+    for k in (1, N // 200, N // 2, N - 1, N):
+        idx.fill_(-1)
+        cd.vmajor_topk(2, N, md, k, idx, n_act)
+        _sync()
+        got = idx.cpu().numpy()
+        assert n_act.cpu().tolist() == [k, k] and np.all(got[:, k:] == -1)
+        for g in range(2):
+            assert np.array_equal(got[g, :k], oracle.topk_active(m[g].astype(np.float64), k)), (g, k)
