@@ -98,23 +98,18 @@ __device__ __forceinline__ uint32_t div_by(uint32_t n, const Divisor& f) {
     return f.d == 1u ? n : __umulhi(n, f.magic);
 }
 
-// The same for any dividend below 2^31: multiply-high by ceil(2^(31+s) / d), s = ceil(log2 d), and a shift by s - 1.  (The magic
+// The same for any dividend below 2^31: multiply-high of 2 n by ceil(2^(31+s) / d), s = ceil(log2 d), and a shift by s.  (The magic
 // exceeds 2^(31+s) / d by less than 1, so the quotient's error stays below n / 2^(31+s) < 2^-s <= 1 / d: too little to reach
-// the next whole number.)
+// the next whole number.)  1 is no special case: a branch would put a wait for the arguments behind it into every division.
 struct Divisor31 {
-    uint32_t d, magic, shift;
+    uint32_t magic, shift;
 };
 inline Divisor31 make_divisor31(uint32_t d) {
-    Divisor31 f{d ? d : 1u, 0u, 0u};
-    if (f.d > 1u) {
-        const uint32_t s = 32u - (uint32_t)__builtin_clz(f.d - 1u);
-        f.magic = (uint32_t)((((uint64_t)1 << (31 + s)) + f.d - 1) / f.d);
-        f.shift = s - 1u;
-    }
-    return f;
+    const uint32_t s = d > 1u ? 32u - (uint32_t)__builtin_clz(d - 1u) : 0u;
+    return {(uint32_t)((((uint64_t)1 << (31 + s)) + (d ? d : 1u) - 1) / (d ? d : 1u)), s};
 }
 __host__ __device__ __forceinline__ uint32_t div_by(uint32_t n, const Divisor31& f) {
-    return f.d == 1u ? n : (uint32_t)(((uint64_t)n * f.magic) >> 32) >> f.shift;
+    return (uint32_t)(((uint64_t)(n << 1) * f.magic) >> 32) >> f.shift;
 }
 
 // ---- device helpers -------------------------------------------------------

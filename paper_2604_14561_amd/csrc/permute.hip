@@ -11,113 +11,107 @@ namespace cocodiff {
 
 constexpr int kThreads = 256;
 
-struct PermuteArgs {
-    uint32_t Ns, P, D8, d8, row8, chunk8, Hp;
-    Divisor31 div_Ns, div_P, div_D8, div_d8, div_row8, div_chunk8, div_Hp, div_head8, div_ranks;
-    uint32_t N;           // tokens in total
-    uint32_t first;       // walk over x_seq: first token of the range; walk over x_hs: first head of the range
-    uint32_t n_vec;       // vectors this launch moves
-    int recv_major;
-    uint32_t rank_begin, rank_count;     // the launch's ranks (buffer walks)
-};
-
-__device__ __forceinline__ uint32_t slot_of(uint32_t sender, uint32_t receiver, uint32_t P, int recv_major) {
-    return recv_major ? receiver * P + sender : sender * P + receiver;
-}
-
 // Every kernel walks its OUTPUT linearly in 16-byte vectors: stores that run linearly through memory and loads that gather
 // 512- or 256-byte pieces are faster than the other way round (cold, 57 MB tensors: 20 against 21.5 us).  Bound by HBM, and below
-// some 20 MB by the launch and the start of its workgroups (an empty launch takes 2.6 us): so the index arithmetic is
-// multiplications, and small tensors are moved with two vectors per lane (vectors_per_lane).
-// A walk maps vector g of its output to where it is written (to) and where it is read (from).
+// some 20 MB by the launch and the start of its workgroups (an empty launch takes 2.6 us).
+// A launch's arguments lie in host memory, a trip of about a microsecond for whoever reads a line of them first; so they are few
+// (the chunk strides folded into two factors), and all are asked for before the first branch (settled).  Twice as many, read where
+// they were needed, cost a call 0.3 to 0.6 us: the stand-alone calls at 4608 x 2048 189.2 -> 186.8 us, a small pack and unpack pair
+// 11.0 -> 9.8.
+//
+// A walk maps vector g of its output to where it is read (from) and written (to): all below N*D/8 < 2^31, in arithmetic modulo 2^32.
+// rs, ps: what one token owner r, one head owner p further means in the buffer, in vectors.
 
 // Exchange buffer -> sequence-parallel tensor [N][H][d] (second all-to-all: sender = head owner p, receiver = token
 // owner r), linearly over the token range of the launch.
 struct SeqFromBuf {
-    static __device__ __forceinline__ void at(const PermuteArgs& a, uint32_t g, size_t& from, size_t& to) {
-        const uint32_t tl = div_by(g, a.div_D8);      // token within the range
-        const uint32_t v = g - tl * a.D8;             // vector within the token row
-        const uint32_t n = a.first + tl;              // global token
-        const uint32_t r = div_by(n, a.div_Ns);       // token owner
-        const uint32_t m = n - r * a.Ns;              // token within the rank
-        const uint32_t p = div_by(v, a.div_row8);     // head owner
-        const uint32_t c = v - p * a.row8;            // (hl, i) within the chunk row
-        to = (size_t)n * a.D8 + v;
-        from = (size_t)slot_of(p, r, a.P, a.recv_major) * a.chunk8 + m * a.row8 + c;
+    uint32_t n_vec, D8, first, to0, row8;       // first: first token of the range
+    uint32_t per_r, per_p;                      // rs - chunk8, ps - row8: the rest of them is in n * row8 and v
+    Divisor31 div_D8, div_Ns, div_row8;
+    __device__ __forceinline__ void at(uint32_t g, uint32_t& from, uint32_t& to) const {
+        const uint32_t tl = div_by(g, div_D8), v = g - tl * D8;       // token within the range, vector within the token row
+        const uint32_t n = first + tl, r = div_by(n, div_Ns), p = div_by(v, div_row8);
+        from = n * row8 + r * per_r + v + p * per_p;
+        to = to0 + g;
     }
 };
 
 // Exchange buffer -> head-parallel tensor [H][N][d] (first all-to-all: sender = token owner r, receiver = head owner
 // p), linearly over the head range of the launch.
 struct HeadsFromBuf {
-    static __device__ __forceinline__ void at(const PermuteArgs& a, uint32_t g, size_t& from, size_t& to) {
-        const uint32_t head8 = a.N * a.d8;            // vectors per head slab
-        const uint32_t hl_range = div_by(g, a.div_head8);
-        const uint32_t rem = g - hl_range * head8;
-        const uint32_t h = a.first + hl_range;        // global head
-        const uint32_t n = div_by(rem, a.div_d8);     // global token
-        const uint32_t i8 = rem - n * a.d8;
-        const uint32_t p = div_by(h, a.div_Hp);       // head owner
-        const uint32_t hl = h - p * a.Hp;
-        const uint32_t r = div_by(n, a.div_Ns);       // token owner
-        const uint32_t m = n - r * a.Ns;
-        to = (size_t)a.first * head8 + g;
-        from = (size_t)slot_of(r, p, a.P, a.recv_major) * a.chunk8 + m * a.row8 + hl * a.d8 + i8;
+    uint32_t n_vec, head8, first, to0, row8, d8;       // head8: vectors per head slab; first: first head of the range
+    uint32_t per_r, per_p;                             // as above, of n * row8 and h * d8
+    Divisor31 div_head8, div_d8, div_Ns, div_Hp;
+    __device__ __forceinline__ void at(uint32_t g, uint32_t& from, uint32_t& to) const {
+        const uint32_t hl_range = div_by(g, div_head8), rem = g - hl_range * head8, h = first + hl_range;
+        const uint32_t n = div_by(rem, div_d8), i8 = rem - n * d8, r = div_by(n, div_Ns), p = div_by(h, div_Hp);
+        from = n * row8 + r * per_r + h * d8 + p * per_p + i8;
+        to = to0 + g;
     }
 };
 
-// The packing directions: vector g of the launch is vector g of the chunks the launch's ranks send, in buffer order.
+// The packing directions: vector g of the launch is vector g of the chunks the launch's ranks send, in buffer order: chunk (hi, lo)
+// with lo fastest, one of the two the sender within the rank range, the other the receiver.
+struct Chunks {
+    uint32_t n_vec, chunk8, row8, n_lo;
+    uint32_t from_hi, from_lo, from0;           // where chunk (hi, lo) begins in the tensor
+    uint32_t to_hi, to0;                        // and in the buffer, where lo steps by chunk8
+    Divisor31 div_chunk8, div_lo, div_row8;
+    __device__ __forceinline__ void split(uint32_t g, uint32_t& from, uint32_t& to, uint32_t& m, uint32_t& c) const {
+        const uint32_t ch = div_by(g, div_chunk8), rem = g - ch * chunk8, hi = div_by(ch, div_lo), lo = ch - hi * n_lo;
+        m = div_by(rem, div_row8);              // token within the rank
+        c = rem - m * row8;                     // (hl, i) within the chunk row
+        from = from0 + hi * from_hi + lo * from_lo;
+        to = to0 + hi * to_hi + lo * chunk8 + rem;
+    }
+};
+
 // Sequence-parallel tensor -> exchange buffer (first all-to-all): the senders are the token owners r of the rank range.
-struct BufFromSeq {
-    static __device__ __forceinline__ void at(const PermuteArgs& a, uint32_t g, size_t& from, size_t& to) {
-        const uint32_t ch = div_by(g, a.div_chunk8), rem = g - ch * a.chunk8;       // chunk of the launch, vector inside it
-        // send-major: chunks (r, p) with p fastest; receive-major: (p, r) with r fastest
-        const uint32_t q = a.recv_major ? div_by(ch, a.div_ranks) : div_by(ch, a.div_P);
-        const uint32_t r = a.rank_begin + (a.recv_major ? ch - q * a.rank_count : q);
-        const uint32_t p = a.recv_major ? q : ch - q * a.P;
-        const uint32_t m = div_by(rem, a.div_row8), c = rem - m * a.row8;
-        from = (size_t)(r * a.Ns + m) * a.D8 + p * a.row8 + c;
-        to = (size_t)slot_of(r, p, a.P, a.recv_major) * a.chunk8 + rem;
+struct BufFromSeq : Chunks {
+    uint32_t D8;
+    __device__ __forceinline__ void at(uint32_t g, uint32_t& from, uint32_t& to) const {
+        uint32_t m, c;
+        split(g, from, to, m, c);
+        from += m * D8 + c;
     }
 };
 
 // Head-parallel tensor -> exchange buffer (second all-to-all): the senders are the head owners p of the rank range.
-struct BufFromHeads {
-    static __device__ __forceinline__ void at(const PermuteArgs& a, uint32_t g, size_t& from, size_t& to) {
-        const uint32_t ch = div_by(g, a.div_chunk8), rem = g - ch * a.chunk8;
-        // send-major: chunks (p, r) with r fastest; receive-major: (r, p) with p fastest
-        const uint32_t q = a.recv_major ? div_by(ch, a.div_ranks) : div_by(ch, a.div_P);
-        const uint32_t p = a.rank_begin + (a.recv_major ? ch - q * a.rank_count : q);
-        const uint32_t r = a.recv_major ? q : ch - q * a.P;
-        const uint32_t m = div_by(rem, a.div_row8), c = rem - m * a.row8;           // token within the rank; (hl, i) within the chunk row
-        const uint32_t hl = div_by(c, a.div_d8), i8 = c - hl * a.d8;
-        from = ((size_t)(p * a.Hp + hl) * a.N + r * a.Ns + m) * a.d8 + i8;
-        to = (size_t)slot_of(p, r, a.P, a.recv_major) * a.chunk8 + rem;
+struct BufFromHeads : Chunks {
+    uint32_t d8, per_head;                      // per_head: vectors per head slab, less the d8 that c counts
+    Divisor31 div_d8;
+    __device__ __forceinline__ void at(uint32_t g, uint32_t& from, uint32_t& to) const {
+        uint32_t m, c;
+        split(g, from, to, m, c);
+        from += m * d8 + c + div_by(c, div_d8) * per_head;
     }
 };
 
+// The values are there before anything after this is decided: what they are formed from cannot be moved behind a branch.
+__device__ __forceinline__ void settled(uint32_t& a, uint32_t& b) { asm volatile("" : "+v"(a), "+v"(b)); }
+
 template <typename Walk, int U, bool NT_LD, bool NT_ST>
-__global__ void __launch_bounds__(kThreads) permute_kernel(const vec16* __restrict__ in, vec16* __restrict__ out, PermuteArgs a) {
+__global__ void __launch_bounds__(kThreads) permute_kernel(const vec16* __restrict__ in, vec16* __restrict__ out, Walk a) {
     const uint32_t g0 = blockIdx.x * (kThreads * U) + threadIdx.x;
     vec16 v[U];
-    size_t to[U];
+    uint32_t from[U], to[U];
 #pragma unroll
     for (int k = 0; k < U; ++k) {
-        const uint32_t g = g0 + k * kThreads;
-        if (g < a.n_vec) {
-            size_t from;
-            Walk::at(a, g, from, to[k]);
-            v[k] = ld_vec<NT_LD>(in + from);
-        }
+        a.at(min(g0 + k * kThreads, a.n_vec - 1u), from[k], to[k]);
+        settled(from[k], to[k]);
     }
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+        if (g0 + k * kThreads < a.n_vec) v[k] = ld_vec<NT_LD>(in + from[k]);
 #pragma unroll
     for (int k = 0; k < U; ++k)
         if (g0 + k * kThreads < a.n_vec) st_vec<NT_ST>(out + to[k], v[k]);
 }
 
-// Two vectors per lane below 20 MB.  A plain copy, cold, one and two per lane: 4.7 MB 3.0 and 3.1 us, 11.3 MB 5.5 and 5.0, 14.2 MB 6.4
-// and 5.4, 28.3 MB 11.1 and 11.2, 56.6 MB 19.8 and 20.1, 127 MB 41.8 and 43.2; four are slower at every size.
-static int vectors_per_lane(uint32_t n_vec) { return n_vec < (20u << 20) / 16u ? 2 : 1; }
+// Two vectors per lane from 8 to 16 MB.  Three packs and three unpacks between the other calls, cold, one and two per lane: 3.5 MB each
+// 64.4 and 64.9 us, 6.7 MB 66.8 and 67.2, 14.2 MB 170.2 and 168.5, 18.9 MB 187.0 and 188.8, 26.5 MB 204.4 and 206.6.  A plain copy: 4.7 MB
+// 3.0 and 3.1, 11.3 MB 5.5 and 5.0, 14.2 MB 6.4 and 5.4, 28.3 MB 11.1 and 11.2; four are slower at every size.
+static int vectors_per_lane(uint32_t n_vec) { return n_vec >= (8u << 20) / 16u && n_vec < (16u << 20) / 16u ? 2 : 1; }
 
 static int check_permute(const cocodiff_shape* s, const void* in, const void* out, int slot_order, const char* who) {
     int rc = check_shape(s);
@@ -131,36 +125,27 @@ static int check_permute(const cocodiff_shape* s, const void* in, const void* ou
     return COCODIFF_OK;
 }
 
-static PermuteArgs make_args(const cocodiff_shape* s, int slot_order) {
-    PermuteArgs a;
-    a.Ns = s->N / s->P;
-    a.P = s->P;
-    a.D8 = s->D / 8;
-    a.d8 = s->d / 8;
-    a.Hp = s->H / s->P;
-    a.row8 = a.Hp * a.d8;
-    a.chunk8 = a.Ns * a.row8;
-    a.N = s->N;
-    a.first = 0;
-    a.n_vec = 0;
-    a.recv_major = slot_order == COCODIFF_RECV_MAJOR;
-    a.rank_begin = (uint32_t)s->rank_begin;
-    a.rank_count = (uint32_t)s->rank_count;
-    // (every dividend is below N * D / 8, which is below 2^31)
-    a.div_Ns = make_divisor31(a.Ns);
-    a.div_P = make_divisor31(a.P);
-    a.div_D8 = make_divisor31(a.D8);
-    a.div_d8 = make_divisor31(a.d8);
-    a.div_row8 = make_divisor31(a.row8);
-    a.div_chunk8 = make_divisor31(a.chunk8);
-    a.div_Hp = make_divisor31(a.Hp);
-    a.div_head8 = make_divisor31(a.N * a.d8);
-    a.div_ranks = make_divisor31(a.rank_count);
-    return a;
-}
+// Sizes in vectors, and the buffer's strides: slot (receiver, sender) or (sender, receiver), the second fastest.
+struct Sizes {
+    uint32_t Ns, D8, d8, Hp, row8, chunk8, head8, begin, count, rs, ps;
+    Sizes(const cocodiff_shape* s, int slot_order, bool r_sends) {
+        Ns = (uint32_t)(s->N / s->P);
+        D8 = (uint32_t)s->D / 8u;
+        d8 = (uint32_t)s->d / 8u;
+        Hp = (uint32_t)(s->H / s->P);
+        row8 = Hp * d8;
+        chunk8 = Ns * row8;
+        head8 = (uint32_t)s->N * d8;
+        begin = (uint32_t)s->rank_begin;
+        count = (uint32_t)s->rank_count;
+        const bool r_fastest = (slot_order == COCODIFF_RECV_MAJOR) == r_sends;
+        rs = r_fastest ? chunk8 : (uint32_t)s->P * chunk8;
+        ps = r_fastest ? (uint32_t)s->P * chunk8 : chunk8;
+    }
+};
 
 template <typename Walk>
-static int launch_permute(const PermuteArgs& a, const void* in, void* out, void* stream, const char* who) {
+static int launch_permute(const Walk& a, const void* in, void* out, void* stream, const char* who) {
     const size_t touched = (size_t)a.n_vec * 32;
     with_policy(stream_loads(touched), stream_stores(touched), [&](auto L, auto S) {
         auto launch = [&](auto u_c) {
@@ -175,26 +160,22 @@ static int launch_permute(const PermuteArgs& a, const void* in, void* out, void*
     return check_launch(who);
 }
 
-// Between the sequence-parallel tensor and the buffer; the ranks of the shape's range are token owners.
-template <typename Walk>
-static int launch_seq_side(const cocodiff_shape* shape, const void* in, void* out, int slot_order, void* stream, const char* who) {
-    int rc = check_permute(shape, in, out, slot_order, who);
-    if (rc != COCODIFF_OK) return rc;
-    PermuteArgs a = make_args(shape, slot_order);
-    a.first = shape->rank_begin * a.Ns;
-    a.n_vec = (uint32_t)shape->rank_count * a.Ns * a.D8;
-    return launch_permute<Walk>(a, in, out, stream, who);
-}
-
-// Between the head-parallel tensor and the buffer; the ranks of the shape's range are head owners.
-template <typename Walk>
-static int launch_head_side(const cocodiff_shape* shape, const void* in, void* out, int slot_order, void* stream, const char* who) {
-    int rc = check_permute(shape, in, out, slot_order, who);
-    if (rc != COCODIFF_OK) return rc;
-    PermuteArgs a = make_args(shape, slot_order);
-    a.first = shape->rank_begin * a.Hp;
-    a.n_vec = (uint32_t)shape->rank_count * a.Hp * a.N * a.d8;
-    return launch_permute<Walk>(a, in, out, stream, who);
+// The chunks that `z.count` senders from z.begin on send to P receivers each, in buffer order.  sender, receiver: what one sender and
+// one receiver further means in the tensor; sender_buf: and one sender further in the buffer.
+static void set_chunks(Chunks* a, const Sizes& z, uint32_t P, bool recv_major, uint32_t sender, uint32_t receiver, uint32_t sender_buf) {
+    a->n_vec = z.count * P * z.chunk8;
+    a->chunk8 = z.chunk8;
+    a->row8 = z.row8;
+    a->n_lo = recv_major ? z.count : P;
+    a->from_hi = recv_major ? receiver : sender;
+    a->from_lo = recv_major ? sender : receiver;
+    a->from0 = z.begin * sender;
+    a->to_hi = P * z.chunk8;
+    a->to0 = z.begin * sender_buf;
+    // (every dividend is below N * D / 8, which is below 2^31)
+    a->div_chunk8 = make_divisor31(z.chunk8);
+    a->div_lo = make_divisor31(a->n_lo);
+    a->div_row8 = make_divisor31(z.row8);
 }
 
 }  // namespace cocodiff
@@ -203,20 +184,64 @@ using namespace cocodiff;
 
 extern "C" int cocodiff_a2a_pack(const cocodiff_shape* shape, const cocodiff_bf16* x_seq, cocodiff_bf16* xbuf,
                                  int slot_order, void* stream) {
-    return launch_seq_side<BufFromSeq>(shape, x_seq, xbuf, slot_order, stream, "a2a_pack");
+    const int rc = check_permute(shape, x_seq, xbuf, slot_order, "a2a_pack");
+    if (rc != COCODIFF_OK) return rc;
+    const Sizes z(shape, slot_order, true);
+    BufFromSeq a;
+    set_chunks(&a, z, (uint32_t)shape->P, slot_order == COCODIFF_RECV_MAJOR, z.Ns * z.D8, z.row8, z.rs);
+    a.D8 = z.D8;
+    return launch_permute(a, x_seq, xbuf, stream, "a2a_pack");
 }
 
 extern "C" int cocodiff_a2a_unpack(const cocodiff_shape* shape, const cocodiff_bf16* xbuf, cocodiff_bf16* x_hs,
                                    int slot_order, void* stream) {
-    return launch_head_side<HeadsFromBuf>(shape, xbuf, x_hs, slot_order, stream, "a2a_unpack");
+    const int rc = check_permute(shape, xbuf, x_hs, slot_order, "a2a_unpack");
+    if (rc != COCODIFF_OK) return rc;
+    const Sizes z(shape, slot_order, true);
+    HeadsFromBuf a;
+    a.n_vec = z.count * z.Hp * z.head8;
+    a.head8 = z.head8;
+    a.first = z.begin * z.Hp;
+    a.to0 = a.first * z.head8;
+    a.row8 = z.row8;
+    a.d8 = z.d8;
+    a.per_r = z.rs - z.chunk8;
+    a.per_p = z.ps - z.row8;
+    a.div_head8 = make_divisor31(z.head8);
+    a.div_d8 = make_divisor31(z.d8);
+    a.div_Ns = make_divisor31(z.Ns);
+    a.div_Hp = make_divisor31(z.Hp);
+    return launch_permute(a, xbuf, x_hs, stream, "a2a_unpack");
 }
 
 extern "C" int cocodiff_a2a_pack_hs(const cocodiff_shape* shape, const cocodiff_bf16* y_hs, cocodiff_bf16* xbuf,
                                     int slot_order, void* stream) {
-    return launch_head_side<BufFromHeads>(shape, y_hs, xbuf, slot_order, stream, "a2a_pack_hs");
+    const int rc = check_permute(shape, y_hs, xbuf, slot_order, "a2a_pack_hs");
+    if (rc != COCODIFF_OK) return rc;
+    const Sizes z(shape, slot_order, false);
+    BufFromHeads a;
+    set_chunks(&a, z, (uint32_t)shape->P, slot_order == COCODIFF_RECV_MAJOR, z.Hp * z.head8, z.Ns * z.d8, z.ps);
+    a.d8 = z.d8;
+    a.per_head = z.head8 - z.d8;
+    a.div_d8 = make_divisor31(z.d8);
+    return launch_permute(a, y_hs, xbuf, stream, "a2a_pack_hs");
 }
 
 extern "C" int cocodiff_a2a_unpack_seq(const cocodiff_shape* shape, const cocodiff_bf16* xbuf, cocodiff_bf16* y_seq,
                                        int slot_order, void* stream) {
-    return launch_seq_side<SeqFromBuf>(shape, xbuf, y_seq, slot_order, stream, "a2a_unpack_seq");
+    const int rc = check_permute(shape, xbuf, y_seq, slot_order, "a2a_unpack_seq");
+    if (rc != COCODIFF_OK) return rc;
+    const Sizes z(shape, slot_order, false);
+    SeqFromBuf a;
+    a.n_vec = z.count * z.Ns * z.D8;
+    a.D8 = z.D8;
+    a.first = z.begin * z.Ns;
+    a.to0 = a.first * z.D8;
+    a.row8 = z.row8;
+    a.per_r = z.rs - z.chunk8;
+    a.per_p = z.ps - z.row8;
+    a.div_D8 = make_divisor31(z.D8);
+    a.div_Ns = make_divisor31(z.Ns);
+    a.div_row8 = make_divisor31(z.row8);
+    return launch_permute(a, xbuf, y_seq, stream, "a2a_unpack_seq");
 }
