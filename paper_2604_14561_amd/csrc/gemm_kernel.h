@@ -630,6 +630,7 @@ __device__ __forceinline__ void wave_barrier() { asm volatile("s_barrier" ::: "m
 // exactly 512 of those, two rounds of 256 compute units, where 432 square tiles are 1.69.
 template <int NI, int NJ, int LAYOUT>
 __global__ void __launch_bounds__(256, workgroups_per_unit(NI, NJ)) qkv_gemm_direct_kernel(GemmArgs a) {
+    fetch_arguments<sizeof(GemmArgs)>();
     constexpr int TM = 2 * NJ * 16, TN = 2 * NI * 16;             // tokens, features per tile
     constexpr int kXBytes = TM * BK * 2, kWBytes = TN * BK * 2;   // one operand tile of one K step
     constexpr int NMFMA = NI * NJ, NREADS = NI + NJ;              // per wavefront and half

@@ -103,6 +103,7 @@ constexpr int kMaxSteps = 8;
 
 template <int STEPS, bool NT_LD, bool NT_ST, bool PACK>   // STEPS 0 = any number of steps, taken kMaxSteps at a time
 __global__ void __launch_bounds__(256) norm_rope_kernel(NormRopeArgs a) {
+    fetch_arguments<sizeof(NormRopeArgs)>();
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t run = blockIdx.x * 4 + (threadIdx.x >> 6);
     uint16_t* __restrict__ base = a.tensor[blockIdx.y];
@@ -176,6 +177,7 @@ constexpr int kUnpackHeads = 6;   // vectors a lane keeps in flight
 // fetched once per lane; kUnpackHeads heads are in flight at a time.
 template <bool NT_LD, bool NT_ST>
 __global__ void __launch_bounds__(256) unpack_norm_rope_kernel(UnpackNormArgs a) {
+    fetch_arguments<sizeof(UnpackNormArgs)>();
     const uint32_t g = blockIdx.x * 256u + threadIdx.x;
     if (g >= a.N * a.d8) return;           // whole head rows leave together: d8 divides 64
     const vec16* __restrict__ buf = reinterpret_cast<const vec16*>(a.buf[blockIdx.y]);

@@ -83,6 +83,7 @@ template <> struct OffsetType<true> { typedef uint32_t type; };
 
 template <bool NT_PREV, bool FROM_BUF, int U, bool FAST>
 __global__ void __launch_bounds__(kSelThreads) select_flag_kernel(FlagPass a) {
+    fetch_arguments<sizeof(FlagPass)>();
     typedef typename OffsetType<FAST>::type off_t;     // byte offsets
     const uint32_t t = blockIdx.x, part = blockIdx.y;
     const uint32_t total = a.sh.S * a.sh.seg8;
@@ -181,6 +182,7 @@ __global__ void __launch_bounds__(THREADS) select_gather_kernel(const vec16* __r
                                                                     int32_t* __restrict__ user_flags,
                                                                     int32_t* __restrict__ idx, int32_t* __restrict__ n_active,
                                                                     vec16* __restrict__ compact, SelectShape sh, uint32_t cap_tiles) {
+    fetch_arguments<5 * sizeof(void*) + sizeof(TileFlags) + sizeof(SelectShape) + 4>();
     __shared__ uint32_t wave_tot[THREADS / 64];
     const uint32_t t = blockIdx.x;
     const bool mine = tile_active<WORDS>(tf, t);
@@ -222,6 +224,7 @@ template <bool GATHER>
 __global__ void __launch_bounds__(kSelThreads) tile_move_kernel(vec16* __restrict__ x, vec16* __restrict__ compact,
                                                                 const int32_t* __restrict__ idx, const int32_t* __restrict__ n_active,
                                                                 SelectShape sh, uint32_t cap_tiles) {
+    fetch_arguments<4 * sizeof(void*) + sizeof(SelectShape) + 4>();
     const uint32_t j = blockIdx.x;
     const int32_t n = *n_active;
     if (n <= 0 || j >= (uint32_t)n) return;
