@@ -16,7 +16,7 @@ HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc", "-fvisibility=hidden",
     # keep the compiler from forming packed-fp32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    # a kernel's first scalar arguments arrive in registers (no trip to where the arguments lie)
+    # a kernel's first scalar arguments arrive in registers (no wait for the memory that holds them)
     "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wall", "-Wno-unused-command-line-argument", "-Wno-inline-asm",
 ]

@@ -114,8 +114,8 @@ __host__ __device__ __forceinline__ uint32_t div_by(uint32_t n, const Divisor31&
 
 // ---- device helpers -------------------------------------------------------
 
-// Asks for every line of a kernel's BYTES of arguments at once.  They lie in host memory: a trip of about a microsecond for the
-// first who reads a line, and the compiler loads an argument where it is needed, one trip after the other along the branches.
+// Asks for every line of a kernel's BYTES of arguments at once.  They are not on chip when a launch starts: the first who reads a line
+// waits for memory, and the compiler loads an argument where it is needed, one such wait after the other along the branches.
 // (Whole calls, cold: norm, selection and projections of the stand-alone calls at 48 x 48 tokens 169.8 -> 167.6 us, one rank of five at 39040 x 640
 // 58.3 -> 56.9, a layer of 2304 x 3072 124.9 -> 123.4, of 560 x 640 12.8 -> 12.2; nothing above 300 us.)
 template <int BYTES>

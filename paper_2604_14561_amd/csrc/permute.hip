@@ -14,7 +14,7 @@ constexpr int kThreads = 256;
 // Every kernel walks its OUTPUT linearly in 16-byte vectors: stores that run linearly through memory and loads that gather
 // 512- or 256-byte pieces are faster than the other way round (cold, 57 MB tensors: 20 against 21.5 us).  Bound by HBM, and below
 // some 20 MB by the launch and the start of its workgroups (an empty launch takes 2.6 us).
-// A launch's arguments lie in host memory, a trip of about a microsecond for whoever reads a line of them first; so they are few
+// A launch's arguments are not on chip when it starts, whoever reads a line of them first waits for memory; so they are few
 // (the chunk strides folded into two factors), and all are asked for before the first branch (settled).  Twice as many, read where
 // they were needed, cost a call 0.3 to 0.6 us: the stand-alone calls at 4608 x 2048 189.2 -> 186.8 us, a small pack and unpack pair
 // 11.0 -> 9.8.
