@@ -247,7 +247,7 @@ def test_topk_ties_nan_and_extremes(oracle):
         _sync()
         assert int(n_act.cpu()[0]) == k
         assert np.array_equal(idx.cpu().numpy()[:k], oracle.topk_active(m.astype(np.float64), k)), k
-    # a segment too long for the LDS key cache: the variant that reads the metric again on every pass
+    # a segment too long for keys in registers: the variant that reads the metric again on every pass
     NL = 40000
     ml = rng.integers(0, 1000, size=NL).astype(np.float32) * 0.25
     mld = torch.from_numpy(ml).to("cuda:0")
@@ -1335,7 +1335,7 @@ def test_proj_fused_select_negative_threshold(oracle, tau):
 @pytest.mark.parametrize("N", [1, 63, 65, 1024, 1025, 8192, 8200, 32768, 32769])
 def test_topk_key_ranges_and_lengths(oracle, N, values):
     """Ranges of keys from one value to all finite floats (one to three histogram passes, a bin taken whole or in part, at the
-    edges of wavefronts, of the workgroup and of the LDS key cache): exactly the oracle's list, nothing behind it."""
+    edges of wavefronts, of the workgroup and of the kept keys): exactly the oracle's list, nothing behind it."""
     import torch
     rng = np.random.default_rng(N)
     many = rng.random(N) < 0.3
