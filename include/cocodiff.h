@@ -161,7 +161,7 @@ COCODIFF_API int cocodiff_qkv_proj_hs(const cocodiff_shape* shape, const cocodif
  * buffers carry normalised values (norm + RoPE on the sending side, the order of Section III-C) and they are rounded
  * once where the chain cocodiff_qkv_proj -> cocodiff_qk_norm_rope rounds twice: the results agree with that chain
  * to within the float tolerance, not bit for bit.  V is bit-identical to cocodiff_qkv_proj_pack / cocodiff_qkv_proj_hs.
- * The two destinations of a tensor hold the same bits.
+ * The two destinations of a tensor hold the same bits, and these do not depend on the rank range or on the other weights.
  * Rules: as cocodiff_qkv_proj and cocodiff_qk_norm_rope; gamma_q / gamma_k required with wq / wk; rope required when Q
  * or K is given; d must be 64, 128 or 256; D a multiple of 64, at least 192 (COCODIFF_ERR_SHAPE otherwise).
  */

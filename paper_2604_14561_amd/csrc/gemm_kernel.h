@@ -322,6 +322,17 @@ __device__ __forceinline__ float sum_of_token(float s) {
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// The sum of the two halves of a head, each as sum_of_token forms it, in all four lanes: the exchange between the rows of 16 lanes leaves
+// `first` in the even and `second` in the odd ones, so one more exchange does instead of two.
+__device__ __forceinline__ float sum_of_halves(float first, float second) {
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(first), __float_as_uint(second), false, false);
+    const float s = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+    const float t = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+    auto c = __builtin_amdgcn_permlane16_swap(__float_as_uint(t), __float_as_uint(t), false, false);
+    return __uint_as_float(c[0]) + __uint_as_float(c[1]);
+}
+
 // Stores.  Cache policy: what a kernel of the same step reads next stays cached -- [N][D], the head-parallel V (the
 // selection reads it), and the exchange buffer of cocodiff_qkv_proj_pack (its unpack follows).  In the fused call nothing on
 // this GPU reads the exchange buffers (they are what the all-to-all would send) or, within the step, the head-parallel Q and
@@ -430,6 +441,8 @@ __device__ __forceinline__ uint32_t store_both(const GemmArgs& a, const TileOut&
 // HEAD = d.  A wavefront holds 16 NI features of its tokens: one or two whole heads, or half of one, whose sums of squares the
 // two wavefronts exchange through `xch` (LDS, [wavefront][token]; two workgroup barriers, the second so that
 // nobody overwrites what the other still reads).
+// A head of 128 is summed in halves of 64 features also where one wavefront holds it: the bits of Q and K do not depend on the
+// tile, so a call that flags V, or takes a range of the ranks, gives those of the call it stands for.
 // Nothing else runs on the unit meanwhile, so this stage's instructions are exposed (where all units end together its stores take
 // longer still): the token's grid coordinates are divided out once, for token tile 0, and then stepped as table row offsets: 16 tokens further is a.row_step16[] further in
 // mixed radix, with carries (the absent axes of a one- or two-axis grid are grids of one cell: they never carry).  The
@@ -441,6 +454,7 @@ __device__ __forceinline__ void store_normalised(const GemmArgs& a, const TileOu
     constexpr int NP = NI / 2;
     constexpr int WF = NI * 16, HEADS = WF >= HEAD ? WF / HEAD : 1;      // features of a wavefront; whole heads among them
     constexpr bool WIDE = HEAD > WF;                                     // a head of two wavefronts
+    constexpr int SUMS = HEAD == 128 && !WIDE ? 2 * HEADS : HEADS;
     static_assert((WF == 64 || WF == 128) && (HEAD == 64 || HEAD == 128 || HEAD == 256) && HEAD <= 2 * WF, "heads per tile");
     if (WIDE) {
         unrolled<NJ>([&](auto j_c) __attribute__((always_inline)) {
@@ -527,17 +541,18 @@ __device__ __forceinline__ void store_normalised(const GemmArgs& a, const TileOu
         float cs[NP][8];
         load_cs(cs);
         next_token_tile();
-        float x[NP][8], s[HEADS] = {};
+        float x[NP][8], s[SUMS] = {};
         unrolled<NP>([&](auto p_c) __attribute__((always_inline)) {
             constexpr int p = decltype(p_c)::value;
             take_acc<NJ, p, j>(x[p], zero);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) s[p * HEADS / NP] += x[p][e] * x[p][e];
+            for (int e = 0; e < 8; ++e) s[p * SUMS / NP] += x[p][e] * x[p][e];
         });
         float rinv[HEADS];
 #pragma unroll
         for (int u = 0; u < HEADS; ++u) {
-            const float ss = WIDE ? xch[(wave & ~1u) * (NJ * 16) + 16 * j + t.tl] + xch[(wave | 1u) * (NJ * 16) + 16 * j + t.tl] : sum_of_token(s[u]);
+            const float ss = WIDE ? xch[(wave & ~1u) * (NJ * 16) + 16 * j + t.tl] + xch[(wave | 1u) * (NJ * 16) + 16 * j + t.tl]
+                             : SUMS > HEADS ? sum_of_halves(s[0], s[SUMS - 1]) : sum_of_token(s[u]);
             rinv[u] = 1.0f / sqrtf(ss * a.inv_d + a.eps);
         }
         vec16 v[NP];

@@ -1282,6 +1282,43 @@ def test_proj_fused_every_long_tile_shape(oracle, bm, bn, N, H, d):
 
 
 @gpu
+@pytest.mark.parametrize("N,H,P,whole,one_rank", [
+    (768, 24, 4, (128, 256), (64, 128)),       # a rank's tiles are 128 features wide
+    (672, 24, 1, (224, 128), (224, 128)),      # 24 feature tiles of 128: the call that flags V takes 96 x 256 (16 flag bytes)
+    (2560, 17, 1, (256, 128), (256, 128)),     # two rounds; 160 x 256 where V is flagged
+])
+def test_proj_fused_bits_do_not_depend_on_the_tile(oracle, N, H, P, whole, one_rank):
+    """Heads of 128 in one wavefront (tiles 256 features wide) or shared by two (128 wide): the same bits, from
+    cocodiff_qkv_proj_fused, from the flagging call and rank by rank."""
+    import torch
+    d, D, NT = 128, 128 * H, N // 16
+    sh, ranks = cd.Shape.make(N, D, H, d, P), [cd.Shape.make(N, D, H, d, P, r, 1) for r in range(P)]
+    plans = [cd.qkv_proj_plan(s, 3, whole_heads=True) for s in (sh, ranks[0])]
+    print(f"fused {N}x{D}: {plans}", flush=True)
+    if plans[0]["compute_units"] == 256:
+        assert [(p["tile_tokens"], p["tile_features"]) for p in plans] == [whole, one_rank]
+    inp = _fused_inputs(np.random.default_rng(N + H), N, D, d)
+    X, Wq, Wk, Wv, gq, gk = (to_dev(inp[k]) for k in ("X", "Wq", "Wk", "Wv", "gamma_q", "gamma_k"))
+    table = torch.from_numpy(cd.rope_table((16, NT), (32, 32), 10000.0)).to("cuda:0")
+    rope = cd.Rope.make((16, NT), (32, 32), 10000.0, table.data_ptr())
+    outs = [[dev_empty((N * D,)) for _ in range(3)] + [dev_empty((H, N, d)) for _ in range(3)] for _ in range(3)]
+    for t in sum(outs, []):
+        t.fill_(-1)
+    weights = (X, Wq, Wk, Wv, gq, gk, 1e-6, rope)
+    cd.qkv_proj_fused(sh, *weights, *outs[0][:3], cd.SEND_MAJOR, *outs[0][3:])
+    for s in ranks:
+        cd.qkv_proj_fused(s, *weights, *outs[1][:3], cd.SEND_MAJOR, *outs[1][3:])
+    flags, idx, n_act = dev_empty((NT,), "i32"), dev_empty((NT,), "i32"), dev_empty((1,), "i32")
+    ws = torch.empty(cd.qkv_proj_fused_select_workspace_bytes(sh, 16), dtype=torch.uint8, device="cuda:0")
+    cd.qkv_proj_fused_select(sh, *weights, *outs[2][:3], cd.SEND_MAJOR, *outs[2][3:], outs[0][5], 16, 0.1, flags, idx, n_act, None, 0, ws)
+    _sync()
+    assert int(n_act.cpu()[0]) == 0
+    for other, what in ((outs[1], "rank by rank"), (outs[2], "flagging")):
+        for i, (a, b) in enumerate(zip(outs[0], other)):
+            assert int((a != b).sum().cpu()) == 0, f"{what}: tensor {i}"
+
+
+@gpu
 @pytest.mark.parametrize("N,H,grid", [(4608, 22, (64, 72)), (3600, 20, (45, 80)), (2304, 20, (48, 48)), (2304, 24, (48, 48))])
 def test_proj_fused_every_tile_of_a_few_rounds(oracle, N, H, grid):
     """Launches of two to four rounds, whose tiles are walked in groups of 6, 5, 5 and 4 rows (29, 17, 15 and 12 rows of tiles, so
