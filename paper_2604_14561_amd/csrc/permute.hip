@@ -108,10 +108,17 @@ __global__ void __launch_bounds__(kThreads) permute_kernel(const vec16* __restri
         if (g0 + k * kThreads < a.n_vec) st_vec<NT_ST>(out + to[k], v[k]);
 }
 
-// Two vectors per lane from 8 to 16 MB.  Three packs and three unpacks between the other calls, cold, one and two per lane: 3.5 MB each
-// 64.4 and 64.9 us, 6.7 MB 66.8 and 67.2, 14.2 MB 170.2 and 168.5, 18.9 MB 187.0 and 188.8, 26.5 MB 204.4 and 206.6.  A plain copy: 4.7 MB
-// 3.0 and 3.1, 11.3 MB 5.5 and 5.0, 14.2 MB 6.4 and 5.4, 28.3 MB 11.1 and 11.2; four are slower at every size.
-static int vectors_per_lane(uint32_t n_vec) { return n_vec >= (8u << 20) / 16u && n_vec < (16u << 20) / 16u ? 2 : 1; }
+// Two vectors per lane where all lanes that the chip holds (256 units x 2048) move the launch at two each but not at one: 8 to 16 MiB
+// of output.  There the launch is one residency of the chip instead of two; below, one vector per lane is one residency already, and
+// above, neither is.  Cold, from a graph, three geometries (24 heads of 128 on 12 ranks, 18 of 64 on 9, 16 of 128 on one), two vectors
+// against one, mean and range over sizes:
+//   4 to 8 MiB      pack and the unpack that reads its buffer -1.4 % (-6 .. +4)     a walk alone +0.8 % (-5 .. +4)
+//   8 to 12 MiB                                               -7.2 % (-14 .. -1)                 -4.5 % (-11 .. 0)
+//   12 to 16 MiB                                              -3.6 % (-8 .. +1)                  -3.2 % (-12 .. +4)
+//   16 to 24 MiB                                              +3.7 % (+1 .. +6)                  -0.4 % (-7 .. +7)
+// (pack and unpack of 12 MiB 13.0 -> 11.8 us, of 18 MiB 17.4 -> 18.2.)  Four are slower at every size.
+constexpr uint32_t kResidentLanes = 256u * 2048u;
+static int vectors_per_lane(uint32_t n_vec) { return n_vec >= kResidentLanes && n_vec < 2u * kResidentLanes ? 2 : 1; }
 
 static int check_permute(const cocodiff_shape* s, const void* in, const void* out, int slot_order, const char* who) {
     int rc = check_shape(s);

@@ -71,11 +71,14 @@ def test_second_all_to_all_rank_ranges(oracle):
     assert np.array_equal(got[3 * cfg.Ns:7 * cfg.Ns], y.transpose(1, 0, 2)[3 * cfg.Ns:7 * cfg.Ns])
 
 
-# Divisors of one, of odd numbers and of powers of two, a last workgroup that is not full, and either side of the size from which a
-# lane moves one vector instead of two (20 MB: 3408 and 3424 tokens of 24 heads of 128).
+# Divisors of one, of odd numbers and of powers of two, a last workgroup that is not full.  5 heads of 72 lie around the sizes between
+# which a lane moves two vectors (524288 to 1048576 vectors of 16 bytes, 720 for every 16 tokens): 11648 tokens are the last size with
+# one and 11664 the first with two, 23296 the last with two and 23312 the first with one again; the last workgroup has 80, 288 and
+# 256 of its 512 vectors at 11664, 11680 and 23296 tokens, 320 in the launch for four of five ranks at 16080.
 @gpu
 @pytest.mark.parametrize("N,H,d,P", [(16, 1, 8, 1), (48, 3, 8, 3), (336, 7, 24, 7), (1040, 5, 72, 1), (5 * 16 * 6, 10, 40, 5), (9 * 16, 9, 264, 9),
-                                     (3408, 24, 128, 1), (3424, 24, 128, 2), (3456, 24, 128, 24)])
+                                     (3408, 24, 128, 1), (3424, 24, 128, 2), (3456, 24, 128, 24), (11648, 5, 72, 1), (11664, 5, 72, 1),
+                                     (11680, 5, 72, 1), (16080, 5, 72, 5), (23296, 5, 72, 1), (23312, 5, 72, 1)])
 def test_permutations_odd_shapes(oracle, N, H, d, P):
     import torch
     print(f"permutations {N} tokens, {H} heads of {d}, {P} ranks", flush=True)
