@@ -16,7 +16,9 @@ HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc", "-fvisibility=hidden",
     # keep the compiler from forming packed-fp32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    # a kernel's first scalar arguments arrive in registers (no wait for the memory that holds them)
+    # a kernel's leading plain arguments, up to the first structure, arrive in registers (no wait for the memory that holds
+    # them): all of the token metric's, top-k's and the copy's, the pointers of the permutations and the list moves.  (Whole
+    # calls without and with it: a cache update by tokens 131.2 and 127.8 us, by tiles 57.0 and 55.8, nothing elsewhere)
     "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wall", "-Wno-unused-command-line-argument", "-Wno-inline-asm",
 ]

@@ -116,8 +116,10 @@ __host__ __device__ __forceinline__ uint32_t div_by(uint32_t n, const Divisor31&
 
 // Asks for every line of a kernel's BYTES of arguments at once.  They are not on chip when a launch starts: the first who reads a line
 // waits for memory, and the compiler loads an argument where it is needed, one such wait after the other along the branches.
-// (Whole calls, cold: norm, selection and projections of the stand-alone calls at 48 x 48 tokens 169.8 -> 167.6 us, one rank of five at 39040 x 640
-// 58.3 -> 56.9, a layer of 2304 x 3072 124.9 -> 123.4, of 560 x 640 12.8 -> 12.2; nothing above 300 us.)
+// (Whole calls, cold, without and with it: a layer of 45 x 80 tokens and 18 heads of 64 36.9 and 36.4 us, the stand-alone calls at 48 x 48
+// tokens and 24 heads of 128 164.4 and 163.5; nothing else beyond what two runs of one side differ by.)  Not for a kernel whose first trip
+// goes by arguments that arrive in registers (the build's preload takes leading plain ones, up to the first structure): it
+// would wait here first.
 template <int BYTES>
 __device__ __forceinline__ void fetch_arguments() {
     const auto* words = (const __attribute__((address_space(4))) uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();
