@@ -150,8 +150,8 @@ def _stream(stream) -> Optional[int]:
     """hipStream_t handle: a torch.cuda.Stream, a raw handle, or None for torch's current stream."""
     if stream is None:
         import torch
-        # the calling thread's current stream as a number; torch.cuda.current_stream() makes an object of it first: 2.7 us, a
-        # third of the host's time for a call of one launch, 0.2 so
+        # the calling thread's current stream as a number; torch.cuda.current_stream() makes an object of it first: 2.8 us, a
+        # third of the host's time for a call of one launch, 0.3 so
         raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
         if raw is None or not torch.cuda.is_initialized():
             return torch.cuda.current_stream().cuda_stream or None

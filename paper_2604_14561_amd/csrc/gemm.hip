@@ -256,11 +256,12 @@ static const TileKernel* tile_shapes(bool whole_heads, int* count) {
 }
 
 // Clocks of one workgroup's tile, fitted to the built shapes: a K step is 17.2 clocks per MFMA of a wavefront and 60 for its
-// barrier, or the operands' way through L1 where that is longer; then the epilogue.  A round is one tile per unit also where two
+// barrier, or the operands' way to the unit where that is longer; then the epilogue.  A round is one tile per unit also where two
 // workgroups share it: they share its matrix cores and its way to L2 too.
-// Operands: a unit keeps no more than about 36 KB of loads in flight whatever the rings hold (streaming reads of 128-byte row
-// pieces by one workgroup per unit, any number of steps ahead: 45 GB/s and unit out of memory, 78 out of the last-level cache), so
-// its rate is that over the latency: 37 to 40 bytes per clock out of L2.
+// Operands: 37 and 40 bytes per clock and unit, fitted (some 78 GB/s).  They are for lines on chip: a launch of one round whose operands
+// come from memory takes its tiles' operand bytes at 44 to 49 GB/s and unit (48 steps, 96 x 128, 160 x 128, 160 x 192 and 288 x 192
+// tiles; a line counts for every unit that shares it, so all units together count more than memory delivers), much the same for
+// every shape, so their order stays.
 // From kLongSteps K steps on, a byte costs another 0.016 clocks where all units are busy (traffic and clock that they share),
 // and the epilogue counts twice: without that, launches of many rounds took tiles of 160 x 256 and 192 x 192 for a last round a
 // little fuller.  Cold inputs, three weights: 5120 x 2560 fused 199.8 us with 160 x 256, 161.6 with 224 x 256; 6144 x 3072 plain
@@ -269,6 +270,9 @@ static const TileKernel* tile_shapes(bool whole_heads, int* count) {
 // 0.2 % slower than the best shape on average, 6.3 % at worst; 0.8 % and 24 % with the estimate of short launches.  That one stands for
 // fewer K steps: 256 .. 20736 tokens x 256 .. 3072 features (120 launches), fastest in 81 and within 3 % in 110, the others
 // host-bound or plain and 4 to 8 % off but for 20736 x 256 with three weights (18.9 us for 15.9).
+// On the two sides of the line, 512 .. 20736 tokens, one to three weights, both forms, cold (48 launches for each D), behind the best
+// built shape on average and at worst: D 896 1.5 and 13 %, 960 1.0 and 16 % (20736 tokens, one weight, plain: 52.7 us for 45.4), 1024 0.4
+// and 9.6 % (12480 tokens, three weights, plain: 80.7 for 73.7), 1088 0.2 and 4.5 %.
 static double tile_clocks(const TileKernel& t, int32_t D, bool whole_heads, double units_busy) {
     const bool is_long = D / BK >= kLongSteps;
     const double mfmas = (t.bm / 32) * (t.bn / 32) * 2.0, operand_bytes = (t.bm + t.bn) * BK * 2.0;
