@@ -1286,16 +1286,18 @@ def test_proj_fused_every_long_tile_shape(oracle, bm, bn, N, H, d):
 
 
 @gpu
-@pytest.mark.parametrize("N,H,P,whole,one_rank", [
-    (768, 24, 4, (128, 256), (64, 128)),       # a rank's tiles are 128 features wide
-    (672, 24, 1, (224, 128), (224, 128)),      # 24 feature tiles of 128: the call that flags V takes 96 x 256 (16 flag bytes)
-    (2560, 17, 1, (256, 128), (256, 128)),     # two rounds; 160 x 256 where V is flagged
+@pytest.mark.parametrize("N,H,d,P,whole,one_rank", [
+    (768, 24, 128, 4, (128, 256), (64, 128)),       # a rank's tiles are 128 features wide
+    (672, 24, 128, 1, (224, 128), (224, 128)),      # 24 feature tiles of 128: the call that flags V takes 96 x 256 (16 flag bytes)
+    (2560, 17, 128, 1, (256, 128), (256, 128)),     # two rounds; 160 x 256 where V is flagged
+    (2048, 42, 64, 1, (256, 128), (256, 128)),      # one head of a wavefront, two in the 160 x 256 tiles of the flagging call
+    (768, 12, 256, 2, (128, 256), (64, 256)),       # two wavefronts of a head in all tiles
 ])
-def test_proj_fused_bits_do_not_depend_on_the_tile(oracle, N, H, P, whole, one_rank):
-    """Heads of 128 in one wavefront (tiles 256 features wide) or shared by two (128 wide): the same bits, from
-    cocodiff_qkv_proj_fused, from the flagging call and rank by rank."""
+def test_proj_fused_bits_do_not_depend_on_the_tile(oracle, N, H, d, P, whole, one_rank):
+    """Heads of 128 in one wavefront (tiles 256 features wide) or shared by two (128 wide), and the other sizes: the same bits,
+    from cocodiff_qkv_proj_fused, from the flagging call and rank by rank."""
     import torch
-    d, D, NT = 128, 128 * H, N // 16
+    D, NT = d * H, N // 16
     sh, ranks = cd.Shape.make(N, D, H, d, P), [cd.Shape.make(N, D, H, d, P, r, 1) for r in range(P)]
     plans = [cd.qkv_proj_plan(s, 3, whole_heads=True) for s in (sh, ranks[0])]
     print(f"fused {N}x{D}: {plans}", flush=True)
@@ -1303,8 +1305,8 @@ def test_proj_fused_bits_do_not_depend_on_the_tile(oracle, N, H, P, whole, one_r
         assert [(p["tile_tokens"], p["tile_features"]) for p in plans] == [whole, one_rank]
     inp = _fused_inputs(np.random.default_rng(N + H), N, D, d)
     X, Wq, Wk, Wv, gq, gk = (to_dev(inp[k]) for k in ("X", "Wq", "Wk", "Wv", "gamma_q", "gamma_k"))
-    table = torch.from_numpy(cd.rope_table((16, NT), (32, 32), 10000.0)).to("cuda:0")
-    rope = cd.Rope.make((16, NT), (32, 32), 10000.0, table.data_ptr())
+    table = torch.from_numpy(cd.rope_table((16, NT), (d // 4, d // 4), 10000.0)).to("cuda:0")
+    rope = cd.Rope.make((16, NT), (d // 4, d // 4), 10000.0, table.data_ptr())
     outs = [[dev_empty((N * D,)) for _ in range(3)] + [dev_empty((H, N, d)) for _ in range(3)] for _ in range(3)]
     for t in sum(outs, []):
         t.fill_(-1)
