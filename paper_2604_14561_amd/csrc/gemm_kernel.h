@@ -602,8 +602,8 @@ __device__ __forceinline__ void wait_loads_and_lds() {
 // A K step is two halves of 32 K elements, one v_mfma_f32_16x16x32_bf16 per 16 x 16 output tile and half.  In step kt a
 // wavefront multiplies half 0 while reading the fragments of half 1, waits until step kt+1 has landed (its own loads; the
 // barrier covers the other wavefronts'), then multiplies half 1 while reading half 0 of step kt+1.  After that barrier every
-// wavefront has its fragments of step kt in registers, so W of step kt+kAhead goes into the W slot of step kt (during half 1
-// of step kt) and X of step kt+1+kAhead into its X slot (during half 0 of step kt+1).
+// wavefront has its fragments of step kt in registers, so W of step kt+kAhead goes into the W slot of step kt (from there on,
+// through half 1) and X of step kt+1+kAhead into its X slot (during half 0 of step kt+1).
 // ---------------------------------------------------------------------------------------------
 constexpr int kMaxLds = 160 * 1024;
 constexpr int ring_lds(int bm, int bn, int ahead) { return ((ahead + 1) * bm + ahead * bn) * BK * 2; }
@@ -728,12 +728,18 @@ __global__ void __launch_bounds__(256, workgroups_per_unit(NI, NJ)) qkv_gemm_dir
     // sched_barrier(0) keeps the order.
     //
     // K step kt: X in the ring slot at byte x_read, W in the one at byte w_read.  X of step kt+kAhead is issued during half 0
-    // (into the X slot x_load that step kt-1 used), W of step kt+kAhead during half 1 (into the W slot of step kt itself).  At the
-    // barrier what is younger than step kt+1's loads may stay in flight: the loads of kAhead - 2 whole steps and the X loads of
-    // one more; in the last steps, which load nothing (TAIL = how many steps follow), those of TAIL - 1 steps.
+    // (into the X slot x_load that step kt-1 used), W of step kt+kAhead from the barrier on and through half 1 (into the W slot of
+    // step kt itself).  At the barrier what is younger than step kt+1's loads may stay in flight: the loads of kAhead - 2 whole
+    // steps and the X loads of one more; in the last steps, which load nothing (TAIL = how many steps follow), those of TAIL - 1
+    // steps.
     uint32_t x_read = 0, x_next = kXBytes, x_load = kAhead * kXBytes, w_read = 0, w_next = kWBytes;
     constexpr int kSpread = NMFMA >= 32 ? NMFMA - 16 : NMFMA >= 16 ? NMFMA - 6 : NMFMA;      // the gaps used for reads and loads
     constexpr int kBarrierAt = NMFMA >= 32 ? NMFMA - 8 : NMFMA - 1;
+    // W's first loads of a step go out behind the barrier already, which frees their slot, an instruction to a gap: of all loads W's have
+    // the shortest way to go, from there to the next step's barrier.  (Weights that come from memory, 24 heads of 128, whole calls
+    // with W's loads dealt out over half 1 and so: 48 x 48 tokens 122.1 and 118.9 us, 16 x 60 x 104 4335 and 4275; 96 x 96
+    // 407.7 and 404.3; others within 0.3 %.)
+    constexpr int kEarly = (NMFMA - 1 - kBarrierAt) / 2;
     constexpr int kTurnAt = NMFMA >= 32 ? NMFMA - 12 : NMFMA > 5 ? NMFMA - 5 : 0;            // and, from there on, for the ring's turn
     constexpr auto turn_at = [](int n) { return kTurnAt + n < NMFMA ? kTurnAt + n : NMFMA - 1; };
     constexpr int kAdvanceAt = kTurnAt >= kSpread ? kTurnAt : NMFMA - 1;      // the operand pointers move on: behind the half's last load
@@ -742,7 +748,7 @@ __global__ void __launch_bounds__(256, workgroups_per_unit(NI, NJ)) qkv_gemm_dir
         constexpr int CUR = decltype(cur_c)::value, TAIL = decltype(tail_c)::value;
         constexpr bool READ = decltype(read_c)::value;
         constexpr bool LOAD = TAIL < 0;
-        constexpr int N_LOADS = !LOAD ? 0 : CUR == 0 ? NJ : NI, OPS = (READ ? NREADS : 0) + 2 * N_LOADS;
+        constexpr int EARLY = CUR == 0 ? 0 : kEarly, N_LOADS = !LOAD ? 0 : CUR == 0 ? NJ : NI - kEarly, OPS = (READ ? NREADS : 0) + 2 * N_LOADS;
         constexpr int IN_FLIGHT = LOAD ? (kAhead - 1) * NJ + (kAhead - 2) * NI : TAIL > 1 ? (TAIL - 1) * (NI + NJ) : 0;
         const uint32_t xs_n = CUR == 0 ? x_read : x_next, ws_n = CUR == 0 ? w_read : w_next;
         const uint32_t lds_l = CUR == 0 ? ld_lds + x_load : ld_lds + kWRing + w_read;
@@ -757,18 +763,23 @@ __global__ void __launch_bounds__(256, workgroups_per_unit(NI, NJ)) qkv_gemm_dir
                     constexpr int t = m * OPS / kSpread + decltype(t_c)::value;
                     constexpr int l = t * 2 * N_LOADS / OPS;       // load instructions before operation t
                     if constexpr ((t + 1) * 2 * N_LOADS / OPS == l) read_frag(wf[CUR ^ 1], xf[CUR ^ 1], xs_n, ws_n, CUR ^ 1, t - l);
-                    else if constexpr (l % 2 == 0) load_dest<4096 * (l / 2)>(lds_l);
+                    else if constexpr (l % 2 == 0) load_dest<4096 * (EARLY + l / 2)>(lds_l);
                     else {
                         // (its M0 is set by the operation before: where that one is in the same gap, no MFMA lies between)
                         if constexpr (decltype(t_c)::value > 0) asm volatile("s_nop 0");
                         if constexpr (CUR == 0) load_to_lds(xk, xoff[l / 2]);
-                        else load_to_lds(wk, woff[l / 2]);
+                        else load_to_lds(wk, woff[EARLY + l / 2]);
                     }
                 });
             }
             if constexpr (CUR == 0 && m == kBarrierAt) {
                 wait_loads_and_lds<IN_FLIGHT>();
                 wave_barrier();
+            }
+            if constexpr (LOAD && CUR == 0 && m > kBarrierAt && (m - kBarrierAt - 1) / 2 < kEarly) {
+                constexpr int l = (m - kBarrierAt - 1) / 2;
+                if constexpr ((m - kBarrierAt) % 2 == 1) load_dest<4096 * l>(ld_lds + kWRing + w_read);
+                else load_to_lds(wk, woff[l]);
             }
             if constexpr (LOAD && CUR == 0 && m == kAdvanceAt) xk += BK * 2;
             if constexpr (LOAD && CUR == 1 && m == kAdvanceAt) wk += BK * 2;
