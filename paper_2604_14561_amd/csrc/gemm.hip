@@ -273,10 +273,13 @@ static const TileKernel* tile_shapes(bool whole_heads, int* count) {
 // On the two sides of the line, 512 .. 20736 tokens, one to three weights, both forms, cold (48 launches for each D), behind the best
 // built shape on average and at worst: D 896 1.5 and 13 %, 960 1.0 and 16 % (20736 tokens, one weight, plain: 52.7 us for 45.4), 1024 0.4
 // and 9.6 % (12480 tokens, three weights, plain: 80.7 for 73.7), 1088 0.2 and 4.5 %.
+constexpr double kBytesPerClock = 37.0;      // of operands, per unit
+static double tile_mfmas(const TileKernel& t) { return (t.bm / 32) * (t.bn / 32) * 2.0; }
+static double tile_operand_bytes(const TileKernel& t) { return (t.bm + t.bn) * BK * 2.0; }
 static double tile_clocks(const TileKernel& t, int32_t D, bool whole_heads, double units_busy) {
     const bool is_long = D / BK >= kLongSteps;
-    const double mfmas = (t.bm / 32) * (t.bn / 32) * 2.0, operand_bytes = (t.bm + t.bn) * BK * 2.0;
-    const double step = std::max(mfmas * 17.2 + 60.0, operand_bytes / (is_long ? 37.0 : 40.0)) + (is_long ? operand_bytes * 0.016 * units_busy : 0.0);
+    const double mfmas = tile_mfmas(t), operand_bytes = tile_operand_bytes(t);
+    const double step = std::max(mfmas * 17.2 + 60.0, operand_bytes / (is_long ? kBytesPerClock : 40.0)) + (is_long ? operand_bytes * 0.016 * units_busy : 0.0);
     return (D / BK) * step + (whole_heads ? 2500.0 + 100.0 * mfmas : 1500.0 + 50.0 * mfmas) * (is_long ? 2.0 : 1.0);
 }
 
@@ -320,6 +323,30 @@ static LaunchPlan plan_launch(int32_t M, int32_t D, int32_t n_tensors, bool whol
     p.tiles_m = (M + p.bm - 1) / p.bm;
     p.tiles_n_per_tensor = (D + p.bn - 1) / p.bn;
     return p;
+}
+
+// Workgroups that only fetch operands (fetch_operands), and the column they begin with.
+// They take units that a launch of one round leaves idle, 8 of them at least, 32 at most (with 16 launches of 4 to 47 MB are 3 % slower,
+// 64 and 128 give the same), from more than 12 K steps on (832 .. 1024 features 2 to 7 % faster, 768 and fewer the same), and where a
+// step's loads take as long as its products: tiles of 288 x 192, 224 x 256 and 256 x 256 are -1 to +2 % with them, 192 x 256 -2 to -7 %.
+// The tiles read the first column themselves meanwhile (from column 0 on: 4 launches of 12 slower by 10 to 13 %).  Where a column takes
+// the fetching units longer than the tiles, they begin further on, so that they are caught up with at the end only (768 x 3072, two
+// weights, 16 units: 37.0 us from column 0 on, 33.5 from 1, 31.9 from 2).
+// Cold, without and with: 46 launches of one round, 270 .. 6600 tokens x 1024 .. 3072 features, one to three weights: 7.9 % less on
+// average, 21 % at most.
+static uint32_t fetching_workgroups(const LaunchPlan& p, int32_t M, int32_t D, int32_t n_tensors, uint32_t n_tiles, uint32_t* from) {
+    constexpr uint32_t kAtLeast = 8, kAtMost = 32;
+    constexpr int kSteps = 12;
+    const uint32_t units = (uint32_t)p.n_cu;
+    *from = 0;
+    if (!p.ring_kernel || p.pick->per_cu > 1 || D / BK <= kSteps || n_tiles + kAtLeast > units) return 0;
+    const double products = tile_mfmas(*p.pick) * 17.2 + 60.0, loads = tile_operand_bytes(*p.pick) / kBytesPerClock;
+    if (products > 1.13 * loads) return 0;
+    const uint32_t fetchers = std::min(units - n_tiles, kAtMost);
+    const double column = ((double)M + (double)n_tensors * D) * kFetchLines * BK * 2.0 / (fetchers * kBytesPerClock);
+    const int columns = (D / BK + kFetchLines - 1) / kFetchLines;
+    *from = (uint32_t)std::max(1, (int)(columns * (1.0 - kFetchLines * std::max(products, loads) / column) + 0.5));
+    return fetchers;
 }
 
 // How many tile rows tile_at walks together in a fused launch of tiles_m x tiles_n tiles on `workgroups` workgroups.  The operands of
@@ -470,7 +497,9 @@ static int proj_launch(const cocodiff_shape* shape, const cocodiff_bf16* x,
     const uint32_t n_tiles = (uint32_t)a.tiles_m * a.tiles_n_per_tensor * a.n_tensors;
     a.n_tiles = (int32_t)n_tiles;
     const uint32_t n_workgroups = (uint32_t)(plan.n_cu * pick->per_cu);      // workgroups at most
-    a.group = layout == OUT_FUSED ? rows_walked_together(plan, (uint32_t)a.tiles_n_per_tensor * a.n_tensors, n_workgroups) : 8u;
+    a.workers = ring_kernel ? std::min(n_tiles, n_workgroups) : n_tiles;
+    const uint32_t fetchers = fetching_workgroups(plan, a.M, a.D, a.n_tensors, n_tiles, &a.fetch_from);
+    a.group = layout == OUT_FUSED ? rows_walked_together(plan, (uint32_t)a.tiles_n_per_tensor * a.n_tensors, a.workers) : 8u;
     // the four pairs of eight consecutive features are 32 consecutive bytes of a table row when every axis has a multiple of four
     bool quad_pairs = true;
     for (int ax = 0; ax < 3; ++ax) a.row_base[ax] = a.row_stride[ax] = a.row_span[ax] = a.row_end[ax] = a.row_step16[ax] = 0;
@@ -514,7 +543,7 @@ static int proj_launch(const cocodiff_shape* shape, const cocodiff_bf16* x,
     static const void* const staged[] = {(const void*)qkv_gemm_staged_kernel<OUT_SEQ>, (const void*)qkv_gemm_staged_kernel<OUT_CHUNKS>,
                                           (const void*)qkv_gemm_staged_kernel<OUT_HEADS>};
     if (ring_kernel)
-        le = hipLaunchKernel(pick->entry[layout == OUT_FUSED && !quad_pairs ? OUT_FUSED_ANY : layout], dim3(std::min(n_tiles, n_workgroups)), dim3(256), kernel_args, pick->lds, st);
+        le = hipLaunchKernel(pick->entry[layout == OUT_FUSED && !quad_pairs ? OUT_FUSED_ANY : layout], dim3(a.workers + fetchers), dim3(256), kernel_args, pick->lds, st);
     else
         le = hipLaunchKernel(staged[layout], dim3(n_tiles), dim3(kStagedThreads), kernel_args, kLdsBytes, st);
     if (le != hipSuccess) return fail(COCODIFF_ERR_HIP, "qkv_proj: launch failed: %s", hipGetErrorString(le));

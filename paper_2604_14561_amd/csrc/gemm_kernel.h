@@ -23,6 +23,8 @@ struct GemmArgs {
     int32_t D;                 // features per tensor = K
     int32_t tiles_m, tiles_n_per_tensor, n_tiles;
     int32_t bm, bn;            // tile of the launch: tokens x features
+    uint32_t workers;          // workgroups that walk tiles; those behind them fetch operands (fetch_operands), from this
+    uint32_t fetch_from;       // column on
     uint32_t group;            // tile rows that are walked together (tile_at)
     // outputs in exchange-buffer (chunk) order instead of [N][D]: tokens per rank, ranks, 16-byte vectors per
     // chunk row and per chunk, slot order
@@ -92,7 +94,7 @@ __device__ __forceinline__ TileWalk tiles_of_block(const GemmArgs& a) {
     const uint32_t n_tiles = (uint32_t)a.n_tiles, xcd = blockIdx.x & 7u;
     const uint32_t per = n_tiles >> 3, rem = n_tiles & 7u;   // XCD x gets per + (x < rem) tiles
     const uint32_t begin = xcd * per + min(xcd, rem);
-    return {begin + (blockIdx.x >> 3), begin + per + (xcd < rem ? 1u : 0u), (gridDim.x >> 3) + (xcd < (gridDim.x & 7u) ? 1u : 0u)};
+    return {begin + (blockIdx.x >> 3), begin + per + (xcd < rem ? 1u : 0u), (a.workers >> 3) + (xcd < (a.workers & 7u) ? 1u : 0u)};
 }
 
 // The accumulators live in the accumulation registers a0 .. a255 by number, and the compiler does not know them: accumulator
@@ -382,7 +384,7 @@ __device__ __forceinline__ uint32_t store_both(const GemmArgs& a, const TileOut&
     // The previous V's lines are loaded whole, laid out as the vectors that they are compared with.  Streamed loads, but cached ones
     // where every unit has one tile and all of V is read at once, behind the K loops: the whole call 39.8 us streamed and 38.1 cached
     // at 4608 x 1024, 41.2 and 40.0 at 3600 x 1152, 48.3 and 46.8 at 3072 x 1536; 80.3 and 81.4 at 1536 x 3072.
-    const bool one_round = (uint32_t)a.n_tiles <= gridDim.x;
+    const bool one_round = (uint32_t)a.n_tiles <= a.workers;
     vec16 prev[AHEAD + 1][NP];
     auto fetch = [&](int j) __attribute__((always_inline)) {
         if (SELECT && j < t.live_j) {
@@ -634,6 +636,43 @@ __device__ __forceinline__ const GemmArgs& arguments_again() {
     return *(const GemmArgs*)(const __attribute__((address_space(4))) GemmArgs*)at;
 }
 
+// What units without a tile do in a launch of one round: read a word of each line of the launch's operands, from column a.fetch_from on
+// in the order in which the K loops come to them.  A K step's loads are a few steps ahead, less than a trip to memory takes; so
+// the tiles find their operands in the last-level cache.  (Streamed loads leave nothing there.)
+// 64 units of 256 without a tile and 16, cold: 768 tokens of 9216, 3072 features, one weight and two with norm and rotation, and the
+// other calls of that rank, 80.2 -> 72.9 us; the latter launch alone 38.4 -> 31.9, 29.4 with everything on chip.
+// By XCD, each fetching what its own units read into its L2, is slower than none: three to seven times the lines, and a unit
+// takes some 37 bytes a clock whoever it reads for.
+constexpr uint32_t kFetchLines = 8;      // a column: 8 lines of every row, 8 K steps
+__device__ __forceinline__ void fetch_operands(const GemmArgs& a) {
+    constexpr uint32_t kLine = BK * 2, kRows = 64 / kFetchLines, kInFlight = 16;
+    const uint32_t K = (uint32_t)a.D, row_lines = K * 2u / kLine, rows = (uint32_t)a.M + (uint32_t)a.n_tensors * K;
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = (gridDim.x - a.workers) * 4u;
+    const uint32_t blocks = (rows + kRows - 1u) / kRows, columns = (row_lines + kFetchLines - 1u) / kFetchLines;
+    uint32_t block = (blockIdx.x - a.workers) * 4u + wave, column = a.fetch_from;      // a load: one column of kRows rows
+    while (column < columns) {
+        uint32_t got[kInFlight] = {};
+#pragma unroll
+        for (uint32_t u = 0; u < kInFlight; ++u) {
+            while (block >= blocks) {
+                block -= blocks;
+                ++column;
+            }
+            const uint32_t r = min(block * kRows + lane / kFetchLines, rows - 1u);
+            const uint32_t line = min(min(column, columns - 1u) * kFetchLines + lane % kFetchLines, row_lines - 1u);
+            const uint32_t f = r - (uint32_t)a.M;
+            const uint16_t* row = r < (uint32_t)a.M ? a.x + ((size_t)a.row_begin + r) * K
+                                  : f < K           ? a.w[0] + (size_t)f * K
+                                  : f < 2u * K      ? a.w[1] + (size_t)(f - K) * K
+                                                    : a.w[2] + (size_t)(f - 2u * K) * K;
+            if (column < columns) got[u] = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const unsigned char*>(row) + line * kLine);
+            block += waves;
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kInFlight; ++u) asm volatile("" ::"v"(got[u]));
+    }
+}
+
 // Scalar steps of the K loop, kept where they are written.
 __device__ __forceinline__ void set_scalar(uint32_t& to, uint32_t from) { asm volatile("s_mov_b32 %0, %1" : "=s"(to) : "s"(from)); }
 
@@ -646,6 +685,10 @@ __device__ __forceinline__ void wave_barrier() { asm volatile("s_barrier" ::: "m
 template <int NI, int NJ, int LAYOUT>
 __global__ void __launch_bounds__(256, workgroups_per_unit(NI, NJ)) qkv_gemm_direct_kernel(GemmArgs a) {
     fetch_arguments<sizeof(GemmArgs)>();
+    if (blockIdx.x >= a.workers) {
+        fetch_operands(a);
+        return;
+    }
     constexpr int TM = 2 * NJ * 16, TN = 2 * NI * 16;             // tokens, features per tile
     constexpr int kXBytes = TM * BK * 2, kWBytes = TN * BK * 2;   // one operand tile of one K step
     constexpr int NMFMA = NI * NJ, NREADS = NI + NJ;              // per wavefront and half

@@ -1275,6 +1275,14 @@ def test_proj_every_long_tile_shape(oracle, bm, bn, N, H, n_tensors):
     test_proj_every_tile_shape(oracle, bm, bn, N, H, n_tensors)
 
 
+# Launches of one round whose idle units fetch operands: 8 of them (the fewest) over the last 5 of 13 K steps, 32 (the most) for
+# 416 tokens, and 16 that begin with the fourth column of eight K steps.
+@gpu
+@pytest.mark.parametrize("bm,bn,N,H,n_tensors", [(128, 256, 7904, 13, 1), (64, 128, 416, 13, 3), (160, 192, 768, 48, 3)])
+def test_proj_units_without_a_tile(oracle, bm, bn, N, H, n_tensors):
+    test_proj_every_tile_shape(oracle, bm, bn, N, H, n_tensors)
+
+
 @gpu
 @pytest.mark.parametrize("bm,bn,N,H,d", [
     (224, 128, 1872, 9, 128), (224, 128, 1904, 17, 64), (192, 128, 1584, 9, 128), (192, 128, 1632, 17, 64), (160, 128, 1296, 9, 128),
