@@ -29,6 +29,16 @@ EXPORTS = (
     "cocodiff_rope_table_fill", "cocodiff_qkv_proj_plan", "cocodiff_util_copy", "cocodiff_util_mfma_rate", "cocodiff_version", "cocodiff_last_error",
 )
 
+# the calls that csrc/marshal.c makes, in its order
+FAST = (
+    "cocodiff_qkv_proj", "cocodiff_qk_norm_rope", "cocodiff_qkv_proj_pack", "cocodiff_qkv_proj_hs", "cocodiff_qk_norm_rope_pack",
+    "cocodiff_a2a_unpack_norm_rope", "cocodiff_a2a_unpack_select", "cocodiff_a2a_pack", "cocodiff_a2a_unpack", "cocodiff_vmajor_select",
+    "cocodiff_vmajor_gather", "cocodiff_vmajor_scatter", "cocodiff_vmajor_token_metric", "cocodiff_vmajor_topk", "cocodiff_a2a_pack_hs",
+    "cocodiff_a2a_unpack_seq", "cocodiff_qkv_proj_fused", "cocodiff_qkv_proj_fused_select",
+)
+(_QKV_PROJ, _QK_NORM_ROPE, _QKV_PROJ_PACK, _QKV_PROJ_HS, _QK_NORM_ROPE_PACK, _UNPACK_NORM_ROPE, _UNPACK_SELECT, _PACK, _UNPACK, _SELECT, _GATHER,
+ _SCATTER, _TOKEN_METRIC, _TOPK, _PACK_HS, _UNPACK_SEQ, _QKV_PROJ_FUSED, _QKV_PROJ_FUSED_SELECT) = range(len(FAST))
+
 
 class CocodiffError(RuntimeError):
     def __init__(self, code: int, message: str):
@@ -124,8 +134,27 @@ def lib() -> ctypes.CDLL:
                      "cocodiff_vmajor_token_metric", "cocodiff_vmajor_topk",
                      "cocodiff_a2a_pack_hs", "cocodiff_a2a_unpack_seq", "cocodiff_rope_table_fill", "cocodiff_util_copy"):
             getattr(L, name).restype = ci
+        L.fast = _native_calls(L)
         _lib = L
     return _lib
+
+
+def _native_calls(L):
+    """Calls with the usual arguments marshalled in native code (csrc/marshal.c): ``L.fast(which, *arguments)`` on the current
+    stream, the call's code or None where the general way below has to take it.  Through ctypes a call takes the host 5 to 6 us, a
+    small call's kernels 3."""
+    try:
+        from . import _marshal
+    except ImportError as missing:
+        raise FileNotFoundError(
+            f"the native part of the binding next to {LIB_PATH} is missing: build it with `python -m paper_2604_14561_amd.build`") from missing
+    try:
+        import torch
+        where = (torch.Tensor, torch.nn.Parameter, Shape, Rope, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+    except (ImportError, AttributeError):
+        return lambda *arguments: None
+    assert _marshal.NAMES == FAST
+    return _marshal.Calls(tuple(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in FAST), *where)
 
 
 def _check(rc: int) -> None:
@@ -166,53 +195,91 @@ def version() -> str:
 
 
 def qkv_proj(shape: Shape, x, wq, wk, wv, q, k, v, stream=None) -> None:
-    _check(lib().cocodiff_qkv_proj(ctypes.byref(shape), _ptr(x), _ptr(wq), _ptr(wk), _ptr(wv),
-                                   _ptr(q), _ptr(k), _ptr(v), _stream(stream)))
+    L = lib()
+    rc = L.fast(_QKV_PROJ, shape, x, wq, wk, wv, q, k, v) if stream is None else None
+    if rc is None:
+        rc = L.cocodiff_qkv_proj(ctypes.byref(shape), _ptr(x), _ptr(wq), _ptr(wk), _ptr(wv),
+                                 _ptr(q), _ptr(k), _ptr(v), _stream(stream))
+    _check(rc)
 
 
 def qk_norm_rope(shape: Shape, q, k, gamma_q, gamma_k, eps: float, rope: Rope, stream=None) -> None:
-    _check(lib().cocodiff_qk_norm_rope(ctypes.byref(shape), _ptr(q), _ptr(k), _ptr(gamma_q), _ptr(gamma_k),
-                                       float(eps), ctypes.byref(rope), _stream(stream)))
+    L = lib()
+    rc = L.fast(_QK_NORM_ROPE, shape, q, k, gamma_q, gamma_k, eps, rope) if stream is None else None
+    if rc is None:
+        rc = L.cocodiff_qk_norm_rope(ctypes.byref(shape), _ptr(q), _ptr(k), _ptr(gamma_q), _ptr(gamma_k),
+                                     float(eps), ctypes.byref(rope), _stream(stream))
+    _check(rc)
 
 
 def qkv_proj_pack(shape: Shape, x, wq, wk, wv, qbuf, kbuf, vbuf, slot_order: int = SEND_MAJOR, stream=None) -> None:
-    _check(lib().cocodiff_qkv_proj_pack(ctypes.byref(shape), _ptr(x), _ptr(wq), _ptr(wk), _ptr(wv),
-                                        _ptr(qbuf), _ptr(kbuf), _ptr(vbuf), int(slot_order), _stream(stream)))
+    L = lib()
+    rc = L.fast(_QKV_PROJ_PACK, shape, x, wq, wk, wv, qbuf, kbuf, vbuf, slot_order) if stream is None else None
+    if rc is None:
+        rc = L.cocodiff_qkv_proj_pack(ctypes.byref(shape), _ptr(x), _ptr(wq), _ptr(wk), _ptr(wv),
+                                      _ptr(qbuf), _ptr(kbuf), _ptr(vbuf), int(slot_order), _stream(stream))
+    _check(rc)
 
 
 def qkv_proj_hs(shape: Shape, x, wq, wk, wv, q_hs, k_hs, v_hs, stream=None) -> None:
-    _check(lib().cocodiff_qkv_proj_hs(ctypes.byref(shape), _ptr(x), _ptr(wq), _ptr(wk), _ptr(wv),
-                                      _ptr(q_hs), _ptr(k_hs), _ptr(v_hs), _stream(stream)))
+    L = lib()
+    rc = L.fast(_QKV_PROJ_HS, shape, x, wq, wk, wv, q_hs, k_hs, v_hs) if stream is None else None
+    if rc is None:
+        rc = L.cocodiff_qkv_proj_hs(ctypes.byref(shape), _ptr(x), _ptr(wq), _ptr(wk), _ptr(wv),
+                                    _ptr(q_hs), _ptr(k_hs), _ptr(v_hs), _stream(stream))
+    _check(rc)
 
 
 def qk_norm_rope_pack(shape: Shape, q, k, gamma_q, gamma_k, eps: float, rope: Rope, qbuf, kbuf,
                       slot_order: int = SEND_MAJOR, stream=None) -> None:
-    _check(lib().cocodiff_qk_norm_rope_pack(ctypes.byref(shape), _ptr(q), _ptr(k), _ptr(gamma_q), _ptr(gamma_k),
-                                            float(eps), ctypes.byref(rope), _ptr(qbuf), _ptr(kbuf), int(slot_order),
-                                            _stream(stream)))
+    L = lib()
+    rc = L.fast(_QK_NORM_ROPE_PACK, shape, q, k, gamma_q, gamma_k, eps, rope, qbuf, kbuf, slot_order) if stream is None else None
+    if rc is None:
+        rc = L.cocodiff_qk_norm_rope_pack(ctypes.byref(shape), _ptr(q), _ptr(k), _ptr(gamma_q), _ptr(gamma_k),
+                                          float(eps), ctypes.byref(rope), _ptr(qbuf), _ptr(kbuf), int(slot_order),
+                                          _stream(stream))
+    _check(rc)
 
 
 def a2a_unpack_norm_rope(shape: Shape, qbuf, kbuf, q_hs, k_hs, gamma_q, gamma_k, eps: float, rope: Rope,
                          slot_order: int = SEND_MAJOR, stream=None) -> None:
-    _check(lib().cocodiff_a2a_unpack_norm_rope(ctypes.byref(shape), _ptr(qbuf), _ptr(kbuf), _ptr(q_hs), _ptr(k_hs),
-                                               _ptr(gamma_q), _ptr(gamma_k), float(eps), ctypes.byref(rope),
-                                               int(slot_order), _stream(stream)))
+    L = lib()
+    rc = L.fast(_UNPACK_NORM_ROPE, shape, qbuf, kbuf, q_hs, k_hs, gamma_q, gamma_k, eps, rope,
+                slot_order) if stream is None else None
+    if rc is None:
+        rc = L.cocodiff_a2a_unpack_norm_rope(ctypes.byref(shape), _ptr(qbuf), _ptr(kbuf), _ptr(q_hs), _ptr(k_hs),
+                                             _ptr(gamma_q), _ptr(gamma_k), float(eps), ctypes.byref(rope),
+                                             int(slot_order), _stream(stream))
+    _check(rc)
 
 
 def a2a_unpack_select(shape: Shape, vbuf, slot_order: int, v_hs, v_prev, tile_tokens: int, tau: float, flags, active_idx,
                       n_active, compact, cap_tiles: int, workspace, stream=None) -> None:
-    _check(lib().cocodiff_a2a_unpack_select(ctypes.byref(shape), _ptr(vbuf), int(slot_order), _ptr(v_hs), _ptr(v_prev),
-                                            int(tile_tokens), float(tau), _ptr(flags), _ptr(active_idx), _ptr(n_active),
-                                            _ptr(compact), int(cap_tiles), _ptr(workspace),
-                                            int(workspace.numel() * workspace.element_size()), _stream(stream)))
+    L = lib()
+    rc = L.fast(_UNPACK_SELECT, shape, vbuf, slot_order, v_hs, v_prev, tile_tokens, tau, flags, active_idx, n_active, compact,
+                cap_tiles, workspace) if stream is None else None
+    if rc is None:
+        rc = L.cocodiff_a2a_unpack_select(ctypes.byref(shape), _ptr(vbuf), int(slot_order), _ptr(v_hs), _ptr(v_prev),
+                                          int(tile_tokens), float(tau), _ptr(flags), _ptr(active_idx), _ptr(n_active),
+                                          _ptr(compact), int(cap_tiles), _ptr(workspace),
+                                          int(workspace.numel() * workspace.element_size()), _stream(stream))
+    _check(rc)
 
 
 def a2a_pack(shape: Shape, x_seq, xbuf, slot_order: int = SEND_MAJOR, stream=None) -> None:
-    _check(lib().cocodiff_a2a_pack(ctypes.byref(shape), _ptr(x_seq), _ptr(xbuf), int(slot_order), _stream(stream)))
+    L = lib()
+    rc = L.fast(_PACK, shape, x_seq, xbuf, slot_order) if stream is None else None
+    if rc is None:
+        rc = L.cocodiff_a2a_pack(ctypes.byref(shape), _ptr(x_seq), _ptr(xbuf), int(slot_order), _stream(stream))
+    _check(rc)
 
 
 def a2a_unpack(shape: Shape, xbuf, x_hs, slot_order: int = SEND_MAJOR, stream=None) -> None:
-    _check(lib().cocodiff_a2a_unpack(ctypes.byref(shape), _ptr(xbuf), _ptr(x_hs), int(slot_order), _stream(stream)))
+    L = lib()
+    rc = L.fast(_UNPACK, shape, xbuf, x_hs, slot_order) if stream is None else None
+    if rc is None:
+        rc = L.cocodiff_a2a_unpack(ctypes.byref(shape), _ptr(xbuf), _ptr(x_hs), int(slot_order), _stream(stream))
+    _check(rc)
 
 
 def vmajor_select_workspace_bytes(S: int, N: int, W: int, tile_tokens: int = 16) -> int:
@@ -221,11 +288,16 @@ def vmajor_select_workspace_bytes(S: int, N: int, W: int, tile_tokens: int = 16)
 
 def vmajor_select(S: int, N: int, W: int, tile_tokens: int, v_cur, v_prev, tau: float, flags, active_idx,
                   n_active, compact, cap_tiles: int, workspace, stream=None, workspace_bytes: Optional[int] = None) -> None:
-    if workspace_bytes is None:
-        workspace_bytes = 0 if workspace is None or isinstance(workspace, int) else workspace.numel() * workspace.element_size()
-    _check(lib().cocodiff_vmajor_select(S, N, W, tile_tokens, _ptr(v_cur), _ptr(v_prev), float(tau), _ptr(flags),
-                                        _ptr(active_idx), _ptr(n_active), _ptr(compact), int(cap_tiles),
-                                        _ptr(workspace), int(workspace_bytes), _stream(stream)))
+    L = lib()
+    rc = L.fast(_SELECT, S, N, W, tile_tokens, v_cur, v_prev, tau, flags, active_idx, n_active, compact, cap_tiles,
+                workspace) if stream is None and workspace_bytes is None else None
+    if rc is None:
+        if workspace_bytes is None:
+            workspace_bytes = 0 if workspace is None or isinstance(workspace, int) else workspace.numel() * workspace.element_size()
+        rc = L.cocodiff_vmajor_select(S, N, W, tile_tokens, _ptr(v_cur), _ptr(v_prev), float(tau), _ptr(flags),
+                                      _ptr(active_idx), _ptr(n_active), _ptr(compact), int(cap_tiles),
+                                      _ptr(workspace), int(workspace_bytes), _stream(stream))
+    _check(rc)
 
 
 def vmajor_select_static(S: int, N: int, W: int, tile_tokens: int, v_cur, v_prev, tau: float, flags, active_idx,
@@ -237,22 +309,38 @@ def vmajor_select_static(S: int, N: int, W: int, tile_tokens: int, v_cur, v_prev
 
 
 def vmajor_gather(S: int, N: int, W: int, tile_tokens: int, x, active_idx, n_active, compact, cap_tiles: int, stream=None) -> None:
-    _check(lib().cocodiff_vmajor_gather(S, N, W, tile_tokens, _ptr(x), _ptr(active_idx), _ptr(n_active), _ptr(compact),
-                                        int(cap_tiles), _stream(stream)))
+    L = lib()
+    rc = L.fast(_GATHER, S, N, W, tile_tokens, x, active_idx, n_active, compact, cap_tiles) if stream is None else None
+    if rc is None:
+        rc = L.cocodiff_vmajor_gather(S, N, W, tile_tokens, _ptr(x), _ptr(active_idx), _ptr(n_active), _ptr(compact),
+                                      int(cap_tiles), _stream(stream))
+    _check(rc)
 
 
 def vmajor_scatter(S: int, N: int, W: int, tile_tokens: int, compact, active_idx, n_active, cache, cap_tiles: int, stream=None) -> None:
-    _check(lib().cocodiff_vmajor_scatter(S, N, W, tile_tokens, _ptr(compact), _ptr(active_idx), _ptr(n_active), _ptr(cache),
-                                         int(cap_tiles), _stream(stream)))
+    L = lib()
+    rc = L.fast(_SCATTER, S, N, W, tile_tokens, compact, active_idx, n_active, cache, cap_tiles) if stream is None else None
+    if rc is None:
+        rc = L.cocodiff_vmajor_scatter(S, N, W, tile_tokens, _ptr(compact), _ptr(active_idx), _ptr(n_active), _ptr(cache),
+                                       int(cap_tiles), _stream(stream))
+    _check(rc)
 
 
 def vmajor_token_metric(S: int, N: int, W: int, v_cur, v_prev, metric, stream=None) -> None:
-    _check(lib().cocodiff_vmajor_token_metric(S, N, W, _ptr(v_cur), _ptr(v_prev), _ptr(metric), _stream(stream)))
+    L = lib()
+    rc = L.fast(_TOKEN_METRIC, S, N, W, v_cur, v_prev, metric) if stream is None else None
+    if rc is None:
+        rc = L.cocodiff_vmajor_token_metric(S, N, W, _ptr(v_cur), _ptr(v_prev), _ptr(metric), _stream(stream))
+    _check(rc)
 
 
 def vmajor_topk(n_seg: int, N: int, metric, n_keep: int, active_idx, n_active, stream=None, global_ids: bool = False) -> None:
-    _check(lib().cocodiff_vmajor_topk(int(n_seg), int(N), _ptr(metric), int(n_keep), int(bool(global_ids)),
-                                      _ptr(active_idx), _ptr(n_active), _stream(stream)))
+    L = lib()
+    rc = L.fast(_TOPK, n_seg, N, metric, n_keep, 1 if global_ids else 0, active_idx, n_active) if stream is None else None
+    if rc is None:
+        rc = L.cocodiff_vmajor_topk(int(n_seg), int(N), _ptr(metric), int(n_keep), int(bool(global_ids)),
+                                    _ptr(active_idx), _ptr(n_active), _stream(stream))
+    _check(rc)
 
 
 def cache_active_count(step: int, n_steps: int, warmup: int, sync_every: int, n_tokens: int) -> int:
@@ -260,11 +348,19 @@ def cache_active_count(step: int, n_steps: int, warmup: int, sync_every: int, n_
 
 
 def a2a_pack_hs(shape: Shape, y_hs, xbuf, slot_order: int = SEND_MAJOR, stream=None) -> None:
-    _check(lib().cocodiff_a2a_pack_hs(ctypes.byref(shape), _ptr(y_hs), _ptr(xbuf), int(slot_order), _stream(stream)))
+    L = lib()
+    rc = L.fast(_PACK_HS, shape, y_hs, xbuf, slot_order) if stream is None else None
+    if rc is None:
+        rc = L.cocodiff_a2a_pack_hs(ctypes.byref(shape), _ptr(y_hs), _ptr(xbuf), int(slot_order), _stream(stream))
+    _check(rc)
 
 
 def a2a_unpack_seq(shape: Shape, xbuf, y_seq, slot_order: int = SEND_MAJOR, stream=None) -> None:
-    _check(lib().cocodiff_a2a_unpack_seq(ctypes.byref(shape), _ptr(xbuf), _ptr(y_seq), int(slot_order), _stream(stream)))
+    L = lib()
+    rc = L.fast(_UNPACK_SEQ, shape, xbuf, y_seq, slot_order) if stream is None else None
+    if rc is None:
+        rc = L.cocodiff_a2a_unpack_seq(ctypes.byref(shape), _ptr(xbuf), _ptr(y_seq), int(slot_order), _stream(stream))
+    _check(rc)
 
 
 def rope_table(grid: Sequence[int], pairs: Sequence[int], theta: float) -> np.ndarray:
@@ -280,9 +376,14 @@ def rope_table(grid: Sequence[int], pairs: Sequence[int], theta: float) -> np.nd
 
 def qkv_proj_fused(shape: Shape, x, wq, wk, wv, gamma_q, gamma_k, eps: float, rope: Optional[Rope], qbuf, kbuf, vbuf,
                    slot_order: int, q_hs, k_hs, v_hs, stream=None) -> None:
-    _check(lib().cocodiff_qkv_proj_fused(ctypes.byref(shape), _ptr(x), _ptr(wq), _ptr(wk), _ptr(wv), _ptr(gamma_q), _ptr(gamma_k),
-                                         float(eps), ctypes.byref(rope) if rope is not None else None, _ptr(qbuf), _ptr(kbuf),
-                                         _ptr(vbuf), int(slot_order), _ptr(q_hs), _ptr(k_hs), _ptr(v_hs), _stream(stream)))
+    L = lib()
+    rc = L.fast(_QKV_PROJ_FUSED, shape, x, wq, wk, wv, gamma_q, gamma_k, eps, rope, qbuf, kbuf, vbuf, slot_order, q_hs, k_hs,
+                v_hs) if stream is None else None
+    if rc is None:
+        rc = L.cocodiff_qkv_proj_fused(ctypes.byref(shape), _ptr(x), _ptr(wq), _ptr(wk), _ptr(wv), _ptr(gamma_q), _ptr(gamma_k),
+                                       float(eps), ctypes.byref(rope) if rope is not None else None, _ptr(qbuf), _ptr(kbuf),
+                                       _ptr(vbuf), int(slot_order), _ptr(q_hs), _ptr(k_hs), _ptr(v_hs), _stream(stream))
+    _check(rc)
 
 
 def qkv_proj_fused_select_workspace_bytes(shape: Shape, tile_tokens: int = 16) -> int:
@@ -292,11 +393,17 @@ def qkv_proj_fused_select_workspace_bytes(shape: Shape, tile_tokens: int = 16) -
 def qkv_proj_fused_select(shape: Shape, x, wq, wk, wv, gamma_q, gamma_k, eps: float, rope: Optional[Rope], qbuf, kbuf, vbuf,
                           slot_order: int, q_hs, k_hs, v_hs, v_prev, tile_tokens: int, tau: float, flags, active_idx, n_active,
                           compact, cap_tiles: int, workspace, stream=None) -> None:
-    _check(lib().cocodiff_qkv_proj_fused_select(
-        ctypes.byref(shape), _ptr(x), _ptr(wq), _ptr(wk), _ptr(wv), _ptr(gamma_q), _ptr(gamma_k), float(eps),
-        ctypes.byref(rope) if rope is not None else None, _ptr(qbuf), _ptr(kbuf), _ptr(vbuf), int(slot_order), _ptr(q_hs),
-        _ptr(k_hs), _ptr(v_hs), _ptr(v_prev), int(tile_tokens), float(tau), _ptr(flags), _ptr(active_idx), _ptr(n_active),
-        _ptr(compact), int(cap_tiles), _ptr(workspace), int(workspace.numel() * workspace.element_size()), _stream(stream)))
+    L = lib()
+    rc = L.fast(_QKV_PROJ_FUSED_SELECT, shape, x, wq, wk, wv, gamma_q, gamma_k, eps, rope, qbuf, kbuf, vbuf, slot_order, q_hs,
+                k_hs, v_hs, v_prev, tile_tokens, tau, flags, active_idx, n_active, compact, cap_tiles,
+                workspace) if stream is None else None
+    if rc is None:
+        rc = L.cocodiff_qkv_proj_fused_select(
+            ctypes.byref(shape), _ptr(x), _ptr(wq), _ptr(wk), _ptr(wv), _ptr(gamma_q), _ptr(gamma_k), float(eps),
+            ctypes.byref(rope) if rope is not None else None, _ptr(qbuf), _ptr(kbuf), _ptr(vbuf), int(slot_order), _ptr(q_hs),
+            _ptr(k_hs), _ptr(v_hs), _ptr(v_prev), int(tile_tokens), float(tau), _ptr(flags), _ptr(active_idx), _ptr(n_active),
+            _ptr(compact), int(cap_tiles), _ptr(workspace), int(workspace.numel() * workspace.element_size()), _stream(stream))
+    _check(rc)
 
 
 def qkv_proj_plan(shape: Shape, n_tensors: int, whole_heads: bool = False) -> dict:

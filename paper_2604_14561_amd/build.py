@@ -1,15 +1,19 @@
-"""Build libcocodiff.so (hand-written HIP for gfx950) in-tree with hipcc."""
+"""Build libcocodiff.so (hand-written HIP for gfx950) in-tree with hipcc, and the binding's native part with gcc."""
 from __future__ import annotations
 
 import glob
 import os
 import re
 import subprocess
+import sysconfig
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libcocodiff.so")
+# the binding's native part, for this interpreter
+MARSHAL_SOURCE = os.path.join(_HERE, "csrc", "marshal.c")
+MARSHAL_PATH = os.path.join(_HERE, "_marshal" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 SOURCES = sorted(glob.glob(os.path.join(_HERE, "csrc", "*.hip")))
 
 HIPCC_FLAGS = [
@@ -29,7 +33,7 @@ def _run(cmd: list) -> str:
     # the host pass does not know the packed-fp32 feature and says so; that is harmless
     err = "\n".join(l for l in proc.stderr.splitlines() if "packed-fp32-ops" not in l)
     if proc.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + err)
+        raise RuntimeError(os.path.basename(cmd[0]) + " failed:\n" + err)
     return err
 
 
@@ -89,6 +93,8 @@ def build(verbose: bool = False) -> str:
             if verbose and err.strip():
                 print(err)
         _run([hipcc] + HIPCC_FLAGS + ["-shared", "-o", LIB_PATH] + objects)
+    _run([os.environ.get("CC", "gcc"), "-O2", "-std=gnu11", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
+          MARSHAL_SOURCE, "-o", MARSHAL_PATH])
     return LIB_PATH
 
 

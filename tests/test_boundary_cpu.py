@@ -142,6 +142,29 @@ def test_binding_refuses_host_tensors():
         cd.a2a_pack(s, x, x, cd.SEND_MAJOR, stream=0)
 
 
+def test_native_marshalling_follows_the_abi():
+    """Every call that csrc/marshal.c makes has the arguments that ctypes is told of, and what it does not handle it leaves
+    to the general way: host tensors, raw pointers, subclasses of int, numbers out of range, another count is an error."""
+    import torch
+    from paper_2604_14561_amd import _marshal
+    L = B.lib()
+    vp, i32, f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_float
+    means = {"S": [ctypes.POINTER(B.Shape)], "r": [ctypes.POINTER(B.Rope)], "R": [ctypes.POINTER(B.Rope)], "t": [vp], "w": [vp, ctypes.c_size_t],
+             "i": [i32], "f": [f32]}
+    assert _marshal.NAMES == B.FAST
+    for name, kinds in zip(B.FAST, _marshal.KINDS):
+        assert sum((means[k] for k in kinds), []) + [vp] == list(getattr(L, name).argtypes), name
+    s, x = cd.Shape.make(256, 256, 4, 64, 2), torch.zeros(256, 256, dtype=torch.int16)
+    for bad in (x, 4096, None, "x"):
+        assert L.fast(B._PACK, s, bad, bad, 0) is None
+    assert L.fast(B._GATHER, 1, 2, 3, 1 << 31, None, None, None, None, 1) is None
+    assert L.fast(B._GATHER, 1, 2, 3, True, None, None, None, None, 1) is None
+    assert L.fast(B._PACK, None, None, None, 0) is None
+    for wrong in ((B._PACK, s, None, None), (B._PACK, s, None, None, 0, 0), (len(B.FAST), s), (-1, s), ()):
+        with pytest.raises(TypeError):
+            L.fast(*wrong)
+
+
 def test_fused_entry_points_check_arguments_before_any_launch():
     L = B.lib()
     fake, odd = ctypes.c_void_p(0x1000), ctypes.c_void_p(0x1004)

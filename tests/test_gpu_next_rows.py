@@ -1433,3 +1433,41 @@ def test_topk_edges_of_the_keys_a_lane_keeps(oracle, N):
         assert n_act.cpu().tolist() == [k, k] and np.all(got[:, k:] == -1)
         for g in range(2):
             assert np.array_equal(got[g, :k], oracle.topk_active(m[g].astype(np.float64), k)), (g, k)
+
+
+@gpu
+def test_binding_native_and_general_way():
+    """The same calls through native marshalling (the current stream) and through ctypes (a stream object, numbers of other
+    kinds): the same results, the same errors."""
+    import torch
+    N, H, d, P = 256, 4, 64, 2
+    D, sh = H * d, cd.Shape.make(256, 256, 4, 64, 2)
+    x = torch.randn(N, D, device="cuda:0", dtype=torch.bfloat16)
+    fast = cd.binding.lib().fast
+    for order in (cd.SEND_MAJOR, cd.RECV_MAJOR):
+        a, b, c = (torch.zeros(N * D, device="cuda:0", dtype=torch.bfloat16) for _ in range(3))
+        assert fast(cd.binding._PACK, sh, x, a, order) == cd.binding.OK
+        cd.a2a_pack(sh, torch.nn.Parameter(x), b, np.int64(order), stream=torch.cuda.current_stream())
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):      # the current stream is the one of the call
+            cd.a2a_pack(sh, x, c, order)
+            got = c.clone()
+        torch.cuda.synchronize()
+        assert torch.equal(a, b) and torch.equal(a, got)
+    assert fast(cd.binding._PACK, sh, x.t(), a, 0) is None
+    with pytest.raises(ValueError):
+        cd.a2a_pack(sh, x.t(), a, 0)
+    with pytest.raises(cd.CocodiffError) as err:
+        cd.a2a_pack(sh, x, a, 7)
+    assert "slot_order" in err.value.message
+    metric = torch.rand(64, device="cuda:0")
+    idx, n = (torch.zeros(k, device="cuda:0", dtype=torch.int32) for k in (64, 1))
+    cd.vmajor_topk(1, 64, metric, 5, idx, n)
+    _sync()
+    first = idx[:5].cpu()
+    cd.vmajor_topk(np.int32(1), 64.0, metric, 5, idx, n, stream=torch.cuda.current_stream().cuda_stream)
+    _sync()
+    assert torch.equal(first, idx[:5].cpu()) and int(n.cpu()[0]) == 5
+    with pytest.raises(cd.CocodiffError):
+        cd.vmajor_topk(1, 64, metric, 65, idx, n)
