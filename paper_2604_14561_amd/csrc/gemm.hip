@@ -219,7 +219,7 @@ struct TileKernel {
     int bm, bn, lds;
     int per_cu;                   // workgroups that share a compute unit
     int min_steps;                // K steps below which the shape is left out
-    const void* entry[5];
+    const void* entry[kLayouts];
 };
 
 // K steps from which on a launch may take the shapes that lie between the others, and counts its operands more dearly (tile_clocks).
@@ -243,10 +243,12 @@ static const TileKernel* tile_shapes(bool whole_heads, int* count) {
             plain[i].entry[OUT_SEQ] = kSeqKernels[i];
             plain[i].entry[OUT_CHUNKS] = kChunkKernels[i];
             plain[i].entry[OUT_HEADS] = kHeadKernels[i];
+            plain[i].entry[OUT_CHUNKS_STREAMED] = kChunkStreamedKernels[i];
         }
         for (int i = 0; i < n_fused; ++i) {
             fused[i].entry[OUT_FUSED] = kFusedKernels[i];
             fused[i].entry[OUT_FUSED_ANY] = kFusedAnyKernels[i];
+            fused[i].entry[OUT_FUSED_STREAMED] = kFusedStreamedKernels[i];
         }
         return true;
     }();
@@ -323,6 +325,21 @@ static LaunchPlan plan_launch(int32_t M, int32_t D, int32_t n_tensors, bool whol
     p.tiles_m = (M + p.bm - 1) / p.bm;
     p.tiles_n_per_tensor = (D + p.bn - 1) / p.bn;
     return p;
+}
+
+// Are the chunks, or the fused call's head-parallel V, streamed past the caches, where a later kernel of the step may read them?
+//   * A tensor of more than 96 MB has left the last-level cache before it is read, and its dirty lines push the operands out of L2: 20736
+//     x 3072, V and then Q and K packed, and their unpack, 951 -> 941 us; the layer in one call at 99840 x 3072 4271 -> 4200, at 40800
+//     x 2304 1083 -> 1063.  Of 28 to 57 MB streaming costs that call 0.7 to 1.6 % (the selection reads V from memory).
+//   * The chunks of a call for some of the ranks are sent away: one of 12 ranks at 9216 x 3072 71.2 -> 70.3 us, one of 16 at 26112 x
+//     2048 69.9 -> 68.0.  (All ranks in one call, so that the unpack reads them: 2144 x 2432 95.3 -> 96.6.)
+//   * A fused launch of one round stores everything at its end, and what is dirty then is written back behind it: 1440 x 1216 22.1 ->
+//     21.3 us, 3600 x 1152 35.8 -> 35.5, 11248 x 512 36.7 -> 35.8.  Below 2 MB there is too little of it, and the selection
+//     waits for memory (256 x 256 12.0 -> 13.3).
+static bool streams_outputs(const cocodiff_shape* shape, OutLayout layout, bool one_round) {
+    const size_t tensor = (size_t)shape->N * shape->D * 2;
+    if (layout == OUT_FUSED) return tensor > (size_t)96 << 20 || (one_round && tensor >= (size_t)2 << 20);
+    return layout == OUT_CHUNKS && (tensor > (size_t)96 << 20 || shape->rank_count < shape->P);
 }
 
 // Workgroups that only fetch operands (fetch_operands), and the column they begin with.
@@ -542,8 +559,12 @@ static int proj_launch(const cocodiff_shape* shape, const cocodiff_bf16* x,
     hipError_t le;
     static const void* const staged[] = {(const void*)qkv_gemm_staged_kernel<OUT_SEQ>, (const void*)qkv_gemm_staged_kernel<OUT_CHUNKS>,
                                           (const void*)qkv_gemm_staged_kernel<OUT_HEADS>};
+    const OutLayout kernel_layout = layout == OUT_FUSED && !quad_pairs                             ? OUT_FUSED_ANY
+                                    : !streams_outputs(shape, layout, n_tiles <= a.workers) ? layout
+                                    : layout == OUT_FUSED                                          ? OUT_FUSED_STREAMED
+                                                                                                   : OUT_CHUNKS_STREAMED;
     if (ring_kernel)
-        le = hipLaunchKernel(pick->entry[layout == OUT_FUSED && !quad_pairs ? OUT_FUSED_ANY : layout], dim3(a.workers + fetchers), dim3(256), kernel_args, pick->lds, st);
+        le = hipLaunchKernel(pick->entry[kernel_layout], dim3(a.workers + fetchers), dim3(256), kernel_args, pick->lds, st);
     else
         le = hipLaunchKernel(staged[layout], dim3(n_tiles), dim3(kStagedThreads), kernel_args, kLdsBytes, st);
     if (le != hipSuccess) return fail(COCODIFF_ERR_HIP, "qkv_proj: launch failed: %s", hipGetErrorString(le));

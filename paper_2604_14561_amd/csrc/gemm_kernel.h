@@ -57,7 +57,13 @@ struct GemmArgs {
 // OUT_FUSED: Q and K are normalised and rotated in the epilogue (on the fp32 accumulators), and every tensor goes to its
 // exchange buffer and to its head-parallel tensor (whichever are given).
 // OUT_FUSED_ANY: the same for rotations in which an axis' pairs are not a multiple of four (pair by pair through the table).
-enum OutLayout { OUT_SEQ = 0, OUT_CHUNKS = 1, OUT_HEADS = 2, OUT_FUSED = 3, OUT_FUSED_ANY = 4 };
+// OUT_CHUNKS_STREAMED, OUT_FUSED_STREAMED: the chunks, and the fused form's head-parallel V, streamed past the caches too (streams_outputs
+// in gemm.hip says when).  Layouts of their own: a branch in the epilogue costs a launch of one round more than it gains (3600 x 1152
+// 36.3 us without, 37.3 with, 35.5 so).
+enum OutLayout { OUT_SEQ = 0, OUT_CHUNKS = 1, OUT_HEADS = 2, OUT_FUSED = 3, OUT_FUSED_ANY = 4, OUT_CHUNKS_STREAMED = 5, OUT_FUSED_STREAMED = 6 };
+constexpr int kLayouts = 7;
+constexpr bool is_fused(int layout) { return layout == OUT_FUSED || layout == OUT_FUSED_ANY || layout == OUT_FUSED_STREAMED; }
+constexpr bool is_chunks(int layout) { return layout == OUT_CHUNKS || layout == OUT_CHUNKS_STREAMED; }
 
 // [rows][64] bf16 tiles (128-byte rows): any 16 consecutive rows of one column land in 16 different
 // 16-byte slots of the 256-byte bank span.
@@ -336,16 +342,19 @@ __device__ __forceinline__ float sum_of_halves(float first, float second) {
 }
 
 // Stores.  Cache policy: what a kernel of the same step reads next stays cached -- [N][D], the head-parallel V (the
-// selection reads it), and the exchange buffer of cocodiff_qkv_proj_pack (its unpack follows).  In the fused call nothing on
-// this GPU reads the exchange buffers (they are what the all-to-all would send) or, within the step, the head-parallel Q and
-// K: streamed past the caches they leave nothing dirty in L2 to be written back under the next round's loads.
+// selection reads it), and the exchange buffer of cocodiff_qkv_proj_pack (its unpack follows) -- but for the STREAMED layouts.
+// In the fused call nothing on this GPU reads the exchange buffers (they are what the all-to-all would send) or, within the
+// step, the head-parallel Q and K: streamed past the caches they leave nothing dirty in L2 to be written back under the next
+// round's loads.
 template <int NI, int NJ, int LAYOUT>
 __device__ __forceinline__ void store_plain(const GemmArgs& a, const TileOut& t, uint16_t* __restrict__ Y) {
     constexpr int NP = NI / 2;
-    const Dest<NP> to = LAYOUT == OUT_SEQ ? dest_seq<NP>(a, t.v8, t.tl) : LAYOUT == OUT_CHUNKS ? dest_chunks<NP>(a, t.v8, t.tl) : dest_heads<NP>(a, t.v8, t.tl);
+    constexpr bool STREAM = LAYOUT == OUT_CHUNKS_STREAMED && NP % 2 == 0;      // whole lines, so feature groups in pairs
+    Dest<NP> to = LAYOUT == OUT_SEQ ? dest_seq<NP>(a, t.v8, t.tl) : is_chunks(LAYOUT) ? dest_chunks<NP>(a, t.v8, t.tl) : dest_heads<NP>(a, t.v8, t.tl);
+    if constexpr (STREAM) to = paired(to, t.tl, a.row8);
     ChunkWalk chunk(a, t.n0);
     const uint32_t row = LAYOUT == OUT_SEQ ? (uint32_t)a.D / 8u : a.d8;
-    vec16* y = reinterpret_cast<vec16*>(Y) + (LAYOUT == OUT_CHUNKS ? 0 : (size_t)t.n0 * row);
+    vec16* y = reinterpret_cast<vec16*>(Y) + (is_chunks(LAYOUT) ? 0 : (size_t)t.n0 * row);
     const bf16x8 zero = zero_fragment();
     for_token_tiles<NI, NJ>(t, zero, [&](auto j_c) __attribute__((always_inline)) {
         vec16 v[NP];
@@ -354,8 +363,12 @@ __device__ __forceinline__ void store_plain(const GemmArgs& a, const TileOut& t,
             take_acc<NJ, decltype(p_c)::value, decltype(j_c)::value>(x, zero);
             v[decltype(p_c)::value] = pack_vec(x);
         });
-        if (LAYOUT == OUT_CHUNKS) {
-            store_groups<false>(y + chunk.at, to, v, t.live_p);
+        if constexpr (STREAM) {
+#pragma unroll
+            for (int p = 0; p < NP; p += 2) pair_lines(v[p], v[p + 1]);
+        }
+        if (is_chunks(LAYOUT)) {
+            store_groups<STREAM>(y + chunk.at, to, v, t.live_p);
             chunk.next(a);
         } else {
             store_groups<false>(y, to, v, t.live_p);
@@ -372,7 +385,7 @@ __device__ __forceinline__ void store_plain(const GemmArgs& a, const TileOut& t,
 // threshold -- practically never -- is compared again in double, from memory, when everything is stored.  The previous
 // vectors of a token tile are fetched AHEAD token tiles before it.  Returns, the same in every lane, a bit per token tile: did
 // any of the wavefront's vectors change?
-template <int NI, int NJ, bool SELECT>
+template <int NI, int NJ, bool SELECT, bool STREAM>
 __device__ __forceinline__ uint32_t store_both(const GemmArgs& a, const TileOut& t, uint16_t* __restrict__ Y, uint16_t* __restrict__ Y2) {
     // (fetched 7 token tiles ahead: 32 x 48 tokens, 24 heads of 128, the call 81.6 us with 5, 79.1 so)
     constexpr int NP = NI / 2, AHEAD = NJ < 7 ? NJ : 7;
@@ -409,7 +422,7 @@ __device__ __forceinline__ uint32_t store_both(const GemmArgs& a, const TileOut&
 #pragma unroll
         for (int p = 0; p < NP; p += 2) pair_lines(v[p], v[p + 1]);
         if (Y) store_groups<true>(yc + chunk.at, to_c, v, t.live_p);
-        if (Y2) store_groups<false>(yh, to_h, v, t.live_p);
+        if (Y2) store_groups<STREAM>(yh, to_h, v, t.live_p);
         if (SELECT) {
             uint32_t largest = 0;
 #pragma unroll
@@ -854,7 +867,7 @@ __global__ void __launch_bounds__(256, workgroups_per_unit(NI, NJ)) qkv_gemm_dir
     // In the fused form the first fragments of the next tile are read behind the epilogue instead, whose values need the
     // registers: 256 x 256 takes 236 vector registers so and the pair-by-pair rotation no scratch memory (256, and 108 bytes a
     // lane, with the fragments held through the epilogue: 96 x 96 tokens, 24 heads, pairs 33 + 31, the whole call 455 us for 439).
-    constexpr bool kReadEarly = LAYOUT != OUT_FUSED && LAYOUT != OUT_FUSED_ANY;
+    constexpr bool kReadEarly = !is_fused(LAYOUT);
     const std::bool_constant<kReadEarly> reading_early;
     for (;;) {
         const uint32_t steps = n_k - kAhead;
@@ -895,18 +908,18 @@ __global__ void __launch_bounds__(256, workgroups_per_unit(NI, NJ)) qkv_gemm_dir
         out.tl = lane & 15u;
         out.v8 = feat / 8u + (lane >> 4);
         uint16_t* y = e.y[tc.tensor];
-        if constexpr (LAYOUT == OUT_FUSED || LAYOUT == OUT_FUSED_ANY) {
+        if constexpr (is_fused(LAYOUT)) {
             uint16_t* y2 = e.y2[tc.tensor];
             // the X slot of the step just finished is free until the next tile's first half loads into it again
             unsigned char* spare = smem + x_load;
             if (e.gamma[tc.tensor]) {     // the same for the whole workgroup: its barriers are taken by all or by none
                 const uint16_t* gamma = e.gamma[tc.tensor];
                 float* xch = reinterpret_cast<float*>(spare);
-                if (e.d == 128u) store_normalised<NI, NJ, LAYOUT == OUT_FUSED, 128>(e, out, gamma, y, y2, xch, wave);
-                else if (e.d == 64u) store_normalised<NI, NJ, LAYOUT == OUT_FUSED, 64>(e, out, gamma, y, y2, xch, wave);
-                else if constexpr (NI == 8) store_normalised<NI, NJ, LAYOUT == OUT_FUSED, 256>(e, out, gamma, y, y2, xch, wave);
+                if (e.d == 128u) store_normalised<NI, NJ, LAYOUT != OUT_FUSED_ANY, 128>(e, out, gamma, y, y2, xch, wave);
+                else if (e.d == 64u) store_normalised<NI, NJ, LAYOUT != OUT_FUSED_ANY, 64>(e, out, gamma, y, y2, xch, wave);
+                else if constexpr (NI == 8) store_normalised<NI, NJ, LAYOUT != OUT_FUSED_ANY, 256>(e, out, gamma, y, y2, xch, wave);
             } else if (e.sel_prev && tc.tensor == 0) {     // V (the first tensor of the launch), flagged on its way out
-                const uint32_t mine = store_both<NI, NJ, true>(e, out, y, y2);
+                const uint32_t mine = store_both<NI, NJ, true, LAYOUT == OUT_FUSED_STREAMED>(e, out, y, y2);
                 // the verdicts of the two wavefronts that share the tokens
                 uint32_t* verdicts = reinterpret_cast<uint32_t*>(spare);
                 if (lane == 0) verdicts[wave] = mine;
@@ -916,7 +929,7 @@ __global__ void __launch_bounds__(256, workgroups_per_unit(NI, NJ)) qkv_gemm_dir
                     e.sel_flag_bytes[(size_t)(out.n0 / 16u + lane) * 16u + tc.f0 / (uint32_t)TN] = (uint8_t)((any >> lane) & 1u);
                 __syncthreads();     // before anybody loads into the slot again
             } else {
-                store_both<NI, NJ, false>(e, out, y, y2);
+                store_both<NI, NJ, false, LAYOUT == OUT_FUSED_STREAMED>(e, out, y, y2);
             }
         } else {
             store_plain<NI, NJ, LAYOUT>(e, out, y);
@@ -943,5 +956,7 @@ extern const void* const kChunkKernels[];
 extern const void* const kHeadKernels[];
 extern const void* const kFusedKernels[];
 extern const void* const kFusedAnyKernels[];
+extern const void* const kChunkStreamedKernels[];
+extern const void* const kFusedStreamedKernels[];
 
 }  // namespace cocodiff

@@ -1275,6 +1275,36 @@ def test_proj_every_long_tile_shape(oracle, bm, bn, N, H, n_tensors):
     test_proj_every_tile_shape(oracle, bm, bn, N, H, n_tensors)
 
 
+# A rank's own call streams its chunks, in whole lines where a wavefront's groups of 32 features come in pairs (tiles 256, 128 and 64
+# features wide, not 192), the call for all ranks does not: the same bits, and nothing outside the rank's chunks is touched.
+@gpu
+@pytest.mark.parametrize("N,H,d,P", [(768, 24, 128, 4), (2560, 5, 64, 5), (18432, 12, 64, 2), (31104, 12, 64, 2), (10560, 22, 64, 2),
+                                     (9216, 24, 128, 12)])
+@pytest.mark.parametrize("order", [0, 1])
+def test_proj_pack_rank_by_rank(N, H, d, P, order):
+    """Tiles of 64 x 64, 32 x 64, 128 x 256, 288 x 192, 256 x 128 and 96 x 128."""
+    import torch
+    D = H * d
+    sh = cd.Shape.make(N, D, H, d, P)
+    x = torch.randn(N, D, device="cuda:0", dtype=torch.bfloat16)
+    w = torch.randn(D, D, device="cuda:0", dtype=torch.bfloat16) * D ** -0.5
+    seq, whole, ranks = (torch.zeros(N * D, device="cuda:0", dtype=torch.bfloat16) for _ in range(3))
+    cd.qkv_proj(sh, x, None, None, w, None, None, seq)
+    cd.a2a_pack(sh, seq, whole, order)
+    for r in range(P):
+        one = cd.Shape.make(N, D, H, d, P, r, 1)
+        print(f"{N}x{D}, rank {r}: {cd.qkv_proj_plan(one, 1)}", flush=True)
+        cd.qkv_proj_pack(one, x, None, None, w, None, None, ranks, order)
+        _sync()
+        chunks = torch.zeros(P * P, dtype=torch.bool)
+        for q in range(r + 1):
+            chunks[q * P:(q + 1) * P] = True
+        sent = chunks if order == cd.SEND_MAJOR else chunks.view(P, P).t().reshape(-1)
+        sent = sent.to("cuda:0").view(-1, 1)
+        assert torch.equal(ranks.view(P * P, -1) * sent, whole.view(P * P, -1) * sent)
+        assert not bool((ranks.view(P * P, -1) * ~sent).any())
+
+
 # Launches of one round whose idle units fetch operands: 8 of them (the fewest) over the last 5 of 13 K steps, 32 (the most) for
 # 416 tokens, and 16 that begin with the fourth column of eight K steps.
 @gpu
