@@ -217,30 +217,32 @@ __global__ void __launch_bounds__(THREADS) select_gather_kernel(const vec16* __r
     }
 }
 
-// Workgroup j moves tile idx[j] (j < n_active, j < cap_tiles) between x [S][N][W] and compact [S][cap*T][W]:
+// LANES lanes move tile idx[j] (j < n_active, j < entries) between x [S][N][W] and compact [S][cap*T][W]:
 // GATHER compact <- x (sender-side extraction of the active tiles), else x <- compact (receiver-side overwrite
 // of the cached tensor).  A list entry outside [0, NT) is skipped, so a corrupt list cannot fault.
 // A chain of trips to memory, count -> list entry -> data: the four pointers arrive in registers, the rest of the arguments is asked for
 // with the list entry, so nothing waits for them.  (Asked for first, they put a trip of their own in front of the count: six moves of 39 MB
 // and what chooses them 128.2 us, 127.8 so; five of 11 MB behind a selection 55.9 and 55.6.)
-template <bool GATHER>
+template <bool GATHER, int LANES>
 __global__ void __launch_bounds__(kSelThreads) tile_move_kernel(vec16* __restrict__ x, vec16* __restrict__ compact,
                                                                 const int32_t* __restrict__ idx, const int32_t* __restrict__ n_active,
-                                                                SelectShape sh, uint32_t cap_tiles) {
-    const uint32_t j = blockIdx.x;
+                                                                SelectShape sh, uint32_t cap_tiles, uint32_t entries) {
+    // (a wavefront moves one tile: its number stays in a scalar register)
+    const uint32_t j = LANES == kSelThreads ? blockIdx.x : __builtin_amdgcn_readfirstlane(blockIdx.x * (kSelThreads / LANES) + threadIdx.x / LANES);
+    const uint32_t lane = LANES == kSelThreads ? threadIdx.x : threadIdx.x % LANES;
     const int32_t n = *n_active;
-    if (n <= 0 || j >= (uint32_t)n) return;
+    if (n <= 0 || j >= (uint32_t)n || j >= entries) return;
     const uint32_t t = (uint32_t)idx[j];
     if (t >= sh.NT) return;
     const uint32_t total = sh.S * sh.seg8;
-    // blockIdx.y strides over the tile's vectors in pieces of kSelUnroll * kSelThreads, so that a short list
+    // blockIdx.y strides over the tile's vectors in pieces of kSelUnroll * LANES, so that a short list
     // still spreads over the whole chip
-    for (uint32_t g0 = blockIdx.y * (kSelUnroll * kSelThreads) + threadIdx.x; g0 < total; g0 += gridDim.y * (kSelUnroll * kSelThreads)) {
+    for (uint32_t g0 = blockIdx.y * (kSelUnroll * LANES) + lane; g0 < total; g0 += gridDim.y * (kSelUnroll * LANES)) {
         vec16 c[kSelUnroll];
         uint64_t dst[kSelUnroll];
 #pragma unroll
         for (int k = 0; k < kSelUnroll; ++k) {
-            const uint32_t g = g0 + k * kSelThreads;
+            const uint32_t g = g0 + k * LANES;
             if (g < total) {
                 const uint32_t s = g / sh.seg8, v = g - s * sh.seg8;
                 const uint64_t x_at = (uint64_t)s * sh.slab8 + (uint64_t)t * sh.seg8 + v;
@@ -251,7 +253,7 @@ __global__ void __launch_bounds__(kSelThreads) tile_move_kernel(vec16* __restric
         }
 #pragma unroll
         for (int k = 0; k < kSelUnroll; ++k)
-            if (g0 + k * kSelThreads < total) st_nt((GATHER ? compact : x) + dst[k], c[k]);
+            if (g0 + k * LANES < total) st_nt((GATHER ? compact : x) + dst[k], c[k]);
     }
 }
 
@@ -471,15 +473,20 @@ static int tile_move(bool gather, int32_t S, int32_t N, int32_t W, int32_t tile_
     if (!x || !compact || !active_idx || !n_active) return fail(COCODIFF_ERR_NULL, "%s: NULL pointer", who);
     if (!aligned16(x) || !aligned16(compact)) return fail(COCODIFF_ERR_ALIGN, "%s: tensors must be 16-byte aligned", who);
     if (cap_tiles < 1) return fail(COCODIFF_ERR_CAPACITY, "%s: cap_tiles (%d) must be >= 1", who, cap_tiles);
-    const uint32_t blocks = (uint32_t)cap_tiles < sh.NT ? (uint32_t)cap_tiles : sh.NT;
-    const uint32_t pieces = (sh.S * sh.seg8 + kSelUnroll * kSelThreads - 1) / (kSelUnroll * kSelThreads);
-    const dim3 grid(blocks, pieces < 64 ? pieces : 64);
-    if (gather)
-        hipLaunchKernelGGL(tile_move_kernel<true>, grid, dim3(kSelThreads), 0, as_stream(stream), (vec16*)x,
-                           (vec16*)compact, active_idx, n_active, sh, (uint32_t)cap_tiles);
-    else
-        hipLaunchKernelGGL(tile_move_kernel<false>, grid, dim3(kSelThreads), 0, as_stream(stream), (vec16*)x,
-                           (vec16*)compact, active_idx, n_active, sh, (uint32_t)cap_tiles);
+    const uint32_t entries = (uint32_t)cap_tiles < sh.NT ? (uint32_t)cap_tiles : sh.NT, total = sh.S * sh.seg8;
+    const auto launch = [&](auto lanes_c) {
+        constexpr uint32_t lanes = decltype(lanes_c)::value, per_group = kSelThreads / lanes;
+        const uint32_t pieces = (total + kSelUnroll * lanes - 1) / (kSelUnroll * lanes);
+        const dim3 grid((entries + per_group - 1) / per_group, pieces < 64 ? pieces : 64);
+        hipLaunchKernelGGL((gather ? tile_move_kernel<true, lanes> : tile_move_kernel<false, lanes>), grid, dim3(kSelThreads), 0, as_stream(stream),
+                           (vec16*)x, (vec16*)compact, active_idx, n_active, sh, (uint32_t)cap_tiles, entries);
+    };
+    // A short tile -- a token, as a rule -- is one wavefront's where a workgroup for each would be more than the chip holds at once (256
+    // units x 8): the chain to the data is gone through once instead of several times.  Token updates with 256 lanes and 64: 40000
+    // tokens x 512 126.3 -> 115.1 us, 9216 x 1536 52.2 -> 50.1, 5520 x 960 44.5 -> 41.8 (longer tokens: 12480 x 3072 128.8 and 134.2);
+    // with fewer tiles more lanes are in flight with 256: 384 x 2688 23.7 and 26.2.
+    if (total <= 256u && entries > 2048u) launch(std::integral_constant<uint32_t, 64>{});
+    else launch(std::integral_constant<uint32_t, kSelThreads>{});
     return check_launch(who);
 }
 

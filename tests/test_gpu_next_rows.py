@@ -1465,6 +1465,33 @@ def test_topk_edges_of_the_keys_a_lane_keeps(oracle, N):
             assert np.array_equal(got[g, :k], oracle.topk_active(m[g].astype(np.float64), k)), (g, k)
 
 
+# Lists of short tiles: a wavefront for each above 2048 entries, a workgroup for each up to there and for longer ones.
+@gpu
+@pytest.mark.parametrize("N,W", [(2048, 2048), (2049, 2048), (2051, 8), (4099, 520), (2050, 2056)])
+@pytest.mark.parametrize("kept", ["none", "one", "most", "all"])
+def test_gather_scatter_of_many_tokens(N, W, kept):
+    import torch
+    n = {"none": 0, "one": 1, "most": N - 2, "all": N}[kept]
+    gen = torch.Generator(device="cuda:0").manual_seed(N + W + n)
+    bits = lambda *shape: torch.randint(-32768, 32767, shape, generator=gen, device="cuda:0", dtype=torch.int16)
+    x, cache = bits(N, W), bits(N, W)
+    idx = torch.full((N,), -7, device="cuda:0", dtype=torch.int32)
+    idx[:n] = torch.randperm(N, generator=gen, device="cuda:0")[:n].sort().values.int()
+    count = torch.tensor([n], device="cuda:0", dtype=torch.int32)
+    for cap in (N, N - 1):
+        compact, out = bits(cap, W), cache.clone()
+        want = compact.clone()
+        listed = idx[:min(n, cap)].long()
+        want[:len(listed)] = x[listed]
+        cd.vmajor_gather(1, N, W, 1, x, idx, count, compact, cap)
+        cd.vmajor_scatter(1, N, W, 1, compact, idx, count, out, cap)
+        _sync()
+        assert torch.equal(compact, want)
+        new = cache.clone()
+        new[listed] = x[listed]
+        assert torch.equal(out, new)
+
+
 @gpu
 def test_binding_native_and_general_way():
     """The same calls through native marshalling (the current stream) and through ctypes (a stream object, numbers of other
