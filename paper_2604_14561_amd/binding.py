@@ -1,4 +1,4 @@
-"""Thin ctypes binding over libcocodiff.so: argument marshalling only.
+"""Thin binding over libcocodiff.so: argument marshalling only, the usual arguments in native code (csrc/marshal.c), the others by ctypes.
 
 Every step of the path runs in the library's HIP kernels.  Tensors are PyTorch
 CUDA(ROCm) tensors used for device memory; only their ``data_ptr()`` crosses the
