@@ -349,9 +349,9 @@ static bool streams_outputs(const cocodiff_shape* shape, OutLayout layout, bool 
 // The tiles read the first column themselves meanwhile (from column 0 on: 4 launches of 12 slower by 10 to 13 %).  Where a column takes
 // the fetching units longer than the tiles, they begin further on, so that they are caught up with at the end only (768 x 3072, two
 // weights, 16 units: 37.0 us from column 0 on, 33.5 from 1, 31.9 from 2).
-// Cold, without and with: 100 launches of one round, 110 .. 10000 tokens x 832 .. 3072 features, one to three weights, 6 to 11 % less on
-// average, 25 % at most.  With everything on chip already they cost 0 to 4 % (2304 x 3072, one weight 37.5 and 39.0 us; 768 x 3072, two
-// weights 29.4 and 29.8).
+// Cold, without and with: 70 launches of one round, 112 .. 9968 tokens x 768 .. 3072 features, one to three weights: 7 % less on average
+// (11 % up to 768 tokens), 25 % at most, 1 % more at worst.  With everything on chip already they cost up to 6 % (one weight, 2304 x 3072:
+// 37.5 us, 39.0 and 39.7 from two columns on; two weights, 768 x 3072: 29.4 and 29.8).
 static uint32_t fetching_workgroups(const LaunchPlan& p, int32_t M, int32_t D, int32_t n_tensors, uint32_t n_tiles, uint32_t* from) {
     constexpr uint32_t kAtLeast = 8, kAtMost = 32;
     constexpr int kSteps = 12;
