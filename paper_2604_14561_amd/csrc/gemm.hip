@@ -350,8 +350,10 @@ static bool streams_outputs(const cocodiff_shape* shape, OutLayout layout, bool 
 // the fetching units longer than the tiles, they begin further on, so that they are caught up with at the end only (768 x 3072, two
 // weights, 16 units: 37.0 us from column 0 on, 33.5 from 1, 31.9 from 2).
 // Cold, without and with: 70 launches of one round, 112 .. 9968 tokens x 768 .. 3072 features, one to three weights: 7 % less on average
-// (11 % up to 768 tokens), 25 % at most, 1 % more at worst.  With everything on chip already they cost up to 6 % (one weight, 2304 x 3072:
-// 37.5 us, 39.0 and 39.7 from two columns on; two weights, 768 x 3072: 29.4 and 29.8).
+// (11 % up to 768 tokens), 25 % at most, 1 % more at worst.  With everything on chip already they leave at once.
+// They hold units that another stream's kernel could take meanwhile; what both take together gets shorter all the same (projections of 9
+// shapes and permutations side by side, cold, without and with: 768 x 3072, two weights 40.5 and 38.2 us, 1552 x 3072 40.3 and 34.7, 3152 x 1536
+// 25.6 and 23.4, 1232 x 1152, three weights 20.1 and 19.6; none longer).
 static uint32_t fetching_workgroups(const LaunchPlan& p, int32_t M, int32_t D, int32_t n_tensors, uint32_t n_tiles, uint32_t* from) {
     constexpr uint32_t kAtLeast = 8, kAtMost = 32;
     constexpr int kSteps = 12;

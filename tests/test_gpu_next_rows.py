@@ -1313,6 +1313,36 @@ def test_proj_units_without_a_tile(oracle, bm, bn, N, H, n_tensors):
     test_proj_every_tile_shape(oracle, bm, bn, N, H, n_tensors)
 
 
+# Fetching workgroups leave where the operands are on chip: the same bits with operands that come from memory, where they stay, and with
+# operands that the call before has just read, for all ranks and for a rank in the middle, plain and fused.
+@gpu
+@pytest.mark.parametrize("N,H,d,P,rank", [(416, 13, 64, 1, 0), (768, 24, 128, 1, 0), (9216, 24, 128, 12, 7), (3152, 12, 128, 1, 0)])
+def test_proj_fetched_operands_cold_and_on_chip(N, H, d, P, rank):
+    import torch
+    D, gen = H * d, torch.Generator(device="cuda:0").manual_seed(N)
+    new = lambda *shape: torch.randn(shape, generator=gen, device="cuda:0", dtype=torch.bfloat16)
+    sh, x, w = cd.Shape.make(N, D, H, d, P, rank, 1), new(N, D), [new(D, D).mul_(D ** -0.5) for _ in range(3)]
+    rows = slice(rank * (N // P), (rank + 1) * (N // P))
+    table = to_dev(cd.rope_table((16, N // 16), (d // 4, d // 4), 10000.0))
+    rope, gamma = cd.Rope.make((16, N // 16), (d // 4, d // 4), 10000.0, table.data_ptr()), new(d)
+    push_out = torch.empty(1 << 29, device="cuda:0", dtype=torch.uint8)      # twice the last-level cache
+    got = []
+    for on_chip in (False, True, True, False):
+        out = [torch.zeros(N, D, device="cuda:0", dtype=torch.bfloat16) for _ in range(5)]
+        if not on_chip:
+            push_out.fill_(len(got))
+        cd.qkv_proj(sh, x, *w, *out[:3])
+        if not on_chip:
+            push_out.fill_(len(got))
+        cd.qkv_proj_fused(sh, x, w[0], w[1], None, gamma, gamma, 1e-6, rope, out[3], out[4], None, cd.SEND_MAJOR, None, None, None)
+        _sync()
+        got.append(out)
+    want = torch.matmul(x[rows].float(), w[0].float().t())
+    assert torch.allclose(got[0][0][rows].float(), want, atol=2e-2, rtol=1e-2)
+    for out in got[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(out, got[0]))
+
+
 @gpu
 @pytest.mark.parametrize("bm,bn,N,H,d", [
     (224, 128, 1872, 9, 128), (224, 128, 1904, 17, 64), (192, 128, 1584, 9, 128), (192, 128, 1632, 17, 64), (160, 128, 1296, 9, 128),
