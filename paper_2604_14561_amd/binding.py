@@ -26,7 +26,7 @@ EXPORTS = (
     "cocodiff_vmajor_select", "cocodiff_vmajor_select_static", "cocodiff_vmajor_select_workspace_bytes", "cocodiff_vmajor_gather",
     "cocodiff_vmajor_scatter", "cocodiff_vmajor_token_metric", "cocodiff_vmajor_topk", "cocodiff_cache_active_count",
     "cocodiff_a2a_pack_hs", "cocodiff_a2a_unpack_seq", "cocodiff_rope_table_bytes",
-    "cocodiff_rope_table_fill", "cocodiff_qkv_proj_plan", "cocodiff_util_copy", "cocodiff_util_mfma_rate", "cocodiff_version", "cocodiff_last_error",
+    "cocodiff_rope_table_fill", "cocodiff_qkv_proj_plan", "cocodiff_qkv_proj_route", "cocodiff_util_copy", "cocodiff_util_mfma_rate", "cocodiff_version", "cocodiff_last_error",
 )
 
 # the calls that csrc/marshal.c makes, in its order
@@ -111,6 +111,8 @@ def lib() -> ctypes.CDLL:
         L.cocodiff_rope_table_fill.argtypes = [rp, vp]
         L.cocodiff_util_copy.argtypes = [vp, vp, sz, vp]
         L.cocodiff_qkv_proj_plan.argtypes = [sp, i32, i32, vp, vp, vp, vp]
+        L.cocodiff_qkv_proj_route.argtypes = [sp, i32, i32, vp, vp, vp, vp, vp, vp]
+        L.cocodiff_qkv_proj_route.restype = ci
         L.cocodiff_qkv_proj_fused.argtypes = [sp, vp, vp, vp, vp, vp, vp, f32, rp, vp, vp, vp, ci, vp, vp, vp, vp]
         L.cocodiff_qkv_proj_fused.restype = ci
         L.cocodiff_qkv_proj_fused_select.argtypes = [sp, vp, vp, vp, vp, vp, vp, f32, rp, vp, vp, vp, ci, vp, vp, vp,
@@ -412,6 +414,16 @@ def qkv_proj_plan(shape: Shape, n_tensors: int, whole_heads: bool = False) -> di
     out = [ctypes.c_int32(0) for _ in range(4)]
     _check(lib().cocodiff_qkv_proj_plan(ctypes.byref(shape), int(n_tensors), int(bool(whole_heads)), *(ctypes.byref(o) for o in out)))
     return {"tile_tokens": out[0].value, "tile_features": out[1].value, "n_tiles": out[2].value, "compute_units": out[3].value}
+
+
+def qkv_proj_route(shape: Shape, n_tensors: int, form: str) -> dict:
+    """How the projection is launched (form: proj, pack, hs, fused, fused_select): tile and number of tiles, workgroups that fetch
+    operands and the column they begin with, whether its chunks or head-parallel V are streamed past the caches."""
+    names = ("tile_tokens", "tile_features", "n_tiles", "fetching", "fetch_from", "streamed")
+    out = [ctypes.c_int32(0) for _ in names]
+    _check(lib().cocodiff_qkv_proj_route(ctypes.byref(shape), int(n_tensors), ("proj", "pack", "hs", "fused", "fused_select").index(form),
+                                         *(ctypes.byref(o) for o in out)))
+    return {name: o.value for name, o in zip(names, out)}
 
 
 def util_copy(src, dst, nbytes: int, stream=None) -> None:

@@ -219,7 +219,7 @@ struct TileKernel {
     int bm, bn, lds;
     int per_cu;                   // workgroups that share a compute unit
     int min_steps;                // K steps below which the shape is left out
-    const void* entry[kLayouts];
+    const void* entry[kLayouts];  // nullptr: not built
 };
 
 // K steps from which on a launch may take the shapes that lie between the others, and counts its operands more dearly (tile_clocks).
@@ -333,13 +333,15 @@ static LaunchPlan plan_launch(int32_t M, int32_t D, int32_t n_tensors, bool whol
 //     x 2304 1083 -> 1063.  Of 28 to 57 MB streaming costs that call 0.7 to 1.6 % (the selection reads V from memory).
 //   * The chunks of a call for some of the ranks are sent away: one of 12 ranks at 9216 x 3072 71.2 -> 70.3 us, one of 16 at 26112 x
 //     2048 69.9 -> 68.0.  (All ranks in one call, so that the unpack reads them: 2144 x 2432 95.3 -> 96.6.)
+//   * Chunks are streamed as whole lines or not at all: tiles 192 and 64 features wide have no such kernel (gemm_chunks_streamed.hip).
 //   * A fused launch of one round stores everything at its end, and what is dirty then is written back behind it: 1440 x 1216 22.1 ->
 //     21.3 us, 3600 x 1152 35.8 -> 35.5, 11248 x 512 36.7 -> 35.8.  Below 2 MB there is too little of it, and the selection
 //     waits for memory (256 x 256 12.0 -> 13.3).
-static bool streams_outputs(const cocodiff_shape* shape, OutLayout layout, bool one_round) {
-    const size_t tensor = (size_t)shape->N * shape->D * 2;
-    if (layout == OUT_FUSED) return tensor > (size_t)96 << 20 || (one_round && tensor >= (size_t)2 << 20);
-    return layout == OUT_CHUNKS && (tensor > (size_t)96 << 20 || shape->rank_count < shape->P);
+// Rotations pair by pair (OUT_FUSED_ANY) have cached stores of V at any size.
+static bool streams_outputs(const cocodiff_shape* shape, OutLayout layout, const LaunchPlan& p, bool one_round) {
+    const size_t written = (size_t)shape->N * shape->D * 2;
+    if (layout == OUT_FUSED) return written > (size_t)96 << 20 || (one_round && written >= (size_t)2 << 20);
+    return layout == OUT_CHUNKS && p.pick->entry[OUT_CHUNKS_STREAMED] && (written > (size_t)96 << 20 || shape->rank_count < shape->P);
 }
 
 // Workgroups that only fetch operands (fetch_operands), and the column they begin with.
@@ -367,6 +369,28 @@ static uint32_t fetching_workgroups(const LaunchPlan& p, int32_t M, int32_t D, i
     const int columns = (D / BK + kFetchLines - 1) / kFetchLines;
     *from = (uint32_t)std::max(1, (int)(columns * (1.0 - kFetchLines * std::max(products, loads) / column) + 0.5));
     return fetchers;
+}
+
+// What is launched for a call: its tile shape, the workgroups that walk tiles and those that fetch for them, the kernel's layout.
+struct Route {
+    LaunchPlan plan;
+    uint32_t n_tiles, workers, fetchers, fetch_from;
+    OutLayout layout;
+};
+static Route route_launch(const cocodiff_shape* shape, int32_t n_tensors, OutLayout layout, bool quad_pairs, bool flags) {
+    Route r{};
+    const int32_t M = shape->rank_count * (shape->N / shape->P);
+    r.plan = plan_launch(M, shape->D, n_tensors, layout == OUT_FUSED, shape->d, flags);
+    if (!r.plan.pick) return r;
+    r.n_tiles = (uint32_t)r.plan.tiles_m * (uint32_t)r.plan.tiles_n_per_tensor * (uint32_t)n_tensors;
+    const uint32_t at_most = (uint32_t)(r.plan.n_cu * r.plan.pick->per_cu);
+    r.workers = r.plan.ring_kernel ? std::min(r.n_tiles, at_most) : r.n_tiles;
+    r.fetchers = fetching_workgroups(r.plan, M, shape->D, n_tensors, r.n_tiles, &r.fetch_from);
+    r.layout = layout;
+    if (layout == OUT_FUSED && !quad_pairs) r.layout = OUT_FUSED_ANY;
+    else if (r.plan.ring_kernel && streams_outputs(shape, layout, r.plan, r.n_tiles <= r.workers))
+        r.layout = layout == OUT_FUSED ? OUT_FUSED_STREAMED : OUT_CHUNKS_STREAMED;
+    return r;
 }
 
 // How many tile rows tile_at walks together in a fused launch of tiles_m x tiles_n tiles on `workgroups` workgroups.  The operands of
@@ -504,22 +528,6 @@ static int proj_launch(const cocodiff_shape* shape, const cocodiff_bf16* x,
     a.M = shape->rank_count * Ns;
     a.D = shape->D;
     if (a.D > 1 << 19) return fail(COCODIFF_ERR_SHAPE, "qkv_proj: D (%d) too large", a.D);
-    const LaunchPlan plan = plan_launch(a.M, a.D, a.n_tensors, layout == OUT_FUSED, shape->d, a.sel_prev != nullptr);
-    if (!plan.pick) return fail(COCODIFF_ERR_HIP, "qkv_proj: cannot read the compute-unit count");
-    if (layout == OUT_FUSED && !plan.ring_kernel)
-        return fail(COCODIFF_ERR_SHAPE, "qkv_proj_fused: D (%d) must be a multiple of 64 and at least 192", a.D);
-    const TileKernel* pick = plan.pick;
-    const bool ring_kernel = plan.ring_kernel;
-    a.bm = plan.bm;
-    a.bn = plan.bn;
-    a.tiles_m = plan.tiles_m;
-    a.tiles_n_per_tensor = plan.tiles_n_per_tensor;
-    const uint32_t n_tiles = (uint32_t)a.tiles_m * a.tiles_n_per_tensor * a.n_tensors;
-    a.n_tiles = (int32_t)n_tiles;
-    const uint32_t n_workgroups = (uint32_t)(plan.n_cu * pick->per_cu);      // workgroups at most
-    a.workers = ring_kernel ? std::min(n_tiles, n_workgroups) : n_tiles;
-    const uint32_t fetchers = fetching_workgroups(plan, a.M, a.D, a.n_tensors, n_tiles, &a.fetch_from);
-    a.group = layout == OUT_FUSED ? rows_walked_together(plan, (uint32_t)a.tiles_n_per_tensor * a.n_tensors, a.workers) : 8u;
     // the four pairs of eight consecutive features are 32 consecutive bytes of a table row when every axis has a multiple of four
     bool quad_pairs = true;
     for (int ax = 0; ax < 3; ++ax) a.row_base[ax] = a.row_stride[ax] = a.row_span[ax] = a.row_end[ax] = a.row_step16[ax] = 0;
@@ -536,6 +544,19 @@ static int proj_launch(const cocodiff_shape* shape, const cocodiff_bf16* x,
             rest /= rows;
         }
     }
+    const Route route = route_launch(shape, a.n_tensors, layout, quad_pairs, a.sel_prev != nullptr);
+    const LaunchPlan& plan = route.plan;
+    if (!plan.pick) return fail(COCODIFF_ERR_HIP, "qkv_proj: cannot read the compute-unit count");
+    if (layout == OUT_FUSED && !plan.ring_kernel)
+        return fail(COCODIFF_ERR_SHAPE, "qkv_proj_fused: D (%d) must be a multiple of 64 and at least 192", a.D);
+    a.bm = plan.bm;
+    a.bn = plan.bn;
+    a.tiles_m = plan.tiles_m;
+    a.tiles_n_per_tensor = plan.tiles_n_per_tensor;
+    a.n_tiles = (int32_t)route.n_tiles;
+    a.workers = route.workers;
+    a.fetch_from = route.fetch_from;
+    a.group = layout == OUT_FUSED ? rows_walked_together(plan, (uint32_t)a.tiles_n_per_tensor * a.n_tensors, a.workers) : 8u;
     // (dividend x divisor below 2^32, as the multiply-high division needs: a weight of more than 2^19 features squared is no
     // memory's)
     a.div_row8 = make_divisor(a.row8);
@@ -562,14 +583,10 @@ static int proj_launch(const cocodiff_shape* shape, const cocodiff_bf16* x,
     hipError_t le;
     static const void* const staged[] = {(const void*)qkv_gemm_staged_kernel<OUT_SEQ>, (const void*)qkv_gemm_staged_kernel<OUT_CHUNKS>,
                                           (const void*)qkv_gemm_staged_kernel<OUT_HEADS>};
-    const OutLayout kernel_layout = layout == OUT_FUSED && !quad_pairs                             ? OUT_FUSED_ANY
-                                    : !streams_outputs(shape, layout, n_tiles <= a.workers) ? layout
-                                    : layout == OUT_FUSED                                          ? OUT_FUSED_STREAMED
-                                                                                                   : OUT_CHUNKS_STREAMED;
-    if (ring_kernel)
-        le = hipLaunchKernel(pick->entry[kernel_layout], dim3(a.workers + fetchers), dim3(256), kernel_args, pick->lds, st);
+    if (plan.ring_kernel)
+        le = hipLaunchKernel(plan.pick->entry[route.layout], dim3(route.workers + route.fetchers), dim3(256), kernel_args, plan.pick->lds, st);
     else
-        le = hipLaunchKernel(staged[layout], dim3(n_tiles), dim3(kStagedThreads), kernel_args, kLdsBytes, st);
+        le = hipLaunchKernel(staged[layout], dim3(route.n_tiles), dim3(kStagedThreads), kernel_args, kLdsBytes, st);
     if (le != hipSuccess) return fail(COCODIFF_ERR_HIP, "qkv_proj: launch failed: %s", hipGetErrorString(le));
     return check_launch("qkv_gemm_kernel");
 }
@@ -701,5 +718,25 @@ extern "C" int cocodiff_qkv_proj_plan(const cocodiff_shape* shape, int32_t n_ten
     if (tile_features) *tile_features = p.bn;
     if (n_tiles) *n_tiles = p.tiles_m * p.tiles_n_per_tensor * n_tensors;
     if (n_compute_units) *n_compute_units = p.n_cu;
+    return COCODIFF_OK;
+}
+
+extern "C" int cocodiff_qkv_proj_route(const cocodiff_shape* shape, int32_t n_tensors, int32_t form, int32_t* tile_tokens, int32_t* tile_features,
+                                       int32_t* n_tiles, int32_t* fetching, int32_t* fetch_from, int32_t* streamed) {
+    int rc = check_shape(shape);
+    if (rc != COCODIFF_OK) return rc;
+    if (n_tensors < 1 || n_tensors > 3) return fail(COCODIFF_ERR_SHAPE, "qkv_proj_route: n_tensors (%d) must be 1, 2 or 3", n_tensors);
+    if (form < 0 || form > 4) return fail(COCODIFF_ERR_SHAPE, "qkv_proj_route: form (%d) must be 0 .. 4", form);
+    const OutLayout layout = form == 0 ? OUT_SEQ : form == 1 ? OUT_CHUNKS : form == 2 ? OUT_HEADS : OUT_FUSED;
+    const Route r = route_launch(shape, n_tensors, layout, true, form == 4 && flags_in_projection(shape, 16));
+    if (!r.plan.pick) return fail(COCODIFF_ERR_HIP, "qkv_proj_route: cannot read the compute-unit count");
+    if (layout == OUT_FUSED && (!r.plan.ring_kernel || (shape->d != 64 && shape->d != 128 && shape->d != 256)))
+        return fail(COCODIFF_ERR_SHAPE, "qkv_proj_route: no fused projection of D (%d) in heads of %d", shape->D, shape->d);
+    if (tile_tokens) *tile_tokens = r.plan.bm;
+    if (tile_features) *tile_features = r.plan.bn;
+    if (n_tiles) *n_tiles = (int32_t)r.n_tiles;
+    if (fetching) *fetching = (int32_t)r.fetchers;
+    if (fetch_from) *fetch_from = (int32_t)r.fetch_from;
+    if (streamed) *streamed = r.layout == OUT_CHUNKS_STREAMED || r.layout == OUT_FUSED_STREAMED;
     return COCODIFF_OK;
 }

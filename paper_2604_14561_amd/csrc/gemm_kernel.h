@@ -58,7 +58,7 @@ struct GemmArgs {
 // exchange buffer and to its head-parallel tensor (whichever are given).
 // OUT_FUSED_ANY: the same for rotations in which an axis' pairs are not a multiple of four (pair by pair through the table).
 // OUT_CHUNKS_STREAMED, OUT_FUSED_STREAMED: the chunks, and the fused form's head-parallel V, streamed past the caches too (streams_outputs
-// in gemm.hip says when).  Layouts of their own: a branch in the epilogue costs a launch of one round more than it gains (3600 x 1152
+// in gemm.hip says when; the chunks by tiles 256 and 128 features wide only).  Layouts of their own: a branch in the epilogue costs a launch of one round more than it gains (3600 x 1152
 // 36.3 us without, 37.3 with, 35.5 so).
 enum OutLayout { OUT_SEQ = 0, OUT_CHUNKS = 1, OUT_HEADS = 2, OUT_FUSED = 3, OUT_FUSED_ANY = 4, OUT_CHUNKS_STREAMED = 5, OUT_FUSED_STREAMED = 6 };
 constexpr int kLayouts = 7;
@@ -349,7 +349,8 @@ __device__ __forceinline__ float sum_of_halves(float first, float second) {
 template <int NI, int NJ, int LAYOUT>
 __device__ __forceinline__ void store_plain(const GemmArgs& a, const TileOut& t, uint16_t* __restrict__ Y) {
     constexpr int NP = NI / 2;
-    constexpr bool STREAM = LAYOUT == OUT_CHUNKS_STREAMED && NP % 2 == 0;      // whole lines, so feature groups in pairs
+    constexpr bool STREAM = LAYOUT == OUT_CHUNKS_STREAMED;
+    static_assert(!STREAM || NP % 2 == 0, "whole lines: feature groups in pairs");
     Dest<NP> to = LAYOUT == OUT_SEQ ? dest_seq<NP>(a, t.v8, t.tl) : is_chunks(LAYOUT) ? dest_chunks<NP>(a, t.v8, t.tl) : dest_heads<NP>(a, t.v8, t.tl);
     if constexpr (STREAM) to = paired(to, t.tl, a.row8);
     ChunkWalk chunk(a, t.n0);

@@ -1275,17 +1275,23 @@ def test_proj_every_long_tile_shape(oracle, bm, bn, N, H, n_tensors):
     test_proj_every_tile_shape(oracle, bm, bn, N, H, n_tensors)
 
 
-# A rank's own call streams its chunks, in whole lines where a wavefront's groups of 32 features come in pairs (tiles 256, 128 and 64
-# features wide, not 192), the call for all ranks does not: the same bits, and nothing outside the rank's chunks is touched.
+# A rank's own call streams its chunks as whole lines where a wavefront's groups of 32 features come in pairs (tiles 256 and 128
+# features wide, not 192 and 64), the call for all ranks does not: the same bits, and nothing outside the rank's chunks is touched.
+# The last four have a last feature tile of 128, 64, 192 and 64 features, of which a wavefront has all, or two of its four groups.
 @gpu
-@pytest.mark.parametrize("N,H,d,P", [(768, 24, 128, 4), (2560, 5, 64, 5), (18432, 12, 64, 2), (31104, 12, 64, 2), (10560, 22, 64, 2),
-                                     (9216, 24, 128, 12)])
+@pytest.mark.parametrize("N,H,d,P,bm,bn", [
+    (768, 24, 128, 4, 64, 64), (2560, 5, 64, 5, 32, 64), (18432, 12, 64, 2, 128, 256), (31104, 12, 64, 2, 288, 192), (10560, 22, 64, 2, 256, 128),
+    (9216, 24, 128, 12, 96, 128), (18432, 10, 64, 2, 128, 256), (24576, 9, 64, 3, 128, 256), (14832, 15, 64, 3, 96, 256), (31296, 21, 64, 3, 256, 256),
+])
 @pytest.mark.parametrize("order", [0, 1])
-def test_proj_pack_rank_by_rank(N, H, d, P, order):
-    """Tiles of 64 x 64, 32 x 64, 128 x 256, 288 x 192, 256 x 128 and 96 x 128."""
+def test_proj_pack_rank_by_rank(N, H, d, P, bm, bn, order):
     import torch
     D = H * d
     sh = cd.Shape.make(N, D, H, d, P)
+    route = cd.binding.qkv_proj_route(cd.Shape.make(N, D, H, d, P, P - 1, 1), 1, "pack")
+    assert not cd.binding.qkv_proj_route(sh, 1, "pack")["streamed"]
+    if cd.qkv_proj_plan(sh, 1)["compute_units"] == 256:
+        assert (route["tile_tokens"], route["tile_features"], route["streamed"]) == (bm, bn, bn % 128 == 0), route
     x = torch.randn(N, D, device="cuda:0", dtype=torch.bfloat16)
     w = torch.randn(D, D, device="cuda:0", dtype=torch.bfloat16) * D ** -0.5
     seq, whole, ranks = (torch.zeros(N * D, device="cuda:0", dtype=torch.bfloat16) for _ in range(3))
@@ -1303,6 +1309,22 @@ def test_proj_pack_rank_by_rank(N, H, d, P, order):
         sent = sent.to("cuda:0").view(-1, 1)
         assert torch.equal(ranks.view(P * P, -1) * sent, whole.view(P * P, -1) * sent)
         assert not bool((ranks.view(P * P, -1) * ~sent).any())
+
+
+# Which launches stream: chunks of some ranks' calls and of tensors above 96 MB, by tiles 256 and 128 features wide only; the fused form's V
+# above 96 MB and, from 2 MB on, in launches of one round.
+@gpu
+@pytest.mark.parametrize("form,N,H,d,P,ranks,streamed", [
+    ("pack", 9216, 24, 128, 12, 12, 0), ("pack", 9216, 24, 128, 12, 1, 1), ("pack", 99840, 24, 128, 8, 1, 0), ("pack", 20736, 24, 128, 12, 12, 1),
+    ("proj", 20736, 24, 128, 12, 12, 0), ("hs", 20736, 24, 128, 12, 12, 0), ("pack", 256, 10, 40, 2, 1, 0),
+    ("fused", 20736, 24, 128, 12, 12, 1), ("fused", 99840, 24, 128, 8, 2, 1),
+    ("fused", 20736, 24, 128, 24, 1, 1), ("fused", 256, 4, 64, 2, 2, 0), ("fused_select", 3600, 18, 64, 9, 9, 1), ("fused_select", 9216, 24, 128, 12, 12, 0),
+])
+def test_proj_route_streamed_outputs(form, N, H, d, P, ranks, streamed):
+    route = cd.binding.qkv_proj_route(cd.Shape.make(N, H * d, H, d, P, 0, ranks), 1, form)
+    print(form, N, H * d, route, flush=True)
+    if cd.qkv_proj_plan(cd.Shape.make(N, H * d, H, d, P), 1)["compute_units"] == 256:
+        assert route["streamed"] == streamed
 
 
 # Launches of one round whose idle units fetch operands: 8 of them (the fewest) over the last 5 of 13 K steps, 32 (the most) for
