@@ -337,9 +337,9 @@ static LaunchPlan plan_launch(int32_t M, int32_t D, int32_t n_tensors, bool whol
 //   * A fused launch of one round stores everything at its end, and what is dirty then is written back behind it: 1440 x 1216 22.1 ->
 //     21.3 us, 3600 x 1152 35.8 -> 35.5, 11248 x 512 36.7 -> 35.8.  Below 2 MB there is too little of it, and the selection
 //     waits for memory (256 x 256 12.0 -> 13.3).
-// Rotations pair by pair (OUT_FUSED_ANY) have cached stores of V at any size.
+// What counts is what the call writes: its own ranks' rows.  Rotations pair by pair (OUT_FUSED_ANY) have cached stores of V at any size.
 static bool streams_outputs(const cocodiff_shape* shape, OutLayout layout, const LaunchPlan& p, bool one_round) {
-    const size_t written = (size_t)shape->N * shape->D * 2;
+    const size_t written = (size_t)shape->rank_count * (shape->N / shape->P) * shape->D * 2;
     if (layout == OUT_FUSED) return written > (size_t)96 << 20 || (one_round && written >= (size_t)2 << 20);
     return layout == OUT_CHUNKS && p.pick->entry[OUT_CHUNKS_STREAMED] && (written > (size_t)96 << 20 || shape->rank_count < shape->P);
 }

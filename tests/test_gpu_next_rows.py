@@ -1312,12 +1312,12 @@ def test_proj_pack_rank_by_rank(N, H, d, P, bm, bn, order):
 
 
 # Which launches stream: chunks of some ranks' calls and of tensors above 96 MB, by tiles 256 and 128 features wide only; the fused form's V
-# above 96 MB and, from 2 MB on, in launches of one round.
+# above 96 MB and, from 2 MB on, in launches of one round.  A call for some of the ranks counts by its own rows.
 @gpu
 @pytest.mark.parametrize("form,N,H,d,P,ranks,streamed", [
     ("pack", 9216, 24, 128, 12, 12, 0), ("pack", 9216, 24, 128, 12, 1, 1), ("pack", 99840, 24, 128, 8, 1, 0), ("pack", 20736, 24, 128, 12, 12, 1),
     ("proj", 20736, 24, 128, 12, 12, 0), ("hs", 20736, 24, 128, 12, 12, 0), ("pack", 256, 10, 40, 2, 1, 0),
-    ("fused", 20736, 24, 128, 12, 12, 1), ("fused", 99840, 24, 128, 8, 2, 1),
+    ("fused", 20736, 24, 128, 12, 12, 1), ("fused", 99840, 24, 128, 8, 1, 0), ("fused", 99840, 24, 128, 8, 2, 1), ("fused", 6144, 24, 128, 24, 1, 0),
     ("fused", 20736, 24, 128, 24, 1, 1), ("fused", 256, 4, 64, 2, 2, 0), ("fused_select", 3600, 18, 64, 9, 9, 1), ("fused_select", 9216, 24, 128, 12, 12, 0),
 ])
 def test_proj_route_streamed_outputs(form, N, H, d, P, ranks, streamed):
