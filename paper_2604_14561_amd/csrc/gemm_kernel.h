@@ -658,26 +658,41 @@ __device__ __forceinline__ const GemmArgs& arguments_again() {
 // By XCD, each fetching what its own units read into its L2, is slower than none: three to seven times the lines, and a unit
 // takes some 37 bytes a clock whoever it reads for.
 // Where the operands are on chip already -- the same weights again, with less than the last-level cache in between -- fetching only
-// takes bandwidth from the tiles.  So each wavefront first asks for 16 lines that nobody has come to yet, 16 rows of the last weight at the
-// last K step, and leaves if all of them are there within 0.42 us: they take 0.28 to 0.40 us from the last-level cache, 0.44 to 0.76
-// if some of them come from memory.  (All 16, since a wavefront that leaves early leaves rows out whose tiles then wait at every step: with
-// one line asked for, a twentieth of the wavefronts left and half of the gain with them.)  60 launches of one round, 352 .. 8736 tokens x
-// 896 .. 3072 features, one to three weights, plain and fused, against no fetching: with everything on chip 1 to 2 % more without the
-// question, 10 % at most, and the same with it (0.1 % less on average); from memory 7.8 and 7.0 % less.
+// takes bandwidth from the tiles.  So each wavefront first asks for 32 lines that nobody has come to yet, 16 of the weights and 16 of x, and
+// the workgroup leaves if all its wavefronts had theirs within 0.42 us: such a load takes 0.28 to 0.44 us from the last-level cache,
+// 0.44 to 0.8 if some of it comes from memory.  As many lines, of both operands and by vote, since a workgroup that leaves takes its
+// share of the rows away and the tiles then wait at every step for the few lines that are missing: one line per wavefront kept half
+// of the gain, 16 of one weight none of it where a tenth of the operands had left the cache.
+// 27 launches of one round, 240 .. 3632 tokens x 1024 .. 3072 features, one to three weights, plain and fused, against no fetching, without
+// the question and with it: all on chip 2.5 % more (13 % at most) and 1.0 %; buffers of about the last-level cache's size in turn 10.4 and
+// 8.9 % less; from memory 8.9 and 9.2 % less.
 constexpr uint32_t kFetchLines = 8;      // a column: 8 lines of every row, 8 K steps
-constexpr uint64_t kOnChip = 42;         // of the 100 MHz clock
+constexpr uint32_t kOnChip = 42;         // of the 100 MHz clock
 __device__ __forceinline__ void fetch_operands(const GemmArgs& a) {
     constexpr uint32_t kLine = BK * 2, kRows = 64 / kFetchLines, kInFlight = 16;
     const uint32_t K = (uint32_t)a.D, row_lines = K * 2u / kLine, rows = (uint32_t)a.M + (uint32_t)a.n_tensors * K;
     const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = (gridDim.x - a.workers) * 4u;
     const uint32_t blocks = (rows + kRows - 1u) / kRows, columns = (row_lines + kFetchLines - 1u) / kFetchLines;
     uint32_t block = (blockIdx.x - a.workers) * 4u + wave, column = a.fetch_from;      // a load: one column of kRows rows
-    const auto* sample = (const __attribute__((address_space(1))) uint32_t*)(a.w[a.n_tensors - 1] + (size_t)((block * 16u + (lane & 15u)) % K) * K + (K - BK));
-    asm volatile("" : "+v"(sample));      // (its address is formed in front of the first look at the clock, and the load stays behind it)
-    const uint64_t asked = __builtin_amdgcn_s_memrealtime();
-    asm volatile("" : "+v"(sample));
-    asm volatile("" ::"v"(*sample));
-    if (__builtin_amdgcn_s_memrealtime() - asked < kOnChip) return;
+    {
+        extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+        const uint32_t i = block * 64u + (lane & 15u), xi = i % (uint32_t)a.M, wi = i % ((uint32_t)a.n_tensors * K);
+        const uint16_t* row = lane & 16u     ? a.x + ((size_t)a.row_begin + xi) * K
+                              : wi < K       ? a.w[0] + (size_t)wi * K
+                              : wi < 2u * K  ? a.w[1] + (size_t)(wi - K) * K
+                                             : a.w[2] + (size_t)(wi - 2u * K) * K;
+        const uint32_t line = kFetchLines + ((lane & 15u) + block) % (row_lines - kFetchLines);
+        const auto* sample = (const __attribute__((address_space(1))) uint32_t*)(row + line * BK);
+        asm volatile("" : "+v"(sample));      // (its address is formed in front of the first look at the clock, and the load stays behind it)
+        const uint64_t asked = __builtin_amdgcn_s_memrealtime();
+        asm volatile("" : "+v"(sample));
+        asm volatile("" ::"v"(*sample));
+        const uint32_t took = (uint32_t)(__builtin_amdgcn_s_memrealtime() - asked);
+        uint32_t* longest = reinterpret_cast<uint32_t*>(smem);
+        if (lane == 0) longest[wave] = took;
+        __syncthreads();
+        if (max(max(longest[0], longest[1]), max(longest[2], longest[3])) < kOnChip) return;
+    }
     while (column < columns) {
         uint32_t got[kInFlight] = {};
 #pragma unroll
