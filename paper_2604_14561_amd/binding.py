@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional, Sequence
 
 import numpy as np
@@ -141,21 +142,37 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+# what csrc/marshal.c's letters stand for
+_KINDS = {"S": [ctypes.POINTER(Shape)], "r": [ctypes.POINTER(Rope)], "R": [ctypes.POINTER(Rope)], "t": [ctypes.c_void_p],
+          "w": [ctypes.c_void_p, ctypes.c_size_t], "i": [ctypes.c_int32], "f": [ctypes.c_float]}
+
+
+def _general_way(*arguments):
+    """L.fast where there is no native marshalling: every call goes through ctypes."""
+    return None
+
+
 def _native_calls(L):
     """Calls with the usual arguments marshalled in native code (csrc/marshal.c): ``L.fast(which, *arguments)`` on the current
     stream, the call's code or None where the general way below has to take it.  Through ctypes a call takes the host 5 to 6 us, a
-    small call's kernels 3."""
+    small call's kernels 3.  An interpreter that it was not built for takes the general way for every call, with a warning; a
+    build of another version of the binding is an error, since it would call with the wrong arguments."""
+    rebuild = "build it with `python -m paper_2604_14561_amd.build`"
     try:
         from . import _marshal
-    except ImportError as missing:
-        raise FileNotFoundError(
-            f"the native part of the binding next to {LIB_PATH} is missing: build it with `python -m paper_2604_14561_amd.build`") from missing
+    except ImportError as why:
+        warnings.warn(f"the binding's native part cannot be loaded ({why}); calls take the host longer: {rebuild}", RuntimeWarning, stacklevel=3)
+        return _general_way
     try:
         import torch
         where = (torch.Tensor, torch.nn.Parameter, Shape, Rope, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
     except (ImportError, AttributeError):
-        return lambda *arguments: None
-    assert _marshal.NAMES == FAST
+        return _general_way
+    wanted = [tuple(getattr(L, name).argtypes) for name in FAST]
+    kinds = getattr(_marshal, "KINDS", ())
+    if (getattr(_marshal, "NAMES", None) != FAST or getattr(_marshal, "SIZES", None) != (ctypes.sizeof(Shape), ctypes.sizeof(Rope))
+            or [(*(c for k in each for c in _KINDS.get(k, (None,))), ctypes.c_void_p) for each in kinds] != wanted):
+        raise RuntimeError(f"{_marshal.__file__} was built for another version of this binding: {rebuild}")
     return _marshal.Calls(tuple(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in FAST), *where)
 
 

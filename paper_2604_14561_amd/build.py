@@ -7,6 +7,7 @@ import re
 import subprocess
 import sysconfig
 import tempfile
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -93,8 +94,13 @@ def build(verbose: bool = False) -> str:
             if verbose and err.strip():
                 print(err)
         _run([hipcc] + HIPCC_FLAGS + ["-shared", "-o", LIB_PATH] + objects)
-    _run([os.environ.get("CC", "gcc"), "-O2", "-std=gnu11", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
-          MARSHAL_SOURCE, "-o", MARSHAL_PATH])
+    include = sysconfig.get_paths()["include"]
+    if os.path.exists(os.path.join(include, "Python.h")):
+        _run([os.environ.get("CC", "gcc"), "-O2", "-std=gnu11", "-Wall", "-shared", "-fPIC", "-I", include, MARSHAL_SOURCE, "-o", MARSHAL_PATH])
+    else:      # the library needs no Python, and the binding works without its native part
+        if os.path.exists(MARSHAL_PATH):
+            os.remove(MARSHAL_PATH)
+        warnings.warn(f"no Python.h in {include}: the binding's native part is not built, and calls take the host longer", RuntimeWarning)
     return LIB_PATH
 
 

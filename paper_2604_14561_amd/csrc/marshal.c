@@ -15,7 +15,8 @@
 #include "../../include/cocodiff.h"
 
 /* which, the function, its arguments as the binding passes them: S shape, r rope, R rope or None, t tensor or None, w tensor passed with its size in
- * bytes, i int32, f float; the stream follows the last one. */
+ * bytes, i int32, f float; the stream follows the last one.  The binding holds NAMES, KINDS and SIZES (of the structures) against its own
+ * when it loads. */
 #define FUNCTIONS(F)                                                                                                         \
     F(qkv_proj, "Sttttttt") F(qk_norm_rope, "Sttttfr") F(qkv_proj_pack, "Sttttttti") F(qkv_proj_hs, "Sttttttt")           \
     F(qk_norm_rope_pack, "Sttttfrtti") F(a2a_unpack_norm_rope, "Sttttttfri") F(a2a_unpack_select, "Stittifttttiw")           \
@@ -252,19 +253,22 @@ static PyTypeObject CallsType = {
 static struct PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", NULL, -1, NULL, NULL, NULL, NULL, NULL};
 
 PyMODINIT_FUNC PyInit__marshal(void) {
-    PyObject *m, *names, *kinds;
+    PyObject *m, *names, *kinds, *sizes;
     s_is_cuda = PyUnicode_InternFromString("is_cuda");
     s_is_contiguous = PyUnicode_InternFromString("is_contiguous");
     s_data_ptr = PyUnicode_InternFromString("data_ptr");
     s_numel = PyUnicode_InternFromString("numel");
     s_element_size = PyUnicode_InternFromString("element_size");
-    if (PyType_Ready(&CallsType) < 0 || !(m = PyModule_Create(&module)) || !(names = PyTuple_New(N_CALLS)) || !(kinds = PyTuple_New(N_CALLS)))
+    if (PyType_Ready(&CallsType) < 0 || !(m = PyModule_Create(&module)) || !(names = PyTuple_New(N_CALLS)) || !(kinds = PyTuple_New(N_CALLS)) ||
+        !(sizes = Py_BuildValue("(nn)", (Py_ssize_t)sizeof(cocodiff_shape), (Py_ssize_t)sizeof(cocodiff_rope))))
         return NULL;
     for (int k = 0; k < N_CALLS; ++k) {
         PyTuple_SET_ITEM(names, k, PyUnicode_FromFormat("cocodiff_%s", kNames[k]));
         PyTuple_SET_ITEM(kinds, k, PyUnicode_FromString(kKinds[k]));
     }
     Py_INCREF(&CallsType);
-    if (PyModule_AddObject(m, "NAMES", names) < 0 || PyModule_AddObject(m, "KINDS", kinds) < 0 || PyModule_AddObject(m, "Calls", (PyObject*)&CallsType) < 0) return NULL;
+    if (PyModule_AddObject(m, "NAMES", names) < 0 || PyModule_AddObject(m, "KINDS", kinds) < 0 || PyModule_AddObject(m, "SIZES", sizes) < 0 ||
+        PyModule_AddObject(m, "Calls", (PyObject*)&CallsType) < 0)
+        return NULL;
     return m;
 }

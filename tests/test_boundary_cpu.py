@@ -165,6 +165,46 @@ def test_native_marshalling_follows_the_abi():
             L.fast(*wrong)
 
 
+def test_without_native_marshalling_calls_go_through_ctypes(monkeypatch):
+    """No module for this interpreter (none built, or one that does not load): a warning, and the same calls and errors."""
+    import sys
+    import torch
+    L = B.lib()
+    monkeypatch.delattr(cd, "_marshal")
+    monkeypatch.setitem(sys.modules, "paper_2604_14561_amd._marshal", None)
+    with pytest.warns(RuntimeWarning, match="paper_2604_14561_amd.build"):
+        fast = B._native_calls(L)
+    monkeypatch.setattr(L, "fast", fast)
+    s, x = cd.Shape.make(256, 256, 4, 64, 2), torch.zeros(256, 256, dtype=torch.int16)
+    assert L.fast(B._PACK, s, x, x, 0) is None
+    with pytest.raises(ValueError):
+        cd.a2a_pack(s, x, x, cd.SEND_MAJOR)
+    with pytest.raises(cd.CocodiffError):
+        cd.a2a_pack(cd.Shape.make(250, 256, 4, 64, 4), 0x1000, 0x2000, cd.SEND_MAJOR, stream=0)
+
+
+@pytest.mark.parametrize("change", [
+    dict(NAMES=B.FAST[::-1]), dict(NAMES=None), dict(SIZES=(28, 36)), dict(SIZES=None), dict(KINDS=()), dict(KINDS=None),
+    dict(KINDS=("Stttttt",), at=0), dict(KINDS=("Stttttfti",), at=0), dict(KINDS=("Sttttttt?",), at=0), dict(KINDS=("Sttj",), at=7),
+])
+def test_native_marshalling_of_another_version_is_refused(monkeypatch, change):
+    """Other calls, another argument (count or kind) or other structures than the binding's: an error that says how to rebuild."""
+    import sys
+    import types
+    L = B.lib()
+    from paper_2604_14561_amd import _marshal
+    stale = types.SimpleNamespace(__file__="_marshal.so", NAMES=_marshal.NAMES, KINDS=_marshal.KINDS, SIZES=_marshal.SIZES, Calls=_marshal.Calls)
+    at = change.pop("at", None)
+    for name, value in change.items():
+        if at is not None:
+            value = _marshal.KINDS[:at] + value + _marshal.KINDS[at + 1:]
+        stale.__dict__.pop(name) if value is None else setattr(stale, name, value)
+    monkeypatch.setattr(cd, "_marshal", stale)
+    monkeypatch.setitem(sys.modules, "paper_2604_14561_amd._marshal", stale)
+    with pytest.raises(RuntimeError, match="paper_2604_14561_amd.build"):
+        B._native_calls(L)
+
+
 def test_fused_entry_points_check_arguments_before_any_launch():
     L = B.lib()
     fake, odd = ctypes.c_void_p(0x1000), ctypes.c_void_p(0x1004)
