@@ -350,9 +350,12 @@ static bool streams_outputs(const cocodiff_shape* shape, OutLayout layout, const
 // step's loads take as long as its products: tiles of 288 x 192, 224 x 256 and 256 x 256 are -1 to +2 % with them, 192 x 256 -2 to -7 %.
 // The tiles read the first column themselves meanwhile (from column 0 on: 4 launches of 12 slower by 10 to 13 %).  Where a column takes
 // the fetching units longer than the tiles, they begin further on, so that they are caught up with at the end only (768 x 3072, two
-// weights, 16 units: 37.0 us from column 0 on, 33.5 from 1, 31.9 from 2).
+// weights, 16 units: 37.0 us from column 0 on, 33.5 from 1, 31.9 from 2).  Their rate is taken a sixth below kBytesPerClock: fetching
+// units that the tiles overtake cost more than they give (432 x 2176, two weights, 18 units: 18.2 us from column 1 on, 15.9 from 2, 17.9
+// without any; on chip 14.5, 12.9 and 12.8; fused 256 x 3072, three weights, 32 units: 29.8 from 1, 28.6 from 2, 30.1 without; 27 launches
+// from memory 9.0 % less than without any at the full rate and 10.0 % so).
 // Cold, without and with: 70 launches of one round, 112 .. 9968 tokens x 768 .. 3072 features, one to three weights: 7 % less on average
-// (11 % up to 768 tokens), 25 % at most, 1 % more at worst.  With everything on chip already they leave at once.
+// (11 % up to 768 tokens), 25 % at most, 1 % more at worst.  With everything on chip already most leave at once (fetch_operands).
 // They hold units that another stream's kernel could take meanwhile; what both take together gets shorter all the same (projections of 9
 // shapes and permutations side by side, cold, without and with: 768 x 3072, two weights 40.5 and 38.2 us, 1552 x 3072 40.3 and 34.7, 3152 x 1536
 // 25.6 and 23.4, 1232 x 1152, three weights 20.1 and 19.6; none longer).
@@ -365,7 +368,7 @@ static uint32_t fetching_workgroups(const LaunchPlan& p, int32_t M, int32_t D, i
     const double products = tile_mfmas(*p.pick) * 17.2 + 60.0, loads = tile_operand_bytes(*p.pick) / kBytesPerClock;
     if (products > 1.13 * loads) return 0;
     const uint32_t fetchers = std::min(units - n_tiles, kAtMost);
-    const double column = ((double)M + (double)n_tensors * D) * kFetchLines * BK * 2.0 / (fetchers * kBytesPerClock);
+    const double column = ((double)M + (double)n_tensors * D) * kFetchLines * BK * 2.0 / (fetchers * kBytesPerClock / 1.2);
     const int columns = (D / BK + kFetchLines - 1) / kFetchLines;
     *from = (uint32_t)std::max(1, (int)(columns * (1.0 - kFetchLines * std::max(products, loads) / column) + 0.5));
     return fetchers;

@@ -664,8 +664,11 @@ __device__ __forceinline__ const GemmArgs& arguments_again() {
 // share of the rows away and the tiles then wait at every step for the few lines that are missing: one line per wavefront kept half
 // of the gain, 16 of one weight none of it where a tenth of the operands had left the cache.
 // 27 launches of one round, 240 .. 3632 tokens x 1024 .. 3072 features, one to three weights, plain and fused, against no fetching, without
-// the question and with it: all on chip 2.5 % more (13 % at most) and 1.0 %; buffers of about the last-level cache's size in turn 10.4 and
-// 8.9 % less; from memory 8.9 and 9.2 % less.
+// the question and with it: all on chip 2.0 % more (10 % at most) and 0.5 %; buffers of about the last-level cache's size in turn 10.7 and
+// 9.4 % less; from memory 9.8 and 10.1 % less.
+// Whole layers in one call (12, 256 .. 2304 tokens x 1408 .. 3072 features), asked and left above 0.42, 0.46 or 0.50 us: all on chip 2.0 % more
+// without the question, 1.4, 0.7 and 0.4 % with it (at worst 8, 5, 3 and 2 %: 1152 x 2048); around the cache's size 13 % less, 9, 5 and 4 %: what is
+// missing there comes in 0.44 to 0.5 us too, since memory has little to do; from memory 11 % less with any.
 constexpr uint32_t kFetchLines = 8;      // a column: 8 lines of every row, 8 K steps
 constexpr uint32_t kOnChip = 42;         // of the 100 MHz clock
 __device__ __forceinline__ void fetch_operands(const GemmArgs& a) {

@@ -1327,6 +1327,24 @@ def test_proj_route_streamed_outputs(form, N, H, d, P, ranks, streamed):
         assert route["streamed"] == streamed
 
 
+# How many units fetch operands, and from which column of eight K steps on: the fewest and the most; so few for so much that they begin
+# further on; a rank in the middle as a call for as many tokens; none with 12 K steps, 7 idle units, two workgroups to a unit, more than one
+# round or tiles whose products take longer than their loads.
+@gpu
+@pytest.mark.parametrize("form,N,H,d,P,ranks,n_tensors,fetching,fetch_from", [
+    ("proj", 7904, 13, 64, 1, 1, 1, 8, 1), ("proj", 416, 13, 64, 1, 1, 3, 32, 1), ("proj", 768, 48, 64, 1, 1, 3, 16, 3),
+    ("pack", 432, 17, 128, 1, 1, 2, 18, 2), ("fused", 768, 24, 128, 1, 1, 2, 16, 3), ("fused", 9216, 24, 128, 12, 1, 2, 16, 3),
+    ("pack", 9216, 24, 128, 12, 1, 1, 32, 1), ("fused_select", 256, 24, 128, 2, 2, 3, 32, 1), ("fused", 256, 24, 128, 2, 2, 3, 32, 2),
+    ("proj", 7904, 12, 64, 1, 1, 1, 0, 0), ("fused_select", 896, 24, 128, 1, 1, 3, 0, 0), ("proj", 96, 13, 64, 1, 1, 1, 0, 0),
+    ("pack", 9216, 24, 128, 12, 12, 3, 0, 0), ("proj", 3152, 12, 128, 1, 1, 3, 0, 0),
+])
+def test_proj_route_fetching_workgroups(form, N, H, d, P, ranks, n_tensors, fetching, fetch_from):
+    route = cd.binding.qkv_proj_route(cd.Shape.make(N, H * d, H, d, P, (P - ranks) // 2, ranks), n_tensors, form)
+    print(form, N, H * d, n_tensors, route, flush=True)
+    if cd.qkv_proj_plan(cd.Shape.make(N, H * d, H, d, P), 1)["compute_units"] == 256:
+        assert (route["fetching"], route["fetch_from"]) == (fetching, fetch_from)
+
+
 # Launches of one round whose idle units fetch operands: 8 of them (the fewest) over the last 5 of 13 K steps, 32 (the most) for
 # 416 tokens, and 16 that begin with the fourth column of eight K steps.
 @gpu
