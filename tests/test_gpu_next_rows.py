@@ -1562,6 +1562,39 @@ def test_gather_scatter_of_many_tokens(N, W, kept):
         assert torch.equal(out, new)
 
 
+# The same with several segments and tiles of two tokens (a lane's division by the segment, the segments' offsets), one entry of the list
+# outside the tensor, and a count above the list's length: what is listed inside is moved, nothing else is touched.
+@gpu
+@pytest.mark.parametrize("S,N,W,T", [(3, 2051, 40, 1), (4, 4102, 64, 2), (24, 4099, 64, 1), (2, 6150, 8, 3), (3, 2048, 40, 1), (25, 2051, 88, 1)])
+@pytest.mark.parametrize("bad", [-1, "NT"])
+def test_gather_scatter_of_many_tiles_in_segments(S, N, W, T, bad):
+    import torch
+    NT = N // T
+    gen = torch.Generator(device="cuda:0").manual_seed(N + W + S)
+    bits = lambda *shape: torch.randint(-32768, 32767, shape, generator=gen, device="cuda:0", dtype=torch.int16)
+    x, cache = bits(S, NT, T, W), bits(S, NT, T, W)
+    for cap in (NT, NT - 3):
+        idx = torch.randperm(NT, generator=gen, device="cuda:0")[:cap].sort().values.int()
+        idx[cap // 3] = NT if bad == "NT" else bad
+        inside = torch.arange(cap, device="cuda:0") != cap // 3
+        listed = idx[inside].long()
+        for n in (cap // 2, NT + 5):
+            count = torch.tensor([n], device="cuda:0", dtype=torch.int32)
+            compact, out = bits(S, cap, T, W), cache.clone()
+            moved = listed[:n - 1] if n < cap else listed
+            slots = torch.arange(cap, device="cuda:0")[inside][:len(moved)]
+            want = compact.clone()
+            want[:, slots] = x[:, moved]
+            cd.vmajor_gather(S, N, W, T, x, idx, count, compact, cap)
+            _sync()
+            assert torch.equal(compact, want)
+            new = cache.clone()
+            new[:, moved] = compact[:, slots]
+            cd.vmajor_scatter(S, N, W, T, compact, idx, count, out, cap)
+            _sync()
+            assert torch.equal(out, new)
+
+
 @gpu
 def test_binding_native_and_general_way():
     """The same calls through native marshalling (the current stream) and through ctypes (a stream object, numbers of other
