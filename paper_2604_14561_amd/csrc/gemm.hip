@@ -335,7 +335,8 @@ static LaunchPlan plan_launch(int32_t M, int32_t D, int32_t n_tensors, bool whol
 //     2048 69.9 -> 68.0.  (All ranks in one call, so that the unpack reads them: 2144 x 2432 95.3 -> 96.6.)
 //   * Chunks are streamed as whole lines or not at all: tiles 192 and 64 features wide have no such kernel (gemm_chunks_streamed.hip).
 //   * A fused launch of one round stores everything at its end, and what is dirty then is written back behind it: 1440 x 1216 22.1 ->
-//     21.3 us, 3600 x 1152 35.8 -> 35.5, 11248 x 512 36.7 -> 35.8.  Below 2 MB there is too little of it, and the selection
+//     21.3 us, 3600 x 1152 35.8 -> 35.5, 11248 x 512 36.7 -> 35.8; with a long K loop too, 896 x 3072 58.8 -> 57.5, 1440 x 3072 79.9 ->
+//     79.3, of some 2.3 MB 0 to 0.5 % more with everything on chip (384 x 3072, 544 x 2176).  Below 2 MB there is too little of it, and the selection
 //     waits for memory (256 x 256 12.0 -> 13.3).
 // What counts is what the call writes: its own ranks' rows.  Rotations pair by pair (OUT_FUSED_ANY) have cached stores of V at any size.
 static bool streams_outputs(const cocodiff_shape* shape, OutLayout layout, const LaunchPlan& p, bool one_round) {
@@ -353,7 +354,7 @@ static bool streams_outputs(const cocodiff_shape* shape, OutLayout layout, const
 // weights, 16 units: 37.0 us from column 0 on, 33.5 from 1, 31.9 from 2).  Their rate is taken a sixth below kBytesPerClock: fetching
 // units that the tiles overtake cost more than they give (432 x 2176, two weights, 18 units: 18.2 us from column 1 on, 15.9 from 2, 17.9
 // without any; on chip 14.5, 12.9 and 12.8; fused 256 x 3072, three weights, 32 units: 29.8 from 1, 28.6 from 2, 30.1 without; 27 launches
-// from memory 9.0 % less than without any at the full rate and 10.0 % so).
+// from memory 9.2 % less than without any at the full rate and 10.1 % so).
 // Cold, without and with: 70 launches of one round, 112 .. 9968 tokens x 768 .. 3072 features, one to three weights: 7 % less on average
 // (11 % up to 768 tokens), 25 % at most, 1 % more at worst.  With everything on chip already most leave at once (fetch_operands).
 // They hold units that another stream's kernel could take meanwhile; what both take together gets shorter all the same (projections of 9

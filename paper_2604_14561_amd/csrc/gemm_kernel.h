@@ -654,7 +654,7 @@ __device__ __forceinline__ const GemmArgs& arguments_again() {
 // in the order in which the K loops come to them.  A K step's loads are a few steps ahead, less than a trip to memory takes; so
 // the tiles find their operands in the last-level cache.  (Streamed loads leave nothing there.)
 // 64 units of 256 without a tile and 16, cold: 768 tokens of 9216, 3072 features, one weight and two with norm and rotation, and the
-// other calls of that rank, 80.2 -> 72.9 us; the latter launch alone 38.4 -> 31.9, 29.4 with everything on chip.
+// other calls of that rank, 72.8 -> 67.7 us; the latter launch alone 38.4 -> 31.9, 29.4 with everything on chip.
 // By XCD, each fetching what its own units read into its L2, is slower than none: three to seven times the lines, and a unit
 // takes some 37 bytes a clock whoever it reads for.
 // Where the operands are on chip already -- the same weights again, with less than the last-level cache in between -- fetching only
@@ -667,8 +667,9 @@ __device__ __forceinline__ const GemmArgs& arguments_again() {
 // the question and with it: all on chip 2.0 % more (10 % at most) and 0.5 %; buffers of about the last-level cache's size in turn 10.7 and
 // 9.4 % less; from memory 9.8 and 10.1 % less.
 // Whole layers in one call (12, 256 .. 2304 tokens x 1408 .. 3072 features), asked and left above 0.42, 0.46 or 0.50 us: all on chip 2.0 % more
-// without the question, 1.4, 0.7 and 0.4 % with it (at worst 8, 5, 3 and 2 %: 1152 x 2048); around the cache's size 13 % less, 9, 5 and 4 %: what is
-// missing there comes in 0.44 to 0.5 us too, since memory has little to do; from memory 11 % less with any.
+// without the question, 1.4, 0.7 and 0.4 % with it (at worst 5 to 8 %, and 2 to 7 %: 1152 x 2048); around the cache's size 13 % less, 9, 5 and 4 %:
+// what is missing there comes in 0.44 to 0.5 us too, since memory has little to do; from memory 11 % less with any.  Leaving where one, two
+// or three of the four wavefronts stay below 0.34 to 0.42 us, or samples spread over all rows, lie between the same two ends.
 constexpr uint32_t kFetchLines = 8;      // a column: 8 lines of every row, 8 K steps
 constexpr uint32_t kOnChip = 42;         // of the 100 MHz clock
 __device__ __forceinline__ void fetch_operands(const GemmArgs& a) {
