@@ -370,10 +370,11 @@ COCODIFF_API int cocodiff_qkv_proj_plan(const cocodiff_shape* shape, int32_t n_t
 
 /* How such a launch runs, for the same uses.  form: 0 cocodiff_qkv_proj, 1 _pack, 2 _hs, 3 _fused (pairs in fours on every axis), 4
  * _fused_select with tiles of 16 tokens.  Besides the tile and the number of tiles: workgroups that only fetch operands on units without
- * a tile, the column of 512 elements along K that they begin with (0 if there are none), and whether the exchange buffer's
+ * a tile, the column of 512 elements along K that they begin with (0 if there are none), the tile rows walked together, and whether the exchange buffer's
  * chunks (1) or the head-parallel V (3, 4) are stored past the caches.  None of it changes a result. */
 COCODIFF_API int cocodiff_qkv_proj_route(const cocodiff_shape* shape, int32_t n_tensors, int32_t form, int32_t* tile_tokens, int32_t* tile_features,
-                                         int32_t* n_tiles, int32_t* fetching, int32_t* fetch_from, int32_t* streamed);
+                                         int32_t* n_tiles, int32_t* fetching, int32_t* fetch_from, int32_t* streamed,
+                                         int32_t* rows_together);
 
 /* Bytes of the cos/sin table described at cocodiff_rope (0 on a bad description; `cs` is ignored). */
 COCODIFF_API size_t cocodiff_rope_table_bytes(const cocodiff_rope* rope);

@@ -112,7 +112,7 @@ def lib() -> ctypes.CDLL:
         L.cocodiff_rope_table_fill.argtypes = [rp, vp]
         L.cocodiff_util_copy.argtypes = [vp, vp, sz, vp]
         L.cocodiff_qkv_proj_plan.argtypes = [sp, i32, i32, vp, vp, vp, vp]
-        L.cocodiff_qkv_proj_route.argtypes = [sp, i32, i32, vp, vp, vp, vp, vp, vp]
+        L.cocodiff_qkv_proj_route.argtypes = [sp, i32, i32, vp, vp, vp, vp, vp, vp, vp]
         L.cocodiff_qkv_proj_route.restype = ci
         L.cocodiff_qkv_proj_fused.argtypes = [sp, vp, vp, vp, vp, vp, vp, f32, rp, vp, vp, vp, ci, vp, vp, vp, vp]
         L.cocodiff_qkv_proj_fused.restype = ci
@@ -435,8 +435,8 @@ def qkv_proj_plan(shape: Shape, n_tensors: int, whole_heads: bool = False) -> di
 
 def qkv_proj_route(shape: Shape, n_tensors: int, form: str) -> dict:
     """How the projection is launched (form: proj, pack, hs, fused, fused_select): tile and number of tiles, workgroups that fetch
-    operands and the column they begin with, whether its chunks or head-parallel V are streamed past the caches."""
-    names = ("tile_tokens", "tile_features", "n_tiles", "fetching", "fetch_from", "streamed")
+    operands and the column they begin with, the tile rows walked together, whether its chunks or head-parallel V are streamed past the caches."""
+    names = ("tile_tokens", "tile_features", "n_tiles", "fetching", "fetch_from", "streamed", "rows_together")
     out = [ctypes.c_int32(0) for _ in names]
     _check(lib().cocodiff_qkv_proj_route(ctypes.byref(shape), int(n_tensors), ("proj", "pack", "hs", "fused", "fused_select").index(form),
                                          *(ctypes.byref(o) for o in out)))

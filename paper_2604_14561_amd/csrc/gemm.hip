@@ -375,28 +375,6 @@ static uint32_t fetching_workgroups(const LaunchPlan& p, int32_t M, int32_t D, i
     return fetchers;
 }
 
-// What is launched for a call: its tile shape, the workgroups that walk tiles and those that fetch for them, the kernel's layout.
-struct Route {
-    LaunchPlan plan;
-    uint32_t n_tiles, workers, fetchers, fetch_from;
-    OutLayout layout;
-};
-static Route route_launch(const cocodiff_shape* shape, int32_t n_tensors, OutLayout layout, bool quad_pairs, bool flags) {
-    Route r{};
-    const int32_t M = shape->rank_count * (shape->N / shape->P);
-    r.plan = plan_launch(M, shape->D, n_tensors, layout == OUT_FUSED, shape->d, flags);
-    if (!r.plan.pick) return r;
-    r.n_tiles = (uint32_t)r.plan.tiles_m * (uint32_t)r.plan.tiles_n_per_tensor * (uint32_t)n_tensors;
-    const uint32_t at_most = (uint32_t)(r.plan.n_cu * r.plan.pick->per_cu);
-    r.workers = r.plan.ring_kernel ? std::min(r.n_tiles, at_most) : r.n_tiles;
-    r.fetchers = fetching_workgroups(r.plan, M, shape->D, n_tensors, r.n_tiles, &r.fetch_from);
-    r.layout = layout;
-    if (layout == OUT_FUSED && !quad_pairs) r.layout = OUT_FUSED_ANY;
-    else if (r.plan.ring_kernel && streams_outputs(shape, layout, r.plan, r.n_tiles <= r.workers))
-        r.layout = layout == OUT_FUSED ? OUT_FUSED_STREAMED : OUT_CHUNKS_STREAMED;
-    return r;
-}
-
 // How many tile rows tile_at walks together in a fused launch of tiles_m x tiles_n tiles on `workgroups` workgroups.  The operands of
 // a launch come from memory when they are read first -- a layer's weights are not on chip -- and a round in which any tile
 // reads something new runs at that pace, since a K step's loads are two steps ahead at most.  So the walk is chosen whose first
@@ -410,13 +388,21 @@ static Route route_launch(const cocodiff_shape* shape, int32_t n_tensors, OutLay
 //   4608 x 2816, 29 x 33         8: 234.1  6: [208.3]  5: [206.9]  4: 219.8  3: 209.2
 //   2304 x 3072, 12 x 36         8: 136.6  6: 133.9  5: [126.9]  4: [125.3]  3: 136.9
 // and with everything on chip 109.5 (8) and 109.6 (4) at 2304 x 3072.
-static uint32_t rows_walked_together(const LaunchPlan& p, uint32_t tiles_n, uint32_t workgroups) {
+// In one round everything is touched at once.  Where some rows are left over from the groups of 8, the last XCD walks them along all
+// columns: 9 rows of 24 columns give it 25 panels of W and the others 3.5, it is the last to end, and fetching workgroups on it
+// take from what it waits for.  So a launch with fetching workgroups and more than 8 rows takes the size with the fewest operand rows for
+// the XCD that has most, if that is a twentieth less.  The whole call, 8 rows / so, on chip and from memory: 1152 x 2048 38.0 / 35.9 and 42.0 /
+// 39.7 us, 1520 x 1024 19.8 / 19.2 and 22.0 / 21.7, 1088 x 2304 42.5 / 41.3 and 45.4 / 45.0; 16 others -3.6 to +0.2 %.  (28 launches without
+// fetching workgroups: -3 to +1.5 %, so they stay.)
+static uint32_t rows_walked_together(const LaunchPlan& p, uint32_t tiles_n, uint32_t workgroups, bool fetching) {
     const uint32_t tiles_m = (uint32_t)p.tiles_m;
-    if (tiles_m > 64 || tiles_n > 64 || tiles_m * tiles_n <= workgroups) return 8;
     const uint32_t n_tiles = tiles_m * tiles_n;
+    const bool one_round = n_tiles <= workgroups;
+    if (tiles_m > 64 || tiles_n > 64 || (one_round && (!fetching || tiles_m <= 8))) return 8;
     const auto bits = [](uint32_t from, uint32_t count) { return (count >= 64 ? ~0ull : (1ull << count) - 1ull) << from; };
     uint32_t best = 8, best_rows = UINT32_MAX;
-    for (uint32_t g : {8u, 6u, 5u, 4u, 3u}) {
+    for (uint32_t g : {8u, 6u, 5u, 4u, 3u, 7u, 9u, 10u}) {
+        if (!one_round && (g == 7 || g > 8)) break;
         uint64_t rows = 0, cols = 0;
         uint32_t most = 0;
         for (uint32_t xcd = 0; xcd < 8; ++xcd) {      // as tiles_of_block deals them out
@@ -437,12 +423,36 @@ static uint32_t rows_walked_together(const LaunchPlan& p, uint32_t tiles_n, uint
             cols |= c;
             most = std::max(most, (uint32_t)(__builtin_popcountll(r) * p.bm + __builtin_popcountll(c) * p.bn));
         }
-        if (rows == bits(0, tiles_m) && cols == bits(0, tiles_n) && most < best_rows) {
+        const bool fewer = one_round && g != 8 ? most < best_rows - best_rows / 20 : most < best_rows;
+        if (rows == bits(0, tiles_m) && cols == bits(0, tiles_n) && fewer) {
             best = g;
             best_rows = most;
         }
     }
     return best;
+}
+
+// What is launched for a call: its tile shape, the workgroups that walk tiles and those that fetch for them, the kernel's layout.
+struct Route {
+    LaunchPlan plan;
+    uint32_t n_tiles, workers, fetchers, fetch_from, group;
+    OutLayout layout;
+};
+static Route route_launch(const cocodiff_shape* shape, int32_t n_tensors, OutLayout layout, bool quad_pairs, bool flags) {
+    Route r{};
+    const int32_t M = shape->rank_count * (shape->N / shape->P);
+    r.plan = plan_launch(M, shape->D, n_tensors, layout == OUT_FUSED, shape->d, flags);
+    if (!r.plan.pick) return r;
+    r.n_tiles = (uint32_t)r.plan.tiles_m * (uint32_t)r.plan.tiles_n_per_tensor * (uint32_t)n_tensors;
+    const uint32_t at_most = (uint32_t)(r.plan.n_cu * r.plan.pick->per_cu);
+    r.workers = r.plan.ring_kernel ? std::min(r.n_tiles, at_most) : r.n_tiles;
+    r.fetchers = fetching_workgroups(r.plan, M, shape->D, n_tensors, r.n_tiles, &r.fetch_from);
+    r.group = layout == OUT_FUSED ? rows_walked_together(r.plan, (uint32_t)r.plan.tiles_n_per_tensor * n_tensors, r.workers, r.fetchers > 0) : 8u;
+    r.layout = layout;
+    if (layout == OUT_FUSED && !quad_pairs) r.layout = OUT_FUSED_ANY;
+    else if (r.plan.ring_kernel && streams_outputs(shape, layout, r.plan, r.n_tiles <= r.workers))
+        r.layout = layout == OUT_FUSED ? OUT_FUSED_STREAMED : OUT_CHUNKS_STREAMED;
+    return r;
 }
 
 }  // namespace cocodiff
@@ -560,7 +570,7 @@ static int proj_launch(const cocodiff_shape* shape, const cocodiff_bf16* x,
     a.n_tiles = (int32_t)route.n_tiles;
     a.workers = route.workers;
     a.fetch_from = route.fetch_from;
-    a.group = layout == OUT_FUSED ? rows_walked_together(plan, (uint32_t)a.tiles_n_per_tensor * a.n_tensors, a.workers) : 8u;
+    a.group = route.group;
     // (dividend x divisor below 2^32, as the multiply-high division needs: a weight of more than 2^19 features squared is no
     // memory's)
     a.div_row8 = make_divisor(a.row8);
@@ -726,7 +736,7 @@ extern "C" int cocodiff_qkv_proj_plan(const cocodiff_shape* shape, int32_t n_ten
 }
 
 extern "C" int cocodiff_qkv_proj_route(const cocodiff_shape* shape, int32_t n_tensors, int32_t form, int32_t* tile_tokens, int32_t* tile_features,
-                                       int32_t* n_tiles, int32_t* fetching, int32_t* fetch_from, int32_t* streamed) {
+                                       int32_t* n_tiles, int32_t* fetching, int32_t* fetch_from, int32_t* streamed, int32_t* rows_together) {
     int rc = check_shape(shape);
     if (rc != COCODIFF_OK) return rc;
     if (n_tensors < 1 || n_tensors > 3) return fail(COCODIFF_ERR_SHAPE, "qkv_proj_route: n_tensors (%d) must be 1, 2 or 3", n_tensors);
@@ -742,5 +752,6 @@ extern "C" int cocodiff_qkv_proj_route(const cocodiff_shape* shape, int32_t n_te
     if (fetching) *fetching = (int32_t)r.fetchers;
     if (fetch_from) *fetch_from = (int32_t)r.fetch_from;
     if (streamed) *streamed = r.layout == OUT_CHUNKS_STREAMED || r.layout == OUT_FUSED_STREAMED;
+    if (rows_together) *rows_together = (int32_t)r.group;
     return COCODIFF_OK;
 }

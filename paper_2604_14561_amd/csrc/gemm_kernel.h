@@ -666,9 +666,9 @@ __device__ __forceinline__ const GemmArgs& arguments_again() {
 // 27 launches of one round, 240 .. 3632 tokens x 1024 .. 3072 features, one to three weights, plain and fused, against no fetching, without
 // the question and with it: all on chip 2.0 % more (10 % at most) and 0.5 %; buffers of about the last-level cache's size in turn 10.7 and
 // 9.4 % less; from memory 9.8 and 10.1 % less.
-// Whole layers in one call (12, 256 .. 2304 tokens x 1408 .. 3072 features), asked and left above 0.42, 0.46 or 0.50 us: all on chip 2.0 % more
-// without the question, 1.4, 0.7 and 0.4 % with it (at worst 5 to 8 %, and 2 to 7 %: 1152 x 2048); around the cache's size 13 % less, 9, 5 and 4 %:
-// what is missing there comes in 0.44 to 0.5 us too, since memory has little to do; from memory 11 % less with any.  Leaving where one, two
+// Whole layers in one call (11, 256 .. 2304 tokens x 1408 .. 3072 features), asked and left below 0.42, 0.46 or 0.50 us: all on chip 1.4 % more
+// without the question, 1.0, 0.6 and 0.3 % with it (2.9 % at most, and 2.4, 2.1, 1.8); around the cache's size 13 % less, 9, 5 and 4 %:
+// what is missing there comes in 0.44 to 0.5 us too, since memory has little to do; from memory 12 % less with any.  Leaving where one, two
 // or three of the four wavefronts stay below 0.34 to 0.42 us, or samples spread over all rows, lie between the same two ends.
 constexpr uint32_t kFetchLines = 8;      // a column: 8 lines of every row, 8 K steps
 constexpr uint32_t kOnChip = 42;         // of the 100 MHz clock

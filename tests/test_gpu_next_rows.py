@@ -1383,6 +1383,26 @@ def test_proj_fetched_operands_cold_and_on_chip(N, H, d, P, rank):
         assert all(torch.equal(a, b) for a, b in zip(out, got[0]))
 
 
+# Launches of one round with fetching workgroups whose tile rows leave some over from groups of 8: 9 rows (once the last is ragged) and 10;
+# 8 rows, no fetching workgroups, and the plain form keep groups of 8.
+@gpu
+@pytest.mark.parametrize("form,N,H,d,rows_together", [
+    ("fused_select", 1152, 16, 128, 9), ("fused", 1136, 32, 64, 9), ("fused", 1520, 16, 64, 5), ("fused_select", 1856, 8, 128, 5),
+    ("fused", 1024, 18, 128, 8), ("fused", 3600, 18, 64, 8), ("proj", 1152, 16, 128, 8),
+])
+def test_proj_route_rows_walked_together(form, N, H, d, rows_together):
+    route = cd.binding.qkv_proj_route(cd.Shape.make(N, H * d, H, d, 1), 3, form)
+    print(form, N, H * d, route, flush=True)
+    if cd.qkv_proj_plan(cd.Shape.make(N, H * d, H, d, 1), 3)["compute_units"] == 256:
+        assert route["rows_together"] == rows_together
+
+
+@gpu
+@pytest.mark.parametrize("bm,bn,N,H,d", [(128, 256, 1152, 16, 128), (128, 256, 1136, 32, 64), (160, 128, 1520, 16, 64), (192, 128, 1856, 8, 128)])
+def test_proj_fused_rows_walked_together_in_one_round(oracle, bm, bn, N, H, d):
+    test_proj_fused_select_every_tile_shape(oracle, bm, bn, N, H, d)
+
+
 @gpu
 @pytest.mark.parametrize("bm,bn,N,H,d", [
     (224, 128, 1872, 9, 128), (224, 128, 1904, 17, 64), (192, 128, 1584, 9, 128), (192, 128, 1632, 17, 64), (160, 128, 1296, 9, 128),
