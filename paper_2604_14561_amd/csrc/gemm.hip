@@ -351,12 +351,12 @@ static bool streams_outputs(const cocodiff_shape* shape, OutLayout layout, const
 // step's loads take as long as its products: tiles of 288 x 192, 224 x 256 and 256 x 256 are -1 to +2 % with them, 192 x 256 -2 to -7 %.
 // The tiles read the first column themselves meanwhile (from column 0 on: 4 launches of 12 slower by 10 to 13 %).  Where a column takes
 // the fetching units longer than the tiles, they begin further on, so that they are caught up with at the end only (768 x 3072, two
-// weights, 16 units: 37.0 us from column 0 on, 33.5 from 1, 31.9 from 2).  Their rate is taken a sixth below kBytesPerClock: fetching
+// weights, 16 units: 37.0 us from column 0 on, 33.5 from 1, 31.9 from 2).  Their rate is taken a tenth below kBytesPerClock: fetching
 // units that the tiles overtake cost more than they give (432 x 2176, two weights, 18 units: 18.2 us from column 1 on, 15.9 from 2, 17.9
-// without any; on chip 14.5, 12.9 and 12.8; fused 256 x 3072, three weights, 32 units: 29.8 from 1, 28.6 from 2, 30.1 without; 27 launches
-// from memory 9.2 % less than without any at the full rate and 10.1 % so).
+// without any; on chip 14.5, 12.9 and 12.8; fused 256 x 3072, three weights, 32 units: 29.8 from 1, 28.6 from 2, 30.1 without; a
+// sixth lower 768 x 3072, two weights, begins from 3: 34.8 alone for 35.4 from 2, but with the rank's other calls 68.5 for 67.7).
 // Cold, without and with: 70 launches of one round, 112 .. 9968 tokens x 768 .. 3072 features, one to three weights: 7 % less on average
-// (11 % up to 768 tokens), 25 % at most, 1 % more at worst.  With everything on chip already most leave at once (fetch_operands).
+// (11 % up to 768 tokens), 25 % at most, 1 % more at worst.  (With everything on chip already: fetch_operands.)
 // They hold units that another stream's kernel could take meanwhile; what both take together gets shorter all the same (projections of 9
 // shapes and permutations side by side, cold, without and with: 768 x 3072, two weights 40.5 and 38.2 us, 1552 x 3072 40.3 and 34.7, 3152 x 1536
 // 25.6 and 23.4, 1232 x 1152, three weights 20.1 and 19.6; none longer).
@@ -369,7 +369,7 @@ static uint32_t fetching_workgroups(const LaunchPlan& p, int32_t M, int32_t D, i
     const double products = tile_mfmas(*p.pick) * 17.2 + 60.0, loads = tile_operand_bytes(*p.pick) / kBytesPerClock;
     if (products > 1.13 * loads) return 0;
     const uint32_t fetchers = std::min(units - n_tiles, kAtMost);
-    const double column = ((double)M + (double)n_tensors * D) * kFetchLines * BK * 2.0 / (fetchers * kBytesPerClock / 1.2);
+    const double column = ((double)M + (double)n_tensors * D) * kFetchLines * BK * 2.0 / (fetchers * kBytesPerClock / 1.1);
     const int columns = (D / BK + kFetchLines - 1) / kFetchLines;
     *from = (uint32_t)std::max(1, (int)(columns * (1.0 - kFetchLines * std::max(products, loads) / column) + 0.5));
     return fetchers;
@@ -392,7 +392,7 @@ static uint32_t fetching_workgroups(const LaunchPlan& p, int32_t M, int32_t D, i
 // columns: 9 rows of 24 columns give it 25 panels of W and the others 3.5, it is the last to end, and fetching workgroups on it
 // take from what it waits for.  So a launch with fetching workgroups and more than 8 rows takes the size with the fewest operand rows for
 // the XCD that has most, if that is a twentieth less.  The whole call, 8 rows / so, on chip and from memory: 1152 x 2048 38.0 / 35.9 and 42.0 /
-// 39.7 us, 1520 x 1024 19.8 / 19.2 and 22.0 / 21.7, 1088 x 2304 42.5 / 41.3 and 45.4 / 45.0; 16 others -3.6 to +0.2 %.  (28 launches without
+// 39.7 us, 544 x 2176 32.5 / 26.0 and 34.7 / 33.5, 1520 x 1024 19.8 / 19.2 and 22.0 / 21.7, 1088 x 2304 42.5 / 41.3 and 45.4 / 45.0; 16 others -3.6 to +0.2 %.  (28 launches without
 // fetching workgroups: -3 to +1.5 %, so they stay.)
 static uint32_t rows_walked_together(const LaunchPlan& p, uint32_t tiles_n, uint32_t workgroups, bool fetching) {
     const uint32_t tiles_m = (uint32_t)p.tiles_m;

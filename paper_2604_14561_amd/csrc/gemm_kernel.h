@@ -657,46 +657,20 @@ __device__ __forceinline__ const GemmArgs& arguments_again() {
 // other calls of that rank, 72.8 -> 67.7 us; the latter launch alone 38.4 -> 31.9, 29.4 with everything on chip.
 // By XCD, each fetching what its own units read into its L2, is slower than none: three to seven times the lines, and a unit
 // takes some 37 bytes a clock whoever it reads for.
-// Where the operands are on chip already -- the same weights again, with less than the last-level cache in between -- fetching only
-// takes bandwidth from the tiles.  So each wavefront first asks for 32 lines that nobody has come to yet, 16 of the weights and 16 of x, and
-// the workgroup leaves if all its wavefronts had theirs within 0.42 us: such a load takes 0.28 to 0.44 us from the last-level cache,
-// 0.44 to 0.8 if some of it comes from memory.  As many lines, of both operands and by vote, since a workgroup that leaves takes its
-// share of the rows away and the tiles then wait at every step for the few lines that are missing: one line per wavefront kept half
-// of the gain, 16 of one weight none of it where a tenth of the operands had left the cache.
-// 27 launches of one round, 240 .. 3632 tokens x 1024 .. 3072 features, one to three weights, plain and fused, against no fetching, without
-// the question and with it: all on chip 2.0 % more (10 % at most) and 0.5 %; buffers of about the last-level cache's size in turn 10.7 and
-// 9.4 % less; from memory 9.8 and 10.1 % less.
-// Whole layers in one call (11, 256 .. 2304 tokens x 1408 .. 3072 features), asked and left below 0.42, 0.46 or 0.50 us: all on chip 1.4 % more
-// without the question, 1.0, 0.6 and 0.3 % with it (2.9 % at most, and 2.4, 2.1, 1.8); around the cache's size 13 % less, 9, 5 and 4 %:
-// what is missing there comes in 0.44 to 0.5 us too, since memory has little to do; from memory 12 % less with any.  Leaving where one, two
-// or three of the four wavefronts stay below 0.34 to 0.42 us, or samples spread over all rows, lie between the same two ends.
+// Where the operands are on chip already -- the same weights again, with less than the last-level cache in between -- fetching takes
+// bandwidth from the tiles for nothing.  Whole layers in one call (11, 256 .. 2304 tokens x 1408 .. 3072 features), without and with it: all on
+// chip 1.4 % more (3 to 5 % at most), around the cache's size 13 % less, from memory 12 % less.  A workgroup cannot tell which it is: asked for 128
+// lines, of which it leaves if all come within 0.42 us, 1.0, -9 and -12 %, within 0.50 us 0.3, -4 and -12 %; a load takes 0.28 to 0.44 us
+// from the last-level cache under load, and 0.44 to 0.5 from memory that has little else to do, while a tenth of the lines missing makes the
+// tiles wait at every step.  (Votes of a workgroup's wavefronts and samples spread over all rows: between the same ends.  Resting 512 to
+// 2048 clocks between batches of four loads: the same on chip, 0 to 5 % more from memory.)
 constexpr uint32_t kFetchLines = 8;      // a column: 8 lines of every row, 8 K steps
-constexpr uint32_t kOnChip = 42;         // of the 100 MHz clock
 __device__ __forceinline__ void fetch_operands(const GemmArgs& a) {
     constexpr uint32_t kLine = BK * 2, kRows = 64 / kFetchLines, kInFlight = 16;
     const uint32_t K = (uint32_t)a.D, row_lines = K * 2u / kLine, rows = (uint32_t)a.M + (uint32_t)a.n_tensors * K;
     const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = (gridDim.x - a.workers) * 4u;
     const uint32_t blocks = (rows + kRows - 1u) / kRows, columns = (row_lines + kFetchLines - 1u) / kFetchLines;
     uint32_t block = (blockIdx.x - a.workers) * 4u + wave, column = a.fetch_from;      // a load: one column of kRows rows
-    {
-        extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-        const uint32_t i = block * 64u + (lane & 15u), xi = i % (uint32_t)a.M, wi = i % ((uint32_t)a.n_tensors * K);
-        const uint16_t* row = lane & 16u     ? a.x + ((size_t)a.row_begin + xi) * K
-                              : wi < K       ? a.w[0] + (size_t)wi * K
-                              : wi < 2u * K  ? a.w[1] + (size_t)(wi - K) * K
-                                             : a.w[2] + (size_t)(wi - 2u * K) * K;
-        const uint32_t line = kFetchLines + ((lane & 15u) + block) % (row_lines - kFetchLines);
-        const auto* sample = (const __attribute__((address_space(1))) uint32_t*)(row + line * BK);
-        asm volatile("" : "+v"(sample));      // (its address is formed in front of the first look at the clock, and the load stays behind it)
-        const uint64_t asked = __builtin_amdgcn_s_memrealtime();
-        asm volatile("" : "+v"(sample));
-        asm volatile("" ::"v"(*sample));
-        const uint32_t took = (uint32_t)(__builtin_amdgcn_s_memrealtime() - asked);
-        uint32_t* longest = reinterpret_cast<uint32_t*>(smem);
-        if (lane == 0) longest[wave] = took;
-        __syncthreads();
-        if (max(max(longest[0], longest[1]), max(longest[2], longest[3])) < kOnChip) return;
-    }
     while (column < columns) {
         uint32_t got[kInFlight] = {};
 #pragma unroll

@@ -1333,7 +1333,7 @@ def test_proj_route_streamed_outputs(form, N, H, d, P, ranks, streamed):
 @gpu
 @pytest.mark.parametrize("form,N,H,d,P,ranks,n_tensors,fetching,fetch_from", [
     ("proj", 7904, 13, 64, 1, 1, 1, 8, 1), ("proj", 416, 13, 64, 1, 1, 3, 32, 1), ("proj", 768, 48, 64, 1, 1, 3, 16, 3),
-    ("pack", 432, 17, 128, 1, 1, 2, 18, 2), ("fused", 768, 24, 128, 1, 1, 2, 16, 3), ("fused", 9216, 24, 128, 12, 1, 2, 16, 3),
+    ("pack", 432, 17, 128, 1, 1, 2, 18, 2), ("fused", 768, 24, 128, 1, 1, 2, 16, 2), ("fused", 9216, 24, 128, 12, 1, 2, 16, 2),
     ("pack", 9216, 24, 128, 12, 1, 1, 32, 1), ("fused_select", 256, 24, 128, 2, 2, 3, 32, 1), ("fused", 256, 24, 128, 2, 2, 3, 32, 2),
     ("proj", 7904, 12, 64, 1, 1, 1, 0, 0), ("fused_select", 896, 24, 128, 1, 1, 3, 0, 0), ("proj", 96, 13, 64, 1, 1, 1, 0, 0),
     ("pack", 9216, 24, 128, 12, 12, 3, 0, 0), ("proj", 3152, 12, 128, 1, 1, 3, 0, 0),
@@ -1353,8 +1353,8 @@ def test_proj_units_without_a_tile(oracle, bm, bn, N, H, n_tensors):
     test_proj_every_tile_shape(oracle, bm, bn, N, H, n_tensors)
 
 
-# Fetching workgroups leave where the operands are on chip: the same bits with operands that come from memory, where they stay, and with
-# operands that the call before has just read, for all ranks and for a rank in the middle, plain and fused.
+# Launches with fetching workgroups: the same bits with operands that come from memory and with operands that the call before has just
+# read, for all ranks and for a rank in the middle, plain and fused.
 @gpu
 @pytest.mark.parametrize("N,H,d,P,rank", [(416, 13, 64, 1, 0), (768, 24, 128, 1, 0), (9216, 24, 128, 12, 7), (3152, 12, 128, 1, 0)])
 def test_proj_fetched_operands_cold_and_on_chip(N, H, d, P, rank):
